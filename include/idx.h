@@ -76,7 +76,8 @@ typedef void *idx_stream;             /* hipStream_t */
  * pointer (256-byte aligned) or NULL; release(ctx, ptr, stream) frees it.
  * Both must be stream-ordered with respect to `stream`: a buffer released on
  * a stream may be reused only by work enqueued after the release.  Passing
- * NULL selects hipMallocAsync / hipFreeAsync on the call's stream.
+ * NULL selects hipMallocAsync / hipFreeAsync on the call's stream, with up to
+ * 8 GiB of freed blocks per device kept mapped for later calls.
  */
 typedef struct idx_allocator {
     void *(*alloc)(void *ctx, size_t bytes, idx_stream stream);

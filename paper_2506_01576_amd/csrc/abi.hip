@@ -16,42 +16,19 @@ int hip_fail(hipError_t e) {
 void *Alloc::get(size_t bytes, hipStream_t s) const {
     if (bytes == 0) bytes = 256;
     if (custom) return a.alloc(a.ctx, bytes, (idx_stream)s);
-    void *p = nullptr;
-    const hipError_t e = hipMallocAsync(&p, bytes, s);
-    if (e != hipSuccess) {
-        g_last_hip = (int)e;
-        (void)hipGetLastError();
-        return nullptr;
-    }
+    hipError_t e = hipSuccess;
+    void *p = cached_get(bytes, s, &e);
+    if (!p) g_last_hip = (int)e;
     return p;
 }
 
 void Alloc::put(void *p, hipStream_t s) const {
     if (!p) return;
     if (custom) a.release(a.ctx, p, (idx_stream)s);
-    else (void)hipFreeAsync(p, s);
+    else cached_put(p, s);
 }
 
 namespace {
-
-// Keep freed stream-ordered memory in the device pool instead of returning it
-// to the driver, so repeated builds and range calls do not pay for mapping.
-void tune_pool_once() {
-    static thread_local int done_dev = -1;
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess) {
-        (void)hipGetLastError();
-        return;
-    }
-    if (done_dev == dev) return;
-    hipMemPool_t pool;
-    if (hipDeviceGetDefaultMemPool(&pool, dev) == hipSuccess) {
-        uint64_t thr = ~0ull;
-        (void)hipMemPoolSetAttribute(pool, hipMemPoolAttrReleaseThreshold, &thr);
-    }
-    (void)hipGetLastError();
-    done_dev = dev;
-}
 
 int cu_count_of_current_device() {
     int dev = 0, cus = 0;
@@ -170,7 +147,6 @@ int new_handle(uint64_t n, int layout, uint32_t k, uint32_t flags, const idx_all
         delete h;
         return alloc ? IDX_ERR_NOMEM : hip_fail((hipError_t)g_last_hip);
     }
-    if (!alloc) tune_pool_once();
     if (h->row_bytes) {
         h->rowids = (uint32_t *)h->alloc.get(h->row_bytes, s);
         if (!h->rowids) {

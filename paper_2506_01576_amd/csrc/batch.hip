@@ -1116,7 +1116,9 @@ int idx_batch_mixed(idx_batch_t b, uint64_t m, const void *lo, const void *hi, c
     const uint64_t parts = scan_partials_for(m);
     char *tmp = nullptr;
     const size_t first_b = ((size_t)m * 4 + 255) & ~(size_t)255;
-    IDX_HIP(hipMallocAsync((void **)&tmp, first_b + parts * 8, s));
+    hipError_t me = hipSuccess;
+    tmp = (char *)cached_get(first_b + parts * 8, s, &me);
+    if (!tmp) return hip_fail(me);
     uint32_t *first = (uint32_t *)tmp;
     uint64_t *partial = (uint64_t *)(tmp + first_b);
     const uint32_t grid = (uint32_t)b->cu_count * 8;
@@ -1166,7 +1168,7 @@ int idx_batch_mixed(idx_batch_t b, uint64_t m, const void *lo, const void *hi, c
         }
         if (hipGetLastError() != hipSuccess) rc = IDX_ERR_HIP;
     } while (0);
-    (void)hipFreeAsync(tmp, s);
+    cached_put(tmp, s);
     return rc;
 }
 

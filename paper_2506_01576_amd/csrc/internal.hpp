@@ -41,6 +41,11 @@ struct Alloc {
     void put(void *p, hipStream_t s) const;
 };
 
+// ---- devmem.hip: the default allocator (hipMallocAsync / hipFreeAsync behind
+// a bounded cache of freed blocks, stream-ordered like them)
+void *cached_get(size_t bytes, hipStream_t s, hipError_t *err);
+void cached_put(void *p, hipStream_t s);
+
 struct LearnedModel;  // learned rank model (learned.hip)
 
 }  // namespace idx
