@@ -88,7 +88,7 @@ typedef struct idx_allocator {
 /*
  * idx_build -- build a static index over n (key, rowid) pairs.
  *
- * Sorts the pairs by key with a stable LSD radix sort (Section 3: the BS
+ * Sorts the pairs by key with a stable radix sort (Section 3: the BS
  * index is a key-value sort; equal keys keep their input order), then for
  * IDX_EBS / IDX_EKS rearranges the sorted array into Eytzinger order with one
  * read and one write per element, in rank order: the thread of sorted rank r

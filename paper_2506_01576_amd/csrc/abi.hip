@@ -233,11 +233,9 @@ int idx_build(const void *keys, const uint32_t *rowids, uint64_t n, int layout, 
         hipError_t e = hipMemsetAsync(dflags, 0, 2 * sizeof(uint32_t), s);
         if (e != hipSuccess) { rc = hip_fail(e); break; }
         (void)hipEventRecord(ev[0], s);
-        rc = sort_pairs(keys, rowids, n, h->u64, sk, sr, sort_tmp, s);
+        rc = sort_pairs(keys, rowids, n, h->u64, sk, sr, sort_tmp, dflags, s);
         if (rc != IDX_OK) break;
         (void)hipEventRecord(ev[1], s);
-        rc = check_sorted(sk, sr, n, h->u64, dflags, s);
-        if (rc != IDX_OK) break;
         if (!direct) {
             rc = build_layout(h, sk, sr, s);
             if (rc != IDX_OK) break;

@@ -93,11 +93,12 @@ namespace idx {
 // ---- sort.hip ---------------------------------------------------------------
 // Bytes of temporary device memory sort_pairs needs for n keys.
 size_t sort_temp_bytes(uint64_t n, bool u64);
-// Stable LSD radix sort of (key, rowid) by key.  in_* are read only; the
-// result is written to out_*; temp holds sort_temp_bytes(n, u64) bytes.
-// Synchronises `s` once (to decide which digit passes can be skipped).
+// Stable sort of (key, rowid) by key.  in_* are read only; the result is
+// written to out_*; temp holds sort_temp_bytes(n, u64) bytes.  flags (device,
+// zeroed, or nullptr): check_sorted's findings on the result.  Synchronises
+// `s` to choose the sort's form (not for sets that fit one workgroup).
 int sort_pairs(const void *keys_in, const uint32_t *rows_in, uint64_t n, bool u64, void *keys_out,
-               uint32_t *rows_out, void *temp, hipStream_t s);
+               uint32_t *rows_out, void *temp, uint32_t *flags, hipStream_t s);
 
 // ---- layout.hip -------------------------------------------------------------
 // Fills the layout buffers of h from the sorted arrays (permutation for
