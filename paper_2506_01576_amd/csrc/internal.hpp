@@ -75,8 +75,6 @@ struct idx_index {
     int cu_count = 256;
     size_t lds_max = 64 * 1024;  // LDS bytes one workgroup may use on this device
     idx::LearnedModel *learned = nullptr;  // attached rank model (BS layout only)
-    void *split = nullptr;       // rank-bucket splitter keys for partitioned lookups
-    uint32_t split_buckets = 0;  // buckets those splitters define (0 = none built)
     // Leaf-line buffer of the model a re-training replaced, kept for the new
     // model's lines when the leaf count is the same (a fresh buffer of that
     // size costs a mapping of device memory on every re-training).
@@ -123,14 +121,6 @@ struct PointIO {
     uint32_t *out;
     bool local_sort;       // sort each tile of lookups in LDS first (Section 7.4)
     bool xcd;              // walk tiles XCD by XCD
-    // a batch partitioned by rank bucket: the bucket of every lookup, and the
-    // rank interval [start(b), start(b) + span] that holds the lower bound of
-    // a key of bucket b, start(b) = b * step + (b > 0) (sorted array only)
-    const uint16_t *bkt = nullptr;
-    uint64_t bstep = 0;
-    uint64_t bspan = 0;
-    // answer of lookup i goes to out[pos[i]] (nullptr: out[i])
-    const uint32_t *pos = nullptr;
 };
 int point_lookup(idx_index *h, const void *q, uint64_t m, uint32_t *out, hipStream_t s);
 // One launch of the handle's point-lookup form over `io`.
@@ -145,24 +135,22 @@ uint32_t pin_entries_for(const idx_index *h, uint32_t levels);
 // ---- reorder.hip ------------------------------------------------------------
 // Point lookups on a batch partitioned by rank bucket first.
 int point_partitioned(idx_index *h, const void *q, uint64_t m, uint32_t *out, hipStream_t s);
-void drop_splitters(idx_index *h, hipStream_t s);
-// The partition for other lookups: one chunk of m <= 2^31 query keys
-// partitioned by rank bucket (keys q and batch positions pos, both in
-// partitioned order); the caller writes each answer at its position.
-struct PartView {
-    const void *q;
-    const uint32_t *pos;
-    uint64_t m;
-    void *scratch;
-    const uint16_t *bkt;  // bucket of every entry (partitioned order)
-    uint64_t bstep;       // ranks per bucket; lower bounds of bucket b lie in
-    uint64_t bspan;       // [b * bstep + (b > 0), that + bspan]
-};
-// Rank interval that holds the lower bound of a key of bucket b.
-__host__ __device__ inline uint64_t bucket_start(uint64_t b, uint64_t step) { return b ? b * step + 1 : 0; }
 constexpr uint64_t kPartChunk = 1ull << 31;
-size_t partition_scratch_bytes(const idx_index *h, uint64_t m);
-int partition_forward(idx_index *h, const void *q, uint64_t m, void *scratch, PartView *out, hipStream_t s);
+// The partition for range counts, by the ranges' lower bounds: one chunk of
+// m <= kPartChunk ranges.  `packed` receives every range's (first rank << 32
+// | count) in partitioned order, here (counted, the sorted array) or from the
+// caller; range_partition_back brings the words to the ranges' positions.
+struct RangePart {
+    const void *lo, *hi;  // bounds in partitioned order
+    uint64_t *packed;
+    const uint32_t *place;
+    bool counted;
+};
+bool range_partition_pays(const idx_index *h, uint64_t m);  // m: ranges of one chunk
+size_t range_partition_bytes(const idx_index *h, uint64_t m);
+int range_partition(idx_index *h, const void *lo, const void *hi, uint64_t m, void *scratch, RangePart *out,
+                    hipStream_t s);
+int range_partition_back(const RangePart &v, uint64_t m, uint64_t *packed, hipStream_t s);
 
 // ---- range.hip --------------------------------------------------------------
 // Exclusive scan of v[0..m) in place, v[m] = total; partial holds

@@ -1055,7 +1055,7 @@ __global__ __launch_bounds__(256) void k_point_lines_pair(Load<K, AOS> keys, uin
         for (int r = 0; r < R; ++r) {
             const uint64_t qi = t0 + (uint64_t)r * pairs + pi;
             if (big[r] && hf == 0) res[r] = window_find_call<K, AOS>(keys, n, b[r], len[r], x[r], TWO);
-            if (v[r] && hf == (big[r] ? 0u : 1u)) io.out[io.pos ? io.pos[qi] : qi] = res[r];
+            if (v[r] && hf == (big[r] ? 0u : 1u)) io.out[qi] = res[r];
         }
     }
 }
@@ -1107,7 +1107,6 @@ QueryIO<KT> lines_io(const idx_index *h, const PointIO &pio, uint64_t tile, uint
     io.xcd = pio.xcd ? 1u : 0u;
     io.sort_off = 0;
     io.rounds = h->params.window_rounds == 1 ? 1u : 2u;
-    io.pos = pio.pos;
     set_tiles(io, tile);
     uint64_t g = io.iters;
     if (h->params.persistent) {
@@ -1216,7 +1215,6 @@ int point_learned(idx_index *h, const PointIO &pio, hipStream_t s) {
         io.xcd = pio.xcd ? 1u : 0u;                                                                         \
         io.sort_off = 0;                                                                                    \
         io.rounds = h->params.window_rounds == 1 ? 1u : 2u;                                                 \
-        io.pos = pio.pos;                                                                                   \
         set_tiles(io, tile);                                                                                \
         uint64_t grid = io.iters;                                                                           \
         if (h->params.persistent) {                                                                         \

@@ -71,17 +71,7 @@ __global__ __launch_bounds__(1024) void k_point_bs(PointArgs<K, AOS> a) {
 #pragma unroll
         for (int r = 0; r < R; ++r) base[r] = 0;
         uint64_t len = n;
-        if (!SORT && a.io.bkt) {
-            // partitioned batch: each lookup's bucket bounds its lower bound,
-            // so the search starts inside that bucket's rank interval (the
-            // steps above it are the same for the whole bucket)
-#pragma unroll
-            for (int r = 0; r < R; ++r) {
-                const uint64_t qi = t0 + src_of<R, SORT>(src, r);
-                base[r] = qi < a.io.m ? bucket_start(a.io.bkt[qi], a.io.bstep) : 0;
-            }
-            len = a.io.bspan;
-        } else if (a.pin_levels) {
+        if (a.pin_levels) {
             uint32_t v[R];
 #pragma unroll
             for (int r = 0; r < R; ++r) v[r] = 1;
@@ -255,7 +245,7 @@ __global__ __launch_bounds__(1024) void k_point_eks_group(PointArgs<K, AOS> a) {
 #pragma unroll
             for (int r = 0; r < R; ++r) {
                 const uint64_t qi = wbase + (uint64_t)r * GPW + grp;
-                if (qi < a.io.m) a.io.out[a.io.pos ? a.io.pos[qi] : qi] = ceq[r] ? a.L.row(cand[r]) : kMiss;
+                if (qi < a.io.m) a.io.out[qi] = ceq[r] ? a.L.row(cand[r]) : kMiss;
             }
         }
     }
@@ -350,7 +340,7 @@ __global__ __launch_bounds__(1024) void k_point_eks_vgroup(PointArgs<K, AOS> a) 
 #pragma unroll
             for (int r = 0; r < R; ++r) {
                 const uint64_t qi = wbase + (uint64_t)r * GPW + grp;
-                if (qi < a.io.m) a.io.out[a.io.pos ? a.io.pos[qi] : qi] = ceq[r] ? a.L.row(cand[r]) : kMiss;
+                if (qi < a.io.m) a.io.out[qi] = ceq[r] ? a.L.row(cand[r]) : kMiss;
             }
         }
     }
@@ -453,10 +443,6 @@ PointArgs<K, AOS> make_args(const idx_index *h, const PointIO &io, uint32_t pin_
     a.io.local_sort = io.local_sort ? 1u : 0u;
     a.io.xcd = io.xcd ? 1u : 0u;
     a.io.rounds = h->params.window_rounds == 1 ? 1u : 2u;
-    a.io.pos = io.pos;
-    a.io.bkt = io.bkt;
-    a.io.bstep = io.bstep;
-    a.io.bspan = io.bspan;
     a.pin = (const K *)h->pin;
     a.pin_entries = pin_levels ? h->pin_keys : 0;
     a.pin_levels = pin_levels;
@@ -654,9 +640,8 @@ int resolve_params(const idx_index *h, const idx_lookup_params *in, idx_lookup_p
     if (p.lds_levels > max_levels) return IDX_ERR_ARG;
     if (p.persistent > 64) return IDX_ERR_ARG;
     // lookup reordering: 0 = none; 1 = sort each tile of block * per_lane
-    // lookups in LDS (one lookup per lane only); 2 = partition the batch by
-    // rank bucket first, answers returned by two counting passes; 3 = the
-    // same partition, each answer written straight to its position
+    // lookups in LDS (one lookup per lane only); 2 and 3 = partition the batch
+    // by rank bucket first
     if (p.reorder > 3) return IDX_ERR_ARG;
     if (p.reorder == 1) {
         const uint64_t T = (uint64_t)p.block * p.per_lane;

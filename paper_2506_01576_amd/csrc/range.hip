@@ -183,91 +183,53 @@ __global__ __launch_bounds__(256) void k_range_count(RangeArgs<K, AOS> a) {
 }
 
 // The same on a batch of ranges partitioned by the rank bucket of their
-// lower bounds (lookup parameter reorder = 2): entry j holds lower bound
-// q2[j] of the range at batch position pos[j], whose upper bound is read
-// there (reading the upper bounds into partitioned order first, in a kernel
-// of their own, cost more).  The tiles are walked XCD by XCD, so the ranges one XCD has in
+// lower bounds (lookup parameter reorder = 2) on the Eytzinger layouts (the
+// sorted array's form is k_part_range_bs): bounds lo and hi in partitioned
+// order.  The tiles are walked XCD by XCD, so the ranges one XCD has in
 // flight fall in a few buckets whose slice of the index stays in its L2.
-// Both ranks go out in partitioned order, one 8-byte pair per range;
-// k_range_put then writes each range's first rank and count at its position
-// (random writes in a kernel of their own cost less than inside this one,
-// where they slow the searches, or than two placement passes).
-// On the sorted array the lower bound's bucket bounds its rank (see
-// bucket_start): both searches start inside that interval, and the upper
-// bound's search widens to the rest of the array only when its answer is
-// past the interval (a range that leaves the bucket).
+// Both ranks go out as one 8-byte word (first rank << 32 | count; both are
+// below 2^32), which the scan unpacks after they are back in order.
 template <typename K, bool AOS>
-__global__ __launch_bounds__(256) void k_range_count_part(RangeArgs<K, AOS> a, const K *__restrict__ q2,
-                                                          const uint32_t *__restrict__ pos,
-                                                          const uint16_t *__restrict__ bkt, uint64_t bstep,
-                                                          uint64_t bspan, uint64_t ntiles, uint64_t iters,
-                                                          uint2 *__restrict__ ranks) {
-    for (uint64_t it = blockIdx.x; it < iters; it += gridDim.x) {
-        const uint64_t tl = tile_of(it, ntiles, 1);
-        if (tl >= ntiles) continue;
-        const uint64_t j = tl * 256 + threadIdx.x;
-        if (j >= a.m) continue;
-        const K L = q2[j], U = a.hi[pos[j]];
-        uint64_t r0 = 0, r1 = 0;
-        if (a.layout == IDX_BS && L <= U) {
-            const bool top = U == key_max<K>();
-            const K x1 = top ? U : (K)(U + 1);
-            const uint64_t base = bucket_start(bkt[j], bstep);
-            bs_ranks_in(a, base, bspan, L, x1, r0, r1);
-            // the window scan may also count the key at base + bspan, so an
-            // answer past the interval shows as end or end + 1
-            const uint64_t end = base + bspan;
-            if (r1 >= end && end < a.G.n) {
-                uint64_t unused;
-                bs_ranks_in(a, end, a.G.n - end, x1, x1, r1, unused);
-            }
-            if (top) r1 = a.G.n;
-        } else {
-            range_ranks(a, L, U, r0, r1);
-        }
-        ranks[j] = make_uint2((uint32_t)r0, (uint32_t)r1);
-    }
-}
-
-// Each range's first rank and count at its position, packed into one 8-byte
-// word (first rank << 32 | count; both are below 2^32): one random write per
-// range instead of two.  The scan that follows unpacks them.
-__global__ __launch_bounds__(256) void k_range_put(const uint2 *__restrict__ ranks, const uint32_t *__restrict__ pos,
-                                                   uint64_t m, uint64_t *__restrict__ packed) {
-    const uint64_t j = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= m) return;
-    const uint2 r = ranks[j];
-    const uint32_t cnt = r.y > r.x ? r.y - r.x : 0u;
-    packed[pos[j]] = ((uint64_t)r.x << 32) | cnt;
+__global__ __launch_bounds__(256) void k_range_count_part(RangeArgs<K, AOS> a, uint64_t ntiles,
+                                                          uint64_t *__restrict__ packed) {
+    const uint64_t tl = tile_of(blockIdx.x, ntiles, 1);
+    if (tl >= ntiles) return;
+    const uint64_t j = tl * 256 + threadIdx.x;
+    if (j >= a.m) return;
+    uint64_t r0, r1;
+    range_ranks(a, a.lo[j], a.hi[j], r0, r1);
+    packed[j] = (r0 << 32) | (r1 > r0 ? r1 - r0 : 0);
 }
 
 // Counts through the partition: per chunk of at most 2^31 ranges, partition
-// the lower bounds, count in partitioned order, then write each range's
-// packed first rank and count at its position (the scan unpacks them).
+// them by their lower bounds, count in partitioned order, then bring each
+// range's packed first rank and count to its position (the scan unpacks them).
 template <typename K, bool AOS>
 int range_count_partitioned(idx_index *h, const RangeArgs<K, AOS> &a, hipStream_t s) {
     const uint64_t m = a.m;
     const uint64_t chunk = m < kPartChunk ? m : kPartChunk;
-    const size_t pb = (partition_scratch_bytes(h, chunk) + 255) & ~(size_t)255;
-    char *t = (char *)h->alloc.get(pb + (size_t)chunk * 8, s);
+    void *t = h->alloc.get(range_partition_bytes(h, chunk), s);
     if (!t) return IDX_ERR_NOMEM;
-    uint2 *ranks = (uint2 *)(t + pb);  // both ranks of every range, partitioned order
     int rc = IDX_OK;
     for (uint64_t c0 = 0; c0 < m && rc == IDX_OK; c0 += chunk) {
         const uint64_t mc = (m - c0) < chunk ? (m - c0) : chunk;
-        PartView v{};
-        rc = partition_forward(h, a.lo + c0, mc, t, &v, s);
+        RangePart v{};
+        rc = range_partition(h, a.lo + c0, a.hi + c0, mc, t, &v, s);
         if (rc != IDX_OK) break;
-        RangeArgs<K, AOS> b = a;
-        b.hi = a.hi + c0;
-        b.m = mc;
-        const uint64_t tiles = (mc + 255) / 256;
-        const uint64_t iters = ((tiles + kXcds - 1) / kXcds) * kXcds;
-        hipLaunchKernelGGL((k_range_count_part<K, AOS>), dim3((uint32_t)iters), dim3(256), 0, s, b, (const K *)v.q,
-                           v.pos, v.bkt, v.bstep, v.bspan, tiles, iters, ranks);
-        hipLaunchKernelGGL(k_range_put, dim3((uint32_t)tiles), dim3(256), 0, s, (const uint2 *)ranks, v.pos, mc,
-                           a.offsets + c0);
-        if (hipGetLastError() != hipSuccess) rc = IDX_ERR_HIP;
+        if (!v.counted) {
+            RangeArgs<K, AOS> b = a;
+            b.lo = (const K *)v.lo;
+            b.hi = (const K *)v.hi;
+            b.m = mc;
+            const uint64_t tiles = (mc + 255) / 256;
+            hipLaunchKernelGGL((k_range_count_part<K, AOS>), dim3((uint32_t)((tiles + kXcds - 1) / kXcds * kXcds)),
+                               dim3(256), 0, s, b, tiles, v.packed);
+            if (hipGetLastError() != hipSuccess) {
+                rc = IDX_ERR_HIP;
+                break;
+            }
+        }
+        rc = range_partition_back(v, mc, a.offsets + c0, s);
     }
     h->alloc.put(t, s);
     return rc;
@@ -417,7 +379,7 @@ __device__ __forceinline__ uint64_t block_scan_u64(uint64_t v, uint64_t *s_wave,
 }
 
 // PACKED: each value is (first rank << 32 | count) and only the count is
-// summed (k_range_put's words).
+// summed (the partition's words).
 template <bool PACKED>
 __global__ __launch_bounds__(SC_THREADS) void k_scan_reduce(const uint64_t *__restrict__ v, uint64_t m,
                                                             uint64_t *__restrict__ partial) {
@@ -459,7 +421,7 @@ __global__ __launch_bounds__(SC_THREADS) void k_scan_partials(uint64_t *__restri
 }
 
 // Tile-local exclusive scan plus the tile's prefix; writes offsets[m] = total.
-// PACKED: the values are k_range_put's words; the counts are scanned and the
+// PACKED: the values are the partition's words; the counts are scanned and the
 // first ranks written to `first`.
 template <bool PACKED>
 __global__ __launch_bounds__(SC_THREADS) void k_scan_apply(uint64_t *__restrict__ v, uint64_t m,
@@ -525,7 +487,7 @@ __global__ __launch_bounds__(SC_THREADS) void k_scan_apply(uint64_t *__restrict_
 }
 
 // Exclusive scan of v[0, m) in place, v[m] = total.  With `first`, v holds
-// k_range_put's packed words: the counts are scanned and the first ranks go
+// the partition's packed words: the counts are scanned and the first ranks go
 // to first[0, m).
 int exclusive_scan(uint64_t *v, uint64_t m, uint64_t *partial, hipStream_t s, uint32_t *first = nullptr) {
     const uint64_t tiles = (m + SC_TILE - 1) / SC_TILE;
@@ -567,7 +529,7 @@ int range_t(idx_index *h, const void *lo, const void *hi, uint64_t m, uint64_t *
     uint64_t *partial = (uint64_t *)(scratch + rank_bytes);
     int rc = IDX_OK;
     uint64_t tot = 0;
-    bool packed = false;  // offsets hold k_range_put's packed words
+    bool packed = false;  // offsets hold the partition's packed words
     const uint32_t blocks = (uint32_t)((m + 255) / 256);
     do {
         if (h->learned && h->params.model != 2) {
@@ -575,7 +537,7 @@ int range_t(idx_index *h, const void *lo, const void *hi, uint64_t m, uint64_t *
             // exist already (writing them would allocate)
             rc = range_count_learned(h, lo, hi, m, a.first_rank, offsets, given == nullptr, s);
             if (rc != IDX_OK) break;
-        } else if (h->params.reorder >= 2 && !given && h->n >= 4) {
+        } else if (h->params.reorder >= 2 && !given && range_partition_pays(h, m < kPartChunk ? m : kPartChunk)) {
             // the caller-given scratch (no-allocation entry point) has no room
             // for the partition: those calls count unpartitioned
             rc = range_count_partitioned(h, a, s);

@@ -7,36 +7,32 @@
 // 768 MiB index costs three to four 128-byte lines that miss L2 (random
 // requests that miss L2 run at ~55 G/s whether the Infinity Cache or HBM
 // serves them), while one XCD's 4 MiB L2 can hold the whole slice of the
-// index that a narrow key range touches.  So the batch is partitioned --
-// counting passes, not a sort -- into B buckets of equal index rank range
-// (about 512 KiB of index each), the lookups walk the partitioned batch XCD
-// by XCD so the buckets one XCD has in flight are few and their lines are
-// reused from its L2, and the answers are carried back to the caller's order.
+// index that a narrow key range touches, and LDS the top of its search.  So
+// the batch is partitioned -- one stable counting pass, not a sort -- into up
+// to 1024 buckets of neighbouring keys, each bucket is searched through a
+// table of its own keys in LDS, and the answers are gathered back.
 //
-// Every scatter below keeps the number of partially written 128-byte lines
-// in flight per XCD well under its L2 (a few dozen output runs per
-// workgroup): an evicted partial line costs HBM a read-modify-write.
+//   1. splitters: NB - 1 index keys, in key order;
+//   2. count: per tile of kPartTile queries, the queries of every bucket (a
+//      table of key cells in LDS, then a search of the few splitters in the
+//      query's cell), as a matrix;
+//   3. scan of the matrix along each bucket;
+//   4. scatter: each tile's queries, put in bucket order in LDS, leave in one
+//      piece per bucket; every query's place goes to `place`, in the caller's
+//      order;
+//   5. lookup: spans of the partitioned batch, walked XCD by XCD so that the
+//      buckets one XCD has in flight fit its L2;
+//   6. gather: out[i] = answer[place[i]].
 //
-//  forward
-//   1. splitters: B - 1 index keys at ranks step, 2 step, ... (step = n / B),
-//      built once per handle and cached;
-//   2. count: every query's fine bucket (a table of key cells in LDS, then
-//      a search of the few splitters in the query's cell), kept as u16, and
-//      per-bucket totals;
-//   3. bucket starts (one workgroup);
-//   4. scatter to B1 coarse buckets (query, batch position, fine bucket);
-//   5. scatter within each coarse bucket to its B2 fine buckets;
-//  lookup
-//   6. the handle's lookup kernel over the partitioned batch, tiles walked
-//      XCD by XCD, answers written in partitioned order;
-//  backward
-//   7. scatter (position, answer) pairs to D output windows of 2 MiB (counts
-//      are known: window d holds positions [d 2^S, (d+1) 2^S));
-//   8. write every answer to its position, windows walked XCD by XCD, so the
-//      writes of one window merge into whole lines in one L2.
-// Within a run, entries land in the order workgroup threads claim them, so
-// the partitioned order is not deterministic; answers never depend on it,
-// and the bucket function only has to be monotone for locality.
+// Step 6 is why one pass suffices in both directions: a tile's answers sit in
+// NB pieces of some tens of bytes to a few hundred, which one XCD's L2 holds
+// for the tiles it works on, so the gather reads every line once and writes
+// the output in order.  Writing the answers to their positions instead costs
+// a 32-byte memory write per 4-byte answer (L2 does not merge the writes of
+// different waves), with a second pass to narrow them 3.2 ms per 2^27
+// lookups against 0.54 ms here.
+//
+// The partition is a pure function of the call: no state stays in the handle.
 #include <type_traits>
 
 #include "internal.hpp"
@@ -47,34 +43,53 @@ namespace idx {
 namespace {
 
 constexpr uint32_t kPartThreads = 1024;
-constexpr uint64_t kPartTile = 65536;          // entries per partition workgroup
-constexpr uint32_t kMaxBuckets = 4096;          // bucket ids fit u16
-constexpr uint32_t kCoarse = 64;                // first-pass bucket count (at most)
-constexpr uint64_t kBucketBytes = 512 * 1024;   // target index bytes per bucket
-constexpr uint32_t kWindowShift = 19;           // at least 2^19 answers (2 MiB) per output window
-constexpr uint32_t kMaxWindows = 256;
-constexpr uint64_t kChunk = 1ull << 31;         // batch positions fit u32
-constexpr int kLoadAhead = 8;                   // entries a thread loads before using them
+constexpr int kPartPer = 8;                            // queries per thread and tile
+constexpr uint32_t kPartTile = kPartThreads * kPartPer;
+constexpr uint32_t kMaxBuckets = 1024;                 // one thread per bucket in the tile's scan
+constexpr uint64_t kBucketBytes = 3 * 512 * 1024;      // index bytes per bucket aimed at
+constexpr uint64_t kBucketQueries = 1024;              // queries per bucket at least, on average
+// Batches below this are looked up as they come: at n = 2^21..2^26 the
+// partition's launches take 62-170 us up to 2^18 queries, unpartitioned
+// lookups 21-68 us; at 2^20 they take 65-221 and 59-271 us.  Range calls: 114-
+// 236 and 71-128 us at 2^18, 143-405 and 164-402 us at 2^20.
+constexpr uint64_t kPartMin = 3ull << 18;
 
-// Splitters from the sorted array: split[j] = key at rank (j + 1) * step.
+// How a call is partitioned.
+struct PartGeo {
+    uint32_t NB;    // buckets (1: not worth a partition)
+    uint32_t L;     // levels of a bucket's table in LDS
+    uint32_t D;     // sorted array: a table entry for every 2^D keys, at least a run of them
+    uint32_t top;   // Eytzinger layouts: the splitters are the keys of the top `top` levels
+    uint64_t step;  // sorted array: ranks per bucket, 2^(L + D); bucket b's keys have their lower bounds in
+                    //   [b * step, (b + 1) * step), or at n
+};
+
+// Splitters of the sorted array: the last key of every bucket's ranks.
 template <typename K, bool AOS>
-__global__ void k_split_sorted(Load<K, AOS> L, uint64_t step, uint32_t B, K *__restrict__ split) {
+__global__ void k_split_sorted(Load<K, AOS> L, uint64_t step, uint32_t NB, K *__restrict__ split) {
     const uint32_t j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= B) return;
-    split[j] = (j + 1 < B) ? L.key((uint64_t)(j + 1) * step) : key_max_v<K>();
+    if (j >= NB) return;
+    split[j] = (j + 1 < NB) ? L.key((uint64_t)(j + 1) * step - 1) : key_max_v<K>();
 }
 
-// Splitters from an Eytzinger layout: every slot whose sorted rank is a
-// multiple of step writes itself.  first = 1 for EBS (1-based slots).
+// Splitters of an Eytzinger layout: the keys of its top levels in key order
+// (a full tree of NB - 1 keys), so that bucket b is the subtree of the b-th
+// node below them.  Key j of that tree: j + 1 = k^e u with u not a multiple
+// of k puts it on level top - 1 - e, at position (u - 1) - (u - 1) / k.
 template <typename K, bool AOS>
-__global__ void k_split_eyt(Load<K, AOS> L, Geo G, uint64_t first, uint64_t step, uint32_t B, K *__restrict__ split) {
-    const uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= G.n) return;
-    if (t == 0) split[B - 1] = key_max_v<K>();
-    const uint64_t r = slot_rank(G, t);
-    if (r == 0 || r % step != 0) return;
-    const uint64_t j = r / step;
-    if (j < B) split[j - 1] = L.key(t + first);
+__global__ void k_split_eyt(Load<K, AOS> L, Geo G, uint64_t off, uint32_t top, uint32_t NB, K *__restrict__ split) {
+    const uint32_t j = blockIdx.x * blockDim.x + threadIdx.x;
+    if (j >= NB) return;
+    if (j + 1 == NB) {
+        split[j] = key_max_v<K>();
+        return;
+    }
+    uint32_t u = j + 1, e = 0;
+    while (u % G.k == 0) {
+        u /= G.k;
+        ++e;
+    }
+    split[j] = L.key(off + G.start[top - 1 - e] + (u - 1) - (u - 1) / G.k);
 }
 
 // Bucket table: the key range from the first splitter to the second-largest
@@ -139,610 +154,856 @@ __device__ __forceinline__ uint32_t bucket_of_cells(const K *s_split, const uint
     return b;
 }
 
-__global__ void k_zero_u32(uint32_t *p, uint32_t count) {
-    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < count) p[i] = 0;
-}
-
-__device__ __forceinline__ uint64_t tile_end(uint64_t lo, uint64_t m) {
-    return lo + kPartTile < m ? lo + kPartTile : m;
-}
-
-// 2. Fine bucket of every query and per-bucket totals.
+// LDS tables of the bucket function.
 template <typename K>
-__global__ __launch_bounds__(kPartThreads) void k_fwd_count(const K *__restrict__ q, uint64_t m,
-                                                            const K *__restrict__ split, uint32_t B,
-                                                            uint16_t *__restrict__ bkt,
+struct Buckets {
+    K *s_split;
+    uint16_t *s_cell;
+    K base;
+    uint32_t sh;
+    // Fills the tables (every thread of the workgroup); s_cell has kCells + 1 entries.
+    __device__ __forceinline__ void build(const K *__restrict__ split, uint32_t NB) {
+        for (uint32_t i = threadIdx.x; i < NB; i += blockDim.x) s_split[i] = split[i];
+        __syncthreads();
+        base = s_split[0];
+        sh = cell_shift(s_split, NB);
+        build_cells(s_split, NB, base, sh, s_cell);
+        __syncthreads();
+    }
+    __device__ __forceinline__ uint32_t of(K x) const { return bucket_of_cells(s_split, s_cell, base, sh, x); }
+};
+
+constexpr size_t kCellBytes = ((kCells + 1) * 2 + 15) & ~(size_t)15;
+
+// 2. Queries of every bucket in every tile: hist[b * tiles + tile].  The
+// tiles are walked XCD by XCD, so the counts that share a line of the matrix
+// are written by one XCD.
+template <typename K>
+__global__ __launch_bounds__(kPartThreads) void k_part_count(const K *__restrict__ q, uint64_t m,
+                                                             const K *__restrict__ split, uint32_t NB, uint32_t tiles,
+                                                             uint32_t iters, uint32_t *__restrict__ hist) {
+    extern __shared__ __align__(16) char smem[];
+    Buckets<K> B{(K *)smem, (uint16_t *)(smem + NB * sizeof(K)), K(0), 0};
+    uint32_t *s_cnt = (uint32_t *)(smem + NB * sizeof(K) + kCellBytes);
+    for (uint32_t b = threadIdx.x; b < NB; b += kPartThreads) s_cnt[b] = 0;
+    B.build(split, NB);
+    for (uint32_t it = blockIdx.x; it < iters; it += gridDim.x) {
+        const uint32_t tile = (uint32_t)tile_of(it, tiles, 1);
+        if (tile >= tiles) continue;  // workgroup-uniform
+        const uint64_t t0 = (uint64_t)tile * kPartTile;
+        K x[kPartPer];
+#pragma unroll
+        for (int u = 0; u < kPartPer; ++u) {
+            const uint64_t i = t0 + (uint32_t)u * kPartThreads + threadIdx.x;
+            x[u] = i < m ? q[i] : K(0);
+        }
+#pragma unroll
+        for (int u = 0; u < kPartPer; ++u) {
+            const uint64_t i = t0 + (uint32_t)u * kPartThreads + threadIdx.x;
+            if (i < m) atomicAdd(&s_cnt[B.of(x[u])], 1u);
+        }
+        __syncthreads();
+        if (threadIdx.x < NB) {  // NB <= kPartThreads
+            hist[(uint64_t)threadIdx.x * tiles + tile] = s_cnt[threadIdx.x];
+            s_cnt[threadIdx.x] = 0;
+        }
+        __syncthreads();
+    }
+}
+
+// Exclusive scan of one value per thread over the workgroup; s_wave holds one
+// entry per wave.  Barriers on both sides.
+__device__ __forceinline__ uint32_t part_scan(uint32_t v, uint32_t *s_wave, uint32_t *total) {
+    const uint32_t lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    uint32_t incl = v;
+#pragma unroll
+    for (int off = 1; off < kWave; off <<= 1) {
+        const uint32_t t = (uint32_t)__shfl_up((int)incl, off, kWave);
+        if (lane >= (uint32_t)off) incl += t;
+    }
+    if (lane == kWave - 1) s_wave[wave] = incl;
+    __syncthreads();
+    uint32_t before = 0, sum = 0;
+    for (uint32_t w = 0; w < blockDim.x / kWave; ++w) {
+        const uint32_t c = s_wave[w];
+        before += w < wave ? c : 0;
+        sum += c;
+    }
+    __syncthreads();
+    *total = sum;
+    return before + incl - v;
+}
+
+// 3. One workgroup per bucket: exclusive scan of its counts along the tiles,
+// in place, and its total.
+constexpr uint32_t kScanThreads = 256;
+constexpr int kScanPer = 16;
+
+__global__ __launch_bounds__(kScanThreads) void k_part_scan(uint32_t *__restrict__ hist, uint32_t tiles,
                                                             uint32_t *__restrict__ total) {
-    extern __shared__ __align__(16) char smem[];
-    K *s_split = (K *)smem;
-    uint32_t *s_hist = (uint32_t *)(s_split + B);
-    uint16_t *s_cell = (uint16_t *)(s_hist + B);  // kCells + 1 entries
-    for (uint32_t i = threadIdx.x; i < B; i += blockDim.x) {
-        s_split[i] = split[i];
-        s_hist[i] = 0;
-    }
-    __syncthreads();
-    const K base = s_split[0];
-    const uint32_t sh = cell_shift(s_split, B);
-    build_cells(s_split, B, base, sh, s_cell);
-    __syncthreads();
-    const uint64_t lo = (uint64_t)blockIdx.x * kPartTile, hi = tile_end(lo, m);
-    // kLoadAhead queries per thread are loaded before any is placed, so
-    // their loads are in flight together
-    for (uint64_t i0 = lo + threadIdx.x; i0 < hi; i0 += (uint64_t)kLoadAhead * blockDim.x) {
-        K v[kLoadAhead];
+    __shared__ uint32_t s_wave[kScanThreads / kWave];
+    uint32_t *row = hist + (uint64_t)blockIdx.x * tiles;
+    uint32_t running = 0;
+    for (uint32_t c0 = 0; c0 < tiles; c0 += kScanThreads * kScanPer) {
+        uint32_t v[kScanPer], sum = 0;
+        const uint32_t first = c0 + threadIdx.x * kScanPer;
 #pragma unroll
-        for (int u = 0; u < kLoadAhead; ++u) {
-            const uint64_t i = i0 + (uint64_t)u * blockDim.x;
-            v[u] = i < hi ? q[i] : K(0);
+        for (int j = 0; j < kScanPer; ++j) {
+            v[j] = first + j < tiles ? row[first + j] : 0u;
+            sum += v[j];
         }
+        uint32_t all;
+        uint32_t acc = running + part_scan(sum, s_wave, &all);
 #pragma unroll
-        for (int u = 0; u < kLoadAhead; ++u) {
-            const uint64_t i = i0 + (uint64_t)u * blockDim.x;
-            if (i >= hi) continue;
-            const uint32_t b = bucket_of_cells(s_split, s_cell, base, sh, v[u]);
-            bkt[i] = (uint16_t)b;
-            atomicAdd(&s_hist[b], 1u);
+        for (int j = 0; j < kScanPer; ++j) {
+            if (first + j < tiles) row[first + j] = acc;
+            acc += v[j];
         }
+        running += all;
     }
-    __syncthreads();
-    for (uint32_t b = threadIdx.x; b < B; b += blockDim.x)
-        if (s_hist[b]) atomicAdd(&total[b], s_hist[b]);
+    if (threadIdx.x == 0) total[blockIdx.x] = running;
 }
 
-// 3. Bucket starts from the totals; coarse and window cursors.  One
-// workgroup of kPartThreads threads; B <= kMaxBuckets.
-__global__ __launch_bounds__(kPartThreads) void k_starts(const uint32_t *__restrict__ total, uint32_t B, uint32_t B2,
-                                                         uint32_t *__restrict__ fcur, uint32_t *__restrict__ ccur,
-                                                         uint32_t D, uint32_t shift, uint32_t *__restrict__ dcur) {
-    __shared__ uint32_t s_sum[kPartThreads];
-    constexpr uint32_t PER = kMaxBuckets / kPartThreads;
-    uint32_t v[PER], sum = 0;
-#pragma unroll
-    for (uint32_t j = 0; j < PER; ++j) {
-        const uint32_t b = threadIdx.x * PER + j;
-        v[j] = b < B ? total[b] : 0;
-        sum += v[j];
-    }
-    s_sum[threadIdx.x] = sum;
-    __syncthreads();
-    // inclusive Hillis-Steele scan of the per-thread sums
-    for (uint32_t off = 1; off < kPartThreads; off <<= 1) {
-        const uint32_t add = threadIdx.x >= off ? s_sum[threadIdx.x - off] : 0;
-        __syncthreads();
-        s_sum[threadIdx.x] += add;
-        __syncthreads();
-    }
-    uint32_t run = s_sum[threadIdx.x] - sum;
-#pragma unroll
-    for (uint32_t j = 0; j < PER; ++j) {
-        const uint32_t b = threadIdx.x * PER + j;
-        if (b < B) {
-            fcur[b] = run;
-            if (b % B2 == 0) ccur[b / B2] = run;
-        }
-        run += v[j];
-    }
-    for (uint32_t d = threadIdx.x; d < D; d += blockDim.x) dcur[d] = d << shift;
-}
-
-// Window cursors of the backward scatter (also set by k_starts): window d
-// starts at position d << shift.
-__global__ void k_window_cursors(uint32_t *__restrict__ dcur, uint32_t D, uint32_t shift) {
-    const uint32_t d = threadIdx.x;
-    if (d < D) dcur[d] = d << shift;
-}
-
-// 4./5./7. One scatter pass: entry i goes to run run_of(i) of NB runs.  Per
-// tile a workgroup reserves one contiguous piece of every run the tile feeds
-// (one global atomic per run), then fills the pieces front to back in rounds
-// of kSub entries sorted by run in LDS, so consecutive lanes write
-// consecutive addresses.  The grid is one workgroup per compute
-// unit, each walking its own tiles, which bounds the partially written lines
-// in flight per XCD to about 32 workgroups x NB runs x 2 per output array.
-struct FwdCoarse {};
-struct FwdFine {};
-struct Bwd {};
-
-template <typename K, typename Pass>
-struct ScatterArgs {
-    const K *__restrict__ q_in;
-    const uint32_t *__restrict__ p_in;   // batch positions (fine pass, backward pass)
-    const uint16_t *__restrict__ b_in;   // fine bucket ids
-    const uint32_t *__restrict__ r_in;   // answers (backward pass)
-    K *__restrict__ q_out;
-    uint32_t *__restrict__ p_out;
-    uint16_t *__restrict__ b_out;
-    uint64_t *__restrict__ pk_out;       // backward: position << 32 | answer
-    uint32_t *__restrict__ cur;          // run cursors
-    uint64_t m;
-    uint64_t ntiles;
-    uint32_t B2;                         // fine buckets per coarse bucket
-    uint32_t NB;                         // runs this pass feeds
-    uint32_t shift;                      // backward: log2 of the output window
-};
-
-template <typename K, typename Pass>
-__device__ __forceinline__ uint32_t run_of(const ScatterArgs<K, Pass> &a, uint64_t i) {
-    if constexpr (std::is_same_v<Pass, FwdCoarse>) return a.b_in[i] / a.B2;
-    else if constexpr (std::is_same_v<Pass, FwdFine>) return a.b_in[i];
-    else return a.p_in[i] >> a.shift;
-}
-
-// Entries of one staged round: each thread loads kSubPer of them, they are
-// sorted by run in LDS, and every run's piece leaves with consecutive lanes
-// writing consecutive addresses.  A tile whose runs span more than kSpan run
-// ids (a fine pass over a small batch) places entries directly instead.
-constexpr uint32_t kSubPer = 4;
-constexpr uint32_t kSub = kPartThreads * kSubPer;
-constexpr uint32_t kSpan = 256;
-
-template <typename K, typename Pass>
-struct Staged {
-    static constexpr bool bwd = std::is_same_v<Pass, Bwd>;
-    // per entry: query key, batch position, fine bucket (forward) or the
-    // (position, answer) pair (backward); and its run relative to the tile's
-    // smallest run
-    static constexpr size_t entry_bytes = (bwd ? 8 : sizeof(K) + 4 + 2) + 2;
-};
-
-template <typename K, typename Pass>
+// 4. The scatter.  Per tile: every query's bucket and its turn in it (LDS
+// atomics), the buckets' starts within the tile, the queries into LDS in
+// bucket order, and out, consecutive threads writing consecutive addresses of
+// a bucket's piece.  A persistent workgroup per compute unit keeps the bucket
+// tables; the next tile's queries are loaded while this one's leave.
+// RANGE: a second key per query (the ranges' upper bounds) moves along.
+// starts[b] (NB + 1 entries) receives the buckets' starts.
+// Bound by memory: 20 B per 64-bit query, 0.70 ms per 2^27 (two passes of 28
+// and 30 B took 2.57 ms).
+template <typename K>
 size_t scatter_lds_bytes(uint32_t NB) {
-    return (((size_t)NB * 4 + 15) & ~(size_t)15) + (size_t)kSub * Staged<K, Pass>::entry_bytes;
+    return (size_t)NB * sizeof(K) + kCellBytes + (size_t)NB * 12 + (size_t)kPartTile * (sizeof(K) + 2) + 16;
 }
 
-template <typename K, typename Pass>
-__global__ __launch_bounds__(kPartThreads) void k_scatter(ScatterArgs<K, Pass> a) {
-    constexpr bool BWD = std::is_same_v<Pass, Bwd>;
-    constexpr bool COARSE = std::is_same_v<Pass, FwdCoarse>;
+template <typename K, bool RANGE>
+__global__ __launch_bounds__(kPartThreads) void k_part_scatter(const K *__restrict__ q, const K *__restrict__ q_hi,
+                                                               uint64_t m, const K *__restrict__ split, uint32_t NB,
+                                                               uint32_t tiles, uint32_t iters,
+                                                               const uint32_t *__restrict__ hist,
+                                                               const uint32_t *__restrict__ total,
+                                                               K *__restrict__ q2, K *__restrict__ q2_hi,
+                                                               uint32_t *__restrict__ place,
+                                                               uint32_t *__restrict__ starts) {
     extern __shared__ __align__(16) char smem[];
-    uint32_t *s_cnt = (uint32_t *)smem;  // per run: count, then cursor
-    char *st = smem + (((size_t)a.NB * 4 + 15) & ~(size_t)15);
-    uint64_t *st_pk = (uint64_t *)st;               // backward
-    K *st_q = (K *)st;                              // forward
-    uint32_t *st_p = (uint32_t *)(st + (size_t)kSub * sizeof(K));
-    uint16_t *st_b = (uint16_t *)((char *)st_p + (size_t)kSub * 4);
-    uint16_t *st_r = BWD ? (uint16_t *)(st + (size_t)kSub * 8) : (uint16_t *)((char *)st_b + (size_t)kSub * 2);
-    __shared__ uint32_t s_sub[kSpan], s_off[kSpan], s_wsum[kSpan / kWave];
-    __shared__ uint32_t s_lo, s_hi;
-    for (uint64_t tl = blockIdx.x; tl < a.ntiles; tl += gridDim.x) {
-        for (uint32_t b = threadIdx.x; b < a.NB; b += blockDim.x) s_cnt[b] = 0;
-        if (threadIdx.x == 0) {
-            s_lo = 0xFFFFFFFFu;
-            s_hi = 0;
+    K *s_q = (K *)smem;
+    char *p = smem + (size_t)kPartTile * sizeof(K);
+    Buckets<K> B{(K *)p, (uint16_t *)(p + NB * sizeof(K)), K(0), 0};
+    p += NB * sizeof(K) + kCellBytes;
+    uint32_t *s_cnt = (uint32_t *)p;   // the tile's queries of each bucket
+    uint32_t *s_start = s_cnt + NB;    // their start within the tile
+    uint32_t *s_off = s_start + NB;    // place in q2 minus place in the tile
+    uint16_t *s_run = (uint16_t *)(s_off + NB);
+    __shared__ uint32_t s_wave[kPartThreads / kWave];
+    const uint32_t tid = threadIdx.x;
+    uint32_t all;
+    const uint32_t base = part_scan(tid < NB ? total[tid] : 0u, s_wave, &all);
+    if (blockIdx.x == 0 && tid < NB) {
+        starts[tid] = base;
+        if (tid == 0) starts[NB] = (uint32_t)m;
+    }
+    if (tid < NB) s_cnt[tid] = 0;
+    B.build(split, NB);
+    K x[kPartPer];
+    auto load = [&](uint32_t tile) {
+        const uint64_t t0 = (uint64_t)tile * kPartTile;
+#pragma unroll
+        for (int u = 0; u < kPartPer; ++u) {
+            const uint64_t i = t0 + (uint32_t)u * kPartThreads + tid;
+            x[u] = i < m ? q[i] : K(0);
         }
-        __syncthreads();
-        const uint64_t lo = tl * kPartTile, hi = tile_end(lo, a.m);
-        uint32_t rmin = 0xFFFFFFFFu, rmax = 0;
-        for (uint64_t i0 = lo + threadIdx.x; i0 < hi; i0 += (uint64_t)kLoadAhead * blockDim.x) {
-            uint32_t rv[kLoadAhead];
+    };
+    uint32_t it = blockIdx.x;
+    uint32_t tile = it < iters ? (uint32_t)tile_of(it, tiles, 1) : tiles;
+    if (tile < tiles) load(tile);
+    while (it < iters) {
+        const uint32_t next = it + gridDim.x;
+        const uint32_t next_tile = next < iters ? (uint32_t)tile_of(next, tiles, 1) : tiles;
+        if (tile < tiles) {  // workgroup-uniform
+            const uint64_t t0 = (uint64_t)tile * kPartTile;
+            const uint32_t cnt = m - t0 < kPartTile ? (uint32_t)(m - t0) : kPartTile;
+            const uint32_t before = tid < NB ? hist[(uint64_t)tid * tiles + tile] : 0u;
+            uint32_t at[kPartPer];  // bucket << 16 | turn, then place in the tile
 #pragma unroll
-            for (int u = 0; u < kLoadAhead; ++u) {
-                const uint64_t i = i0 + (uint64_t)u * blockDim.x;
-                rv[u] = i < hi ? run_of(a, i) : 0xFFFFFFFFu;
+            for (int u = 0; u < kPartPer; ++u) {
+                at[u] = 0;
+                if ((uint32_t)u * kPartThreads + tid < cnt) {
+                    const uint32_t b = B.of(x[u]);
+                    at[u] = (b << 16) | atomicAdd(&s_cnt[b], 1u);
+                }
             }
+            __syncthreads();
+            const uint32_t start = part_scan(tid < NB ? s_cnt[tid] : 0u, s_wave, &all);
+            if (tid < NB) {
+                s_start[tid] = start;
+                s_off[tid] = base + before - start;
+                s_cnt[tid] = 0;
+            }
+            __syncthreads();
 #pragma unroll
-            for (int u = 0; u < kLoadAhead; ++u) {
-                if (rv[u] == 0xFFFFFFFFu) continue;
-                atomicAdd(&s_cnt[rv[u]], 1u);
-                rmin = rv[u] < rmin ? rv[u] : rmin;
-                rmax = rv[u] > rmax ? rv[u] : rmax;
+            for (int u = 0; u < kPartPer; ++u) {
+                const uint32_t j = (uint32_t)u * kPartThreads + tid;
+                if (j >= cnt) continue;
+                const uint32_t b = at[u] >> 16, pos = s_start[b] + (at[u] & 0xFFFFu);
+                s_q[pos] = x[u];
+                s_run[pos] = (uint16_t)b;
+                place[t0 + j] = s_off[b] + pos;
+                at[u] = pos;
             }
+            if constexpr (RANGE) {
+#pragma unroll
+                for (int u = 0; u < kPartPer; ++u) {
+                    const uint32_t j = (uint32_t)u * kPartThreads + tid;
+                    x[u] = j < cnt ? q_hi[t0 + j] : K(0);
+                }
+            } else if (next_tile < tiles) {
+                load(next_tile);
+            }
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < kPartPer; ++u) {
+                const uint32_t j = (uint32_t)u * kPartThreads + tid;
+                if (j < cnt) q2[s_off[s_run[j]] + j] = s_q[j];
+            }
+            __syncthreads();
+            if constexpr (RANGE) {
+#pragma unroll
+                for (int u = 0; u < kPartPer; ++u)
+                    if ((uint32_t)u * kPartThreads + tid < cnt) s_q[at[u]] = x[u];
+                if (next_tile < tiles) load(next_tile);
+                __syncthreads();
+#pragma unroll
+                for (int u = 0; u < kPartPer; ++u) {
+                    const uint32_t j = (uint32_t)u * kPartThreads + tid;
+                    if (j < cnt) q2_hi[s_off[s_run[j]] + j] = s_q[j];
+                }
+                __syncthreads();
+            }
+        } else if (next_tile < tiles) {
+            load(next_tile);
         }
-        if (rmin != 0xFFFFFFFFu) {
-            atomicMin(&s_lo, rmin);
-            atomicMax(&s_hi, rmax);
+        it = next;
+        tile = next_tile;
+    }
+}
+
+// 6. out[i] = ans[place[i]], tiles walked XCD by XCD like the scatter's, so
+// the pieces that a stretch of tiles reads stay in one L2.
+template <typename T>
+__global__ __launch_bounds__(256) void k_part_gather(const T *__restrict__ ans, const uint32_t *__restrict__ place,
+                                                     uint64_t m, uint64_t tiles, T *__restrict__ out) {
+    constexpr int U = 8;
+    const uint64_t tile = tile_of(blockIdx.x, tiles, 1);
+    if (tile >= tiles) return;
+    const uint64_t t0 = tile * (256 * U);
+    uint32_t at[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const uint64_t i = t0 + (uint32_t)u * 256 + threadIdx.x;
+        at[u] = i < m ? place[i] : 0u;
+    }
+    T v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = ans[at[u]];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const uint64_t i = t0 + (uint32_t)u * 256 + threadIdx.x;
+        if (i < m) out[i] = v[u];
+    }
+}
+
+// ------------------------------------------------------------------ lookups
+
+// A workgroup takes a span of the partitioned batch, bucket by bucket: it
+// copies the bucket's table to LDS, 2^L entries in heap order (entry v's
+// children are 2v and 2v + 1, which keeps a wave's reads of one level on
+// different banks), and each lane walks R queries down it in lockstep, then
+// down the rest of the bucket in memory, which its XCD's L2 holds.
+//
+// Bound by L2 requests: 128 channels serve about 270 G/s, and with 8192
+// queries in flight per compute unit no line stays in the 32 KiB L1 between
+// two dependent probes, so every probe is one.  On the sorted array, per 2^27
+// lookups at n = 2^26: 11 probes and a short-window scan from the bucket's
+// rank interval 4.74 ms; 12 levels in LDS and 5 probes 3.92 ms (7 requests a
+// lookup); 13 levels in LDS, then the one line that holds the lower bound,
+// read by eight lanes with one load, 1.67 ms (2.2 requests; VALU work now
+// weighs as much).
+constexpr uint32_t kLookThreads = 1024;
+constexpr int kLookPer = 4;        // queries per lane at once
+constexpr uint32_t kSpan = kLookThreads * kLookPer;  // queries per workgroup: two workgroups per compute unit keep
+                                                     // the queries an XCD has in flight within a bucket or two
+                                                     // (twice the span: its L2 thrashed, 4.89 ms)
+constexpr uint32_t kMaxLevels1 = 13;  // levels in LDS: 64 KiB of 64-bit keys, two workgroups per compute unit
+constexpr uint32_t kMinLevels = 6;
+
+// The last step of a search reads a run of keys with kRunLanes lanes, 16 bytes
+// each, one request: a whole line.  (Half a line halves the lanes' work, 1.53
+// against 1.67 ms per 2^27 lookups, but needs twice the buckets at n = 2^26,
+// and the count, scatter and gather lose 0.26 ms to their shorter pieces.)
+constexpr uint32_t kRunLanes = 8;
+
+template <typename K>
+constexpr uint32_t run_log() {  // log2 of the keys of a run
+    return (kRunLanes == 4 ? 2u : 3u) + (sizeof(K) == 8 ? 1u : 2u);
+}
+
+// Tables of the sorted array: entry i in key order is the key at rank
+// b * step + (i + 1) 2^D - 1, i < 2^L - 1 (heap entry 0 is unused).  With c
+// entries below x, bucket b's x has its lower bound in the 2^D ranks from
+// b * step + c 2^D.  Ranks past the array count as above everything.  Written once per call, so that the many workgroups of
+// one bucket copy it with consecutive loads.
+template <typename K, bool AOS>
+__global__ __launch_bounds__(256) void k_part_tables(Load<K, AOS> A, uint64_t n, PartGeo P, K *__restrict__ tab) {
+    const uint64_t t = (uint64_t)blockIdx.x * 256 + threadIdx.x;
+    const uint32_t b = (uint32_t)(t >> P.L), v = (uint32_t)(t & ((1u << P.L) - 1u));
+    if (b >= P.NB || v == 0) return;
+    const uint32_t l = 31u - (uint32_t)__clz((int)v);
+    const uint64_t i = ((2ull * (v - (1u << l)) + 1) << (P.L - 1 - l)) - 1;
+    const uint64_t at = b * P.step + ((i + 1) << P.D) - 1;
+    tab[t] = at < n ? A.key(at) : key_max_v<K>();
+}
+
+template <typename K>
+__device__ __forceinline__ void fill_table(const K *__restrict__ tab, uint32_t b, uint32_t L, K *s_tab) {
+    const uint4 *src = (const uint4 *)(tab + ((uint64_t)b << L));
+    const uint32_t chunks = (uint32_t)(sizeof(K) << L) / 16;  // L >= kMinLevels
+    for (uint32_t v = threadIdx.x; v < chunks; v += kLookThreads) ((uint4 *)s_tab)[v] = src[v];
+}
+
+// Start rank (relative to the bucket) of the 2^D ranks that hold each x.
+template <typename K, int R>
+__device__ __forceinline__ void table_find(const K *s_tab, const PartGeo &P, const K (&x)[R], uint32_t (&rel)[R]) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) rel[r] = 1;
+    for (uint32_t l = 0; l < P.L; ++l) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) rel[r] = 2 * rel[r] + (s_tab[rel[r]] < x[r] ? 1u : 0u);
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) rel[r] = (rel[r] - (1u << P.L)) << P.D;
+}
+
+// Value of lane k of each group of kRunLanes lanes.
+template <int k>
+__device__ __forceinline__ uint32_t run_lane(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_ds_swizzle((int)v, (0x20 - (int)kRunLanes) | (k << 5));
+}
+template <int k>
+__device__ __forceinline__ uint64_t run_lane(uint64_t v) {
+    return ((uint64_t)run_lane<k>((uint32_t)(v >> 32)) << 32) | run_lane<k>((uint32_t)v);
+}
+
+// Lanes k and k + 1 of each group have their queries' runs (from rank `run` of
+// the bucket, a multiple of the run's keys) read by the group, 16 bytes a
+// lane: keys below x into below, and whether one equals x.  Ranks from `have`
+// on are past the array.
+template <typename K, int k>
+__device__ __forceinline__ void run_pair(const K *__restrict__ keys, uint32_t have, uint32_t run, K x,
+                                         uint32_t &below, bool &equal) {
+    constexpr int V = 16 / sizeof(K);
+    constexpr uint32_t MASK = (1u << kRunLanes) - 1u;
+    const uint32_t lane = threadIdx.x & (kWave - 1), sub = lane & (kRunLanes - 1), shift = lane & (32u - kRunLanes);
+    const bool upper = lane >= 32;
+    const K xs[2] = {run_lane<k>(x), run_lane<k + 1>(x)};
+    uint32_t at[2] = {run_lane<k>(run), run_lane<k + 1>(run)};
+    uint4 w[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        at[u] += sub * V;
+        w[u] = *(const uint4 *)((const char *)keys + at[u] * (uint32_t)sizeof(K));
+    }
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        K kk[V];
+        if constexpr (sizeof(K) == 8) {
+            kk[0] = ((uint64_t)w[u].y << 32) | w[u].x;
+            kk[1] = ((uint64_t)w[u].w << 32) | w[u].z;
+        } else {
+            kk[0] = w[u].x;
+            kk[1] = w[u].y;
+            kk[2] = w[u].z;
+            kk[3] = w[u].w;
         }
-        __syncthreads();
-        for (uint32_t b = threadIdx.x; b < a.NB; b += blockDim.x) {
-            const uint32_t c = s_cnt[b];
-            s_cnt[b] = c ? atomicAdd(&a.cur[b], c) : 0u;
+        uint32_t c = 0;
+        bool e = false;
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+            const uint64_t lt = __ballot(at[u] + v < have && kk[v] < xs[u]);
+            c += (uint32_t)__popc((upper ? (uint32_t)(lt >> 32) : (uint32_t)lt) >> shift & MASK);
+            e |= kk[v] == xs[u];
         }
-        __syncthreads();
-        const uint32_t r_lo = s_lo;
-        if (s_hi - r_lo >= kSpan) {
-            // direct placement: four entries per thread per round, so their loads overlap
-            for (uint64_t i0 = lo + threadIdx.x; i0 < hi; i0 += 4 * (uint64_t)blockDim.x) {
-                uint32_t d[4];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const uint64_t i = i0 + (uint64_t)u * blockDim.x;
-                    d[u] = i < hi ? atomicAdd(&s_cnt[run_of(a, i)], 1u) : 0u;
-                }
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const uint64_t i = i0 + (uint64_t)u * blockDim.x;
-                    if (i >= hi) continue;
-                    if constexpr (COARSE) {
-                        a.q_out[d[u]] = a.q_in[i];
-                        a.p_out[d[u]] = (uint32_t)i;
-                        a.b_out[d[u]] = a.b_in[i];
-                    } else if constexpr (!BWD) {
-                        a.q_out[d[u]] = a.q_in[i];
-                        a.p_out[d[u]] = a.p_in[i];
-                        a.b_out[d[u]] = a.b_in[i];
-                    } else {
-                        a.pk_out[d[u]] = ((uint64_t)a.p_in[i] << 32) | a.r_in[i];
-                    }
-                }
-            }
-            __syncthreads();  // before the next tile clears the counters
-            continue;
-        }
-        // staged rounds of kSub entries
-        for (uint64_t s0 = lo; s0 < hi; s0 += kSub) {
-            const uint32_t ns = hi - s0 < kSub ? (uint32_t)(hi - s0) : kSub;
-            if (threadIdx.x < kSpan) s_sub[threadIdx.x] = 0;
-            __syncthreads();
-            uint32_t rr[kSubPer], rk[kSubPer], pp[kSubPer];
-            K qq[kSubPer];
-            uint16_t bb[kSubPer];
-            uint64_t pk[kSubPer];
-#pragma unroll
-            for (uint32_t u = 0; u < kSubPer; ++u) {
-                const uint32_t j = u * kPartThreads + threadIdx.x;
-                rr[u] = kSpan;
-                if (j >= ns) continue;
-                const uint64_t i = s0 + j;
-                rr[u] = run_of(a, i) - r_lo;
-                rk[u] = atomicAdd(&s_sub[rr[u]], 1u);
-                if constexpr (BWD) {
-                    pk[u] = ((uint64_t)a.p_in[i] << 32) | a.r_in[i];
-                } else {
-                    qq[u] = a.q_in[i];
-                    pp[u] = COARSE ? (uint32_t)i : a.p_in[i];
-                    bb[u] = a.b_in[i];
-                }
-            }
-            __syncthreads();
-            // exclusive scan of the run counts of this round
-            if (threadIdx.x < kSpan) {
-                const uint32_t lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
-                const uint32_t v = s_sub[threadIdx.x];
-                uint32_t inc = v;
-#pragma unroll
-                for (int off = 1; off < kWave; off <<= 1) {
-                    const uint32_t x = (uint32_t)__shfl_up((int)inc, off, kWave);
-                    if (lane >= (uint32_t)off) inc += x;
-                }
-                if (lane == kWave - 1) s_wsum[w] = inc;
-                s_off[threadIdx.x] = inc - v;
-            }
-            __syncthreads();
-            if (threadIdx.x < kSpan) {
-                uint32_t add = 0;
-                for (uint32_t w = 0; w < threadIdx.x / kWave; ++w) add += s_wsum[w];
-                s_off[threadIdx.x] += add;
-            }
-            __syncthreads();
-            // entries into the staging area, sorted by run
-#pragma unroll
-            for (uint32_t u = 0; u < kSubPer; ++u) {
-                if (rr[u] >= kSpan) continue;
-                const uint32_t j = s_off[rr[u]] + rk[u];
-                st_r[j] = (uint16_t)rr[u];
-                if constexpr (BWD) {
-                    st_pk[j] = pk[u];
-                } else {
-                    st_q[j] = qq[u];
-                    st_p[j] = pp[u];
-                    st_b[j] = bb[u];
-                }
-            }
-            __syncthreads();
-            // every run's piece: consecutive staged entries to consecutive addresses
-#pragma unroll
-            for (uint32_t u = 0; u < kSubPer; ++u) {
-                const uint32_t j = u * kPartThreads + threadIdx.x;
-                if (j >= ns) continue;
-                const uint32_t r = st_r[j];
-                const uint32_t d = s_cnt[r_lo + r] + (j - s_off[r]);
-                if constexpr (BWD) {
-                    a.pk_out[d] = st_pk[j];
-                } else {
-                    a.q_out[d] = st_q[j];
-                    a.p_out[d] = st_p[j];
-                    a.b_out[d] = st_b[j];
-                }
-            }
-            __syncthreads();
-            if (threadIdx.x < kSpan && r_lo + threadIdx.x < a.NB) s_cnt[r_lo + threadIdx.x] += s_sub[threadIdx.x];
-            __syncthreads();
+        const uint64_t eq = __ballot(e);
+        const bool hit = ((upper ? (uint32_t)(eq >> 32) : (uint32_t)eq) >> shift & MASK) != 0;
+        if (sub == (uint32_t)(k + u)) {
+            below = c;
+            equal = hit;
         }
     }
 }
 
-// 8. Answers to their positions.  One workgroup per compute unit walking
-// its XCD's share of the tiles in order, so the entries one XCD has in
-// flight stay within about one output window, whose lines fill in its L2.
-constexpr uint32_t kPlaceThreads = 1024;
-constexpr uint32_t kPlacePer = 4;
-
-__global__ __launch_bounds__(kPlaceThreads) void k_place(const uint64_t *__restrict__ pk, uint64_t m, uint64_t ntiles,
-                                                         uint64_t iters, uint32_t *__restrict__ out) {
-    constexpr uint64_t TILE = (uint64_t)kPlaceThreads * kPlacePer;
-    for (uint64_t it = blockIdx.x; it < iters; it += gridDim.x) {
-        const uint64_t tl = tile_of(it, ntiles, 1);
-        if (tl >= ntiles) continue;
-        const uint64_t t0 = tl * TILE;
-        uint64_t v[kPlacePer];
+// Lower bounds of x[R] from rank `base` on: rel[r] comes as the start of the
+// 2^D ranks that hold it (a multiple of a run's keys; base + rel <= n) and
+// leaves as the lower bound.  All lanes of the wave call this together.  hit:
+// the key there equals x.
+template <typename K, bool AOS, int R>
+__device__ __forceinline__ void settle(const Load<K, AOS> &A, uint64_t n, uint64_t base, const PartGeo &P,
+                                       const K (&x)[R], uint32_t (&rel)[R], bool (&hit)[R]) {
+    constexpr uint32_t last = AOS ? 0u : run_log<K>();  // keys and row IDs interleaved: probes to the end
+    const uint32_t have = n - base < 0xFFFFFFFFull ? (uint32_t)(n - base) : 0xFFFFFFFFu;
+    for (uint32_t e = P.D; e-- > last;) {
 #pragma unroll
-        for (uint32_t r = 0; r < kPlacePer; ++r) {
-            const uint64_t i = t0 + (uint64_t)r * kPlaceThreads + threadIdx.x;
-            v[r] = i < m ? pk[i] : ~0ull;
+        for (int r = 0; r < R; ++r) {
+            const uint32_t at = rel[r] + (1u << e) - 1;
+            rel[r] += (at < have && A.key(base + at) < x[r]) ? 1u << e : 0u;
         }
+    }
+    if constexpr (AOS) {
 #pragma unroll
-        for (uint32_t r = 0; r < kPlacePer; ++r)
-            if (v[r] != ~0ull) out[v[r] >> 32] = (uint32_t)v[r];
+        for (int r = 0; r < R; ++r) {
+            const K k = rel[r] < have ? A.key(base + rel[r]) : key_max_v<K>();
+            hit[r] = rel[r] < have && k == x[r];
+            rel[r] += rel[r] < have && k < x[r] ? 1u : 0u;  // the bucket's last key is below x
+        }
+    } else {
+        const K *keys = A.k + base;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            uint32_t below = 0;
+            bool equal = false;
+            run_pair<K, 0>(keys, have, rel[r], x[r], below, equal);
+            run_pair<K, 2>(keys, have, rel[r], x[r], below, equal);
+            if constexpr (kRunLanes == 8) {
+                run_pair<K, 4>(keys, have, rel[r], x[r], below, equal);
+                run_pair<K, 6>(keys, have, rel[r], x[r], below, equal);
+            }
+            rel[r] += below;
+            hit[r] = equal && rel[r] < have;
+        }
     }
 }
 
-// Length of the rank interval [bucket_start(b), that + span] holding the
-// lower bound of any key of bucket b: splitter b - 1 (rank b * step) is below
-// the key and splitter b (rank (b + 1) * step) is not, so the lower bound is
-// in [b * step + 1, (b + 1) * step] (from 0 for b = 0, up to n for the last
-// bucket); the largest such interval serves every bucket and never reaches
-// past n.
-uint64_t bucket_span(uint64_t n, uint32_t B) {
-    const uint64_t step = n / B;
-    const uint64_t last = n - (B - 1) * step - 1;
-    return step > last ? step : last;
+// The bucket of partitioned position p: the last b with starts[b] <= p.
+__device__ __forceinline__ uint32_t bucket_at(const uint32_t *__restrict__ starts, uint32_t NB, uint32_t p) {
+    uint32_t lo = 0, hi = NB;
+    while (hi - lo > 1) {
+        const uint32_t mid = (lo + hi) / 2;
+        if (starts[mid] <= p) lo = mid;
+        else hi = mid;
+    }
+    return lo;
 }
 
-// Bucket count for the handle: a power of two giving about kBucketBytes of
-// index per bucket, at most kMaxBuckets and at most n.
-uint32_t buckets_for(const idx_index *h) {
-    const uint64_t bytes = h->n * ((h->u64 ? 8 : 4) + 4);
-    uint32_t B = 2;
-    while (B < kMaxBuckets && (uint64_t)B * kBucketBytes < bytes) B <<= 1;
-    while (B > 2 && B > h->n) B >>= 1;
-    return B;
+// Calls body(b, p0, p1) for the pieces [p0, p1) of this workgroup's span, one
+// bucket each (workgroup-uniform).
+template <typename Body>
+__device__ __forceinline__ void for_pieces(uint64_t m, const uint32_t *__restrict__ starts, uint32_t NB, uint64_t spans,
+                                           Body &&body) {
+    const uint64_t sp = tile_of(blockIdx.x, spans, 1);
+    if (sp >= spans) return;
+    uint32_t p0 = (uint32_t)(sp * kSpan);
+    const uint32_t end = m - sp * kSpan < kSpan ? (uint32_t)m : p0 + kSpan;
+    uint32_t b = bucket_at(starts, NB, p0);
+    while (p0 < end) {
+        while (starts[b + 1] <= p0) ++b;
+        const uint32_t p1 = starts[b + 1] < end ? starts[b + 1] : end;
+        body(b, p0, p1);
+        p0 = p1;
+    }
 }
 
 template <typename K, bool AOS>
-int build_splitters_t(idx_index *h, uint32_t B, hipStream_t s) {
-    const uint64_t step = h->n / B;
-    const Load<K, AOS> L = make_load<K, AOS>(h);
+__global__ __launch_bounds__(kLookThreads, 8) void k_part_bs(Load<K, AOS> A, uint64_t n, const K *__restrict__ q,
+                                                             uint64_t m, const uint32_t *__restrict__ starts,
+                                                             PartGeo P, const K *__restrict__ tab, uint64_t spans,
+                                                             uint32_t *__restrict__ ans) {
+    extern __shared__ __align__(16) char smem[];
+    K *s_tab = (K *)smem;
+    constexpr int R = kLookPer;
+    for_pieces(m, starts, P.NB, spans, [&](uint32_t b, uint32_t p0, uint32_t p1) {
+        K x[R];  // a piece is at most one round of the workgroup's queries
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const uint32_t i = p0 + (uint32_t)r * kLookThreads + threadIdx.x;
+            x[r] = q[i < p1 ? i : p0];
+        }
+        fill_table(tab, b, P.L, s_tab);
+        __syncthreads();
+        uint32_t rel[R];
+        table_find<K, R>(s_tab, P, x, rel);
+        bool hit[R];
+        const uint64_t base = b * P.step;
+        settle<K, AOS, R>(A, n, base, P, x, rel, hit);
+        uint32_t res[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) res[r] = hit[r] ? A.row(base + rel[r]) : kMiss;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const uint32_t i = p0 + (uint32_t)r * kLookThreads + threadIdx.x;
+            if (i < p1) ans[i] = res[r];
+        }
+        __syncthreads();
+    });
+}
+
+// Binary Eytzinger layout: bucket b is the subtree of slot NB + b (1-based),
+// whose next L full levels are the table; the descent goes on from there.
+template <typename K, bool AOS>
+__global__ __launch_bounds__(kLookThreads) void k_part_ebs(Load<K, AOS> A, uint64_t n, uint32_t m_full,
+                                                           const K *__restrict__ q, uint64_t m,
+                                                           const uint32_t *__restrict__ starts, PartGeo P,
+                                                           uint64_t spans, uint32_t *__restrict__ ans) {
+    extern __shared__ __align__(16) char smem[];
+    K *s_tab = (K *)smem;
+    const uint32_t L = P.L;
+    for_pieces(m, starts, P.NB, spans, [&](uint32_t b, uint32_t p0, uint32_t p1) {
+        const uint64_t root = (uint64_t)P.NB + b;
+        for (uint32_t v = 1 + threadIdx.x; v < (1u << L); v += kLookThreads) {
+            const uint32_t l = 31u - (uint32_t)__clz((int)v);
+            s_tab[v] = A.key((root << l) + (v - (1u << l)));
+        }
+        __syncthreads();
+        for (uint32_t t = p0 + threadIdx.x; t < p1; t += kLookThreads * kLookPer) {
+            K x[kLookPer], ck[kLookPer];
+            uint64_t i[kLookPer];
+            {
+                uint32_t v[kLookPer];
+#pragma unroll
+                for (int r = 0; r < kLookPer; ++r) {
+                    const uint32_t at = t + (uint32_t)r * kLookThreads;
+                    x[r] = q[at < p1 ? at : t];
+                    v[r] = 1;
+                    ck[r] = key_max_v<K>();
+                }
+                for (uint32_t l = 0; l < L; ++l) {
+#pragma unroll
+                    for (int r = 0; r < kLookPer; ++r) {
+                        const K k = s_tab[v[r]];
+                        const bool right = k < x[r];
+                        ck[r] = right ? ck[r] : k;
+                        v[r] = 2 * v[r] + (right ? 1u : 0u);
+                    }
+                }
+#pragma unroll
+                for (int r = 0; r < kLookPer; ++r) i[r] = (root << L) + (v[r] - (1u << L));
+            }
+            for (uint32_t l = P.top + L; l < m_full; ++l) {
+#pragma unroll
+                for (int r = 0; r < kLookPer; ++r) {
+                    const K k = A.key(i[r]);
+                    const bool right = k < x[r];
+                    ck[r] = right ? ck[r] : k;
+                    i[r] = 2 * i[r] + (right ? 1 : 0);
+                }
+            }
+            uint32_t res[kLookPer];
+#pragma unroll
+            for (int r = 0; r < kLookPer; ++r) {
+                if (i[r] <= n) {
+                    const K k = A.key(i[r]);
+                    const bool right = k < x[r];
+                    ck[r] = right ? ck[r] : k;
+                    i[r] = 2 * i[r] + (right ? 1 : 0);
+                }
+                const uint64_t j = i[r] >> (__builtin_ctzll(~i[r]) + 1);
+                if (j != 0 && j < P.NB) ck[r] = A.key(j);  // the lower bound lies above the bucket
+                res[r] = (j != 0 && ck[r] == x[r]) ? A.row(j) : kMiss;
+            }
+#pragma unroll
+            for (int r = 0; r < kLookPer; ++r) {
+                const uint32_t at = t + (uint32_t)r * kLookThreads;
+                if (at < p1) ans[at] = res[r];
+            }
+        }
+        __syncthreads();
+    });
+}
+
+// Both ranks of every range on the sorted array, as one packed word (first
+// rank << 32 | count) in partitioned order.  The range's lower bound names
+// the bucket; an upper bound past the bucket is searched in the rest of the
+// array.
+template <typename K, bool AOS>
+__global__ __launch_bounds__(kLookThreads, 8) void k_part_range_bs(Load<K, AOS> A, uint64_t n,
+                                                                   const K *__restrict__ q, const K *__restrict__ q_hi,
+                                                                   uint64_t m, const uint32_t *__restrict__ starts,
+                                                                   PartGeo P, const K *__restrict__ tab, uint64_t spans,
+                                                                   uint64_t *__restrict__ packed) {
+    extern __shared__ __align__(16) char smem[];
+    K *s_tab = (K *)smem;
+    constexpr int R = 4;  // bounds: two ranges per lane at once
+    for_pieces(m, starts, P.NB, spans, [&](uint32_t b, uint32_t p0, uint32_t p1) {
+        fill_table(tab, b, P.L, s_tab);
+        __syncthreads();
+        const uint64_t base = b * P.step;
+        for (uint32_t t0 = p0; t0 < p1; t0 += kLookThreads * (R / 2)) {
+            K x[R];
+            bool empty[R / 2], all[R / 2];
+#pragma unroll
+            for (int r = 0; r < R / 2; ++r) {
+                const uint32_t i = t0 + (uint32_t)r * kLookThreads + threadIdx.x, at = i < p1 ? i : p0;
+                const K l = q[at], u = q_hi[at];
+                empty[r] = l > u;
+                all[r] = u == key_max_v<K>();  // nothing is above u
+                x[2 * r] = l;
+                x[2 * r + 1] = all[r] ? u : (K)(u + 1);
+            }
+            uint32_t rel[R];
+            table_find<K, R>(s_tab, P, x, rel);
+            bool hit[R];
+            settle<K, AOS, R>(A, n, base, P, x, rel, hit);
+#pragma unroll
+            for (int r = 0; r < R / 2; ++r) {
+                const uint32_t i = t0 + (uint32_t)r * kLookThreads + threadIdx.x;
+                uint64_t r1 = base + rel[2 * r + 1];
+                if (rel[2 * r + 1] == P.step && !empty[r] && !all[r]) {  // past the bucket
+                    uint64_t len = n - r1;
+                    while (len) {
+                        const uint64_t half = len >> 1;
+                        if (A.key(r1 + half) < x[2 * r + 1]) {
+                            r1 += half + 1;
+                            len -= half + 1;
+                        } else {
+                            len = half;
+                        }
+                    }
+                }
+                if (all[r]) r1 = n;
+                const uint64_t r0 = base + rel[2 * r];
+                if (i < p1) packed[i] = empty[r] ? 0ull : (r0 << 32) | (r1 > r0 ? r1 - r0 : 0ull);
+            }
+        }
+        __syncthreads();
+    });
+}
+
+// The buckets of a batch of m queries: at most kMaxBuckets, no fewer than
+// kBucketQueries queries each on average (they share the cost of the
+// bucket's table), and otherwise as small as a table of up to 13 levels over
+// whole lines makes them: 1.5 MiB of 64-bit keys and row IDs, 2 MiB of 32-bit
+// ones (an XCD's L2 holds the one or two in flight).  Small sets get shorter
+// tables, for eight buckets or more.
+PartGeo part_geo(const idx_index *h, uint64_t m) {
+    PartGeo P{};
+    P.NB = 1;
+    if (h->n < 4) return P;
     if (h->layout == IDX_BS) {
-        hipLaunchKernelGGL((k_split_sorted<K, AOS>), dim3((B + 255) / 256), dim3(256), 0, s, L, step, B, (K *)h->split);
-    } else {
-        const uint64_t first = h->layout == IDX_EBS ? 1 : 0;
-        hipLaunchKernelGGL((k_split_eyt<K, AOS>), dim3((uint32_t)((h->n + 255) / 256)), dim3(256), 0, s, L, h->geo,
-                           first, step, B, (K *)h->split);
+        P.L = kMaxLevels1;
+        P.D = h->u64 ? run_log<uint64_t>() : run_log<uint32_t>();
+        auto buckets = [&] { return (h->n + (1ull << (P.L + P.D)) - 1) >> (P.L + P.D); };
+        while (P.L > kMinLevels && buckets() < 8) --P.L;
+        // (few queries: larger buckets, of 2^26 ranks at most, whose byte offsets fit 32 bits)
+        while (buckets() > kMaxBuckets || (buckets() > 2 && buckets() * kBucketQueries > m && P.L + P.D < 26)) ++P.D;
+        while (P.L > kMinLevels && (1ull << P.L) * buckets() > 8 * m) {  // few queries per bucket: shorter tables
+            --P.L;
+            ++P.D;
+        }
+        P.step = 1ull << (P.L + P.D);
+        P.NB = (uint32_t)buckets();
+        return P;
     }
-    IDX_LAUNCH_CHECK();
-    return IDX_OK;
-}
-
-int build_splitters(idx_index *h, uint32_t B, hipStream_t s) {
-    if (h->split && h->split_buckets == B) return IDX_OK;
-    drop_splitters(h, s);
-    h->split = h->alloc.get((size_t)B * (h->u64 ? 8 : 4), s);
-    if (!h->split) return IDX_ERR_NOMEM;
-    int rc;
-    if (h->u64) rc = h->aos ? build_splitters_t<uint64_t, true>(h, B, s) : build_splitters_t<uint64_t, false>(h, B, s);
-    else rc = h->aos ? build_splitters_t<uint32_t, true>(h, B, s) : build_splitters_t<uint32_t, false>(h, B, s);
-    if (rc != IDX_OK) {
-        drop_splitters(h, s);
-        return rc;
+    const uint64_t bytes = h->n * ((h->u64 ? 8 : 4) + 4);
+    uint32_t want = 2;
+    while (want < kMaxBuckets && want * kBucketBytes < bytes) want <<= 1;
+    while (want > 2 && (want * kBucketQueries > m || want > h->n / 2)) want >>= 1;
+    while (P.top < h->geo.m && P.NB * h->geo.k <= want) {
+        P.NB *= h->geo.k;
+        ++P.top;
     }
-    h->split_buckets = B;
-    return IDX_OK;
+    P.L = kMaxLevels1;
+    while (P.L > kMinLevels && (1ull << P.L) * P.NB > 8 * m) --P.L;
+    if (P.L > h->geo.m - P.top) P.L = h->geo.m - P.top;
+    return P;
 }
-
-// Scratch of one chunk of m queries (256-byte aligned regions).
-struct PartBufs {
-    void *q1;         // coarse-partitioned queries; later the (position, answer) pairs
-    uint32_t *p1;     // coarse-partitioned positions; later the answers in partitioned order
-    uint16_t *b1;     // coarse-partitioned fine bucket ids
-    uint16_t *bkt;    // fine bucket id of every query; after the fine pass, in partitioned order
-    void *q2;         // fine-partitioned queries
-    uint32_t *p2;     // fine-partitioned positions
-    uint32_t *total;  // kMaxBuckets per-bucket totals
-    uint32_t *fcur;   // kMaxBuckets
-    uint32_t *ccur;   // kCoarse
-    uint32_t *dcur;   // kMaxWindows
-};
 
 size_t up256(size_t v) { return (v + 255) & ~(size_t)255; }
 
-size_t part_bytes(uint64_t m, size_t kb) {
-    return up256(m * 8 > m * kb ? m * 8 : m * kb) + up256(m * 4) + 2 * up256(m * 2) + up256(m * kb) + up256(m * 4) +
-           up256((size_t)(2 * kMaxBuckets + kCoarse + kMaxWindows) * 4);
+uint64_t part_tiles(uint64_t m) { return (m + kPartTile - 1) / kPartTile; }
+
+// Scratch of one chunk of m queries (256-byte aligned regions).
+struct PartBufs {
+    void *q2, *q2_hi;   // queries (and upper bounds) in partitioned order
+    uint32_t *place;    // place of every query in that order
+    void *ans;          // answers in partitioned order: u32, or u64 for ranges
+    uint32_t *hist;     // NB x tiles
+    uint32_t *total;    // NB
+    uint32_t *starts;   // NB + 1
+    void *split;        // NB keys
+    void *tab;          // the buckets' tables: NB << L keys (sorted array)
+};
+
+size_t part_bytes(uint64_t m, size_t kb, const PartGeo &P, bool range) {
+    const uint32_t NB = P.NB;
+    return up256(m * kb) * (range ? 2 : 1) + up256(m * 4) + up256(m * (range ? 8 : 4)) +
+           up256((size_t)NB * part_tiles(m) * 4) + up256((size_t)NB * 4) + up256(((size_t)NB + 1) * 4) +
+           up256((size_t)NB * kb) + up256(((size_t)NB << P.L) * kb);
 }
 
-PartBufs carve(char *t, uint64_t m, size_t kb) {
+PartBufs carve(char *t, uint64_t m, size_t kb, const PartGeo &P, bool range) {
+    const uint32_t NB = P.NB;
     PartBufs p{};
-    p.q1 = t;
-    t += up256(m * 8 > m * kb ? m * 8 : m * kb);
-    p.p1 = (uint32_t *)t;
-    t += up256(m * 4);
-    p.b1 = (uint16_t *)t;
-    t += up256(m * 2);
-    p.bkt = (uint16_t *)t;
-    t += up256(m * 2);
-    p.q2 = t;
-    t += up256(m * kb);
-    p.p2 = (uint32_t *)t;
-    t += up256(m * 4);
-    p.total = (uint32_t *)t;
-    p.fcur = p.total + kMaxBuckets;
-    p.ccur = p.fcur + kMaxBuckets;
-    p.dcur = p.ccur + kCoarse;
+    auto take = [&](size_t b) {
+        char *r = t;
+        t += up256(b);
+        return r;
+    };
+    p.q2 = take(m * kb);
+    p.q2_hi = range ? take(m * kb) : nullptr;
+    p.place = (uint32_t *)take(m * 4);
+    p.ans = take(m * (range ? 8 : 4));
+    p.hist = (uint32_t *)take((size_t)NB * part_tiles(m) * 4);
+    p.total = (uint32_t *)take((size_t)NB * 4);
+    p.starts = (uint32_t *)take(((size_t)NB + 1) * 4);
+    p.split = take((size_t)NB * kb);
+    p.tab = take(((size_t)NB << P.L) * kb);
     return p;
 }
 
-// Forward passes (steps 2-5): fine buckets, their starts, then the coarse
-// and fine scatters; the partitioned queries land in P.q2 with their batch
-// positions in P.p2.
-template <typename K>
-int partition_fwd(idx_index *h, const K *q, uint64_t m, uint32_t B, const PartBufs &P, hipStream_t s) {
-    const uint32_t B1 = B < kCoarse ? B : kCoarse;
-    const uint32_t B2 = B / B1;
-    const uint64_t tiles = (m + kPartTile - 1) / kPartTile;
-    const uint32_t sgrid = (uint32_t)(tiles < (uint64_t)h->cu_count ? tiles : (uint64_t)h->cu_count);
-    uint32_t shift = kWindowShift;
-    while (((m - 1) >> shift) + 1 > kMaxWindows) ++shift;
-    const uint32_t D = (uint32_t)(((m - 1) >> shift) + 1);
-    // totals start at zero (a fill kernel, not a memset node, so the
-    // sequence can be captured in a graph)
-    hipLaunchKernelGGL(k_zero_u32, dim3(kMaxBuckets / 256), dim3(256), 0, s, P.total, kMaxBuckets);
+// Steps 1-4.
+template <typename K, bool AOS>
+int partition_t(idx_index *h, const K *q, const K *q_hi, uint64_t m, const PartGeo &P, const PartBufs &B,
+                hipStream_t s) {
+    const Load<K, AOS> A = make_load<K, AOS>(h);
+    const uint32_t NB = P.NB;
+    if (h->layout == IDX_BS)
+        hipLaunchKernelGGL((k_split_sorted<K, AOS>), dim3((NB + 255) / 256), dim3(256), 0, s, A, P.step, NB,
+                           (K *)B.split);
+    else
+        hipLaunchKernelGGL((k_split_eyt<K, AOS>), dim3((NB + 255) / 256), dim3(256), 0, s, A, h->geo,
+                           (uint64_t)(h->layout == IDX_EBS ? 1 : 0), P.top, NB, (K *)B.split);
     IDX_LAUNCH_CHECK();
-    hipLaunchKernelGGL((k_fwd_count<K>), dim3((uint32_t)tiles), dim3(kPartThreads),
-                       (size_t)B * (sizeof(K) + 4) + (kCells + 1) * 2, s, q,
-                       m, (const K *)h->split, B, P.bkt, P.total);
+    const uint32_t tiles = (uint32_t)part_tiles(m);
+    const uint32_t iters = (tiles + kXcds - 1) / kXcds * kXcds;
+    const uint32_t cus = (uint32_t)h->cu_count / kXcds * kXcds;  // a multiple of the XCDs: workgroups keep their share
+    const uint32_t one = cus ? cus : kXcds, two = 2 * one;
+    hipLaunchKernelGGL((k_part_count<K>), dim3(iters < two ? iters : two), dim3(kPartThreads),
+                       (size_t)NB * (sizeof(K) + 4) + kCellBytes, s, q, m, (const K *)B.split, NB, tiles, iters, B.hist);
     IDX_LAUNCH_CHECK();
-    hipLaunchKernelGGL(k_starts, dim3(1), dim3(kPartThreads), 0, s, P.total, B, B2, P.fcur, P.ccur, D, shift, P.dcur);
+    hipLaunchKernelGGL(k_part_scan, dim3(NB), dim3(kScanThreads), 0, s, B.hist, tiles, B.total);
     IDX_LAUNCH_CHECK();
-    {
-        ScatterArgs<K, FwdCoarse> a{};
-        a.q_in = q;
-        a.b_in = P.bkt;
-        a.q_out = (K *)P.q1;
-        a.p_out = P.p1;
-        a.b_out = P.b1;
-        a.cur = P.ccur;
-        a.m = m;
-        a.ntiles = tiles;
-        a.B2 = B2;
-        a.NB = B1;
-        const size_t lds = scatter_lds_bytes<K, FwdCoarse>(B1);
-        hipLaunchKernelGGL((k_scatter<K, FwdCoarse>), dim3(sgrid), dim3(kPartThreads), lds, s, a);
-        IDX_LAUNCH_CHECK();
-    }
-    {
-        ScatterArgs<K, FwdFine> a{};
-        a.q_in = (const K *)P.q1;
-        a.p_in = P.p1;
-        a.b_in = P.b1;
-        a.q_out = (K *)P.q2;
-        a.p_out = P.p2;
-        a.b_out = P.bkt;  // caller-order bucket ids are no longer needed
-        a.cur = P.fcur;
-        a.m = m;
-        a.ntiles = tiles;
-        a.B2 = B2;
-        a.NB = B;
-        const size_t lds = scatter_lds_bytes<K, FwdFine>(B);
-        hipLaunchKernelGGL((k_scatter<K, FwdFine>), dim3(sgrid), dim3(kPartThreads), lds, s, a);
-        IDX_LAUNCH_CHECK();
-    }
-    return IDX_OK;
-}
-
-// Backward passes (steps 7-8): answers `ans` in partitioned order (positions
-// P.p2) to out[position].  Uses P.q1 for the (position, answer) pairs and
-// the window cursors P.dcur, which k_starts set; a second placement over the
-// same partition resets them first.
-int place_back(idx_index *h, const PartBufs &P, uint64_t m, const uint32_t *ans, uint32_t *out, hipStream_t s) {
-    const uint64_t tiles = (m + kPartTile - 1) / kPartTile;
-    const uint32_t sgrid = (uint32_t)(tiles < (uint64_t)h->cu_count ? tiles : (uint64_t)h->cu_count);
-    uint32_t shift = kWindowShift;
-    while (((m - 1) >> shift) + 1 > kMaxWindows) ++shift;
-    const uint32_t D = (uint32_t)(((m - 1) >> shift) + 1);
-    hipLaunchKernelGGL(k_window_cursors, dim3(1), dim3(kMaxWindows), 0, s, P.dcur, D, shift);
-    IDX_LAUNCH_CHECK();
-    {
-        ScatterArgs<uint32_t, Bwd> a{};
-        a.p_in = P.p2;
-        a.r_in = ans;
-        a.pk_out = (uint64_t *)P.q1;
-        a.cur = P.dcur;
-        a.m = m;
-        a.ntiles = tiles;
-        a.NB = D;
-        a.shift = shift;
-        const size_t lds = scatter_lds_bytes<uint32_t, Bwd>(D);
-        hipLaunchKernelGGL((k_scatter<uint32_t, Bwd>), dim3(sgrid), dim3(kPartThreads), lds, s, a);
-        IDX_LAUNCH_CHECK();
-    }
-    const uint64_t ptile = (uint64_t)kPlaceThreads * kPlacePer;
-    const uint64_t ptiles = (m + ptile - 1) / ptile;
-    const uint64_t piters = ((ptiles + kXcds - 1) / kXcds) * kXcds;
-    uint64_t pgrid = (uint64_t)h->cu_count - (uint64_t)h->cu_count % kXcds;
-    if (pgrid == 0) pgrid = kXcds;
-    if (pgrid > piters) pgrid = piters;
-    hipLaunchKernelGGL(k_place, dim3((uint32_t)pgrid), dim3(kPlaceThreads), 0, s, (const uint64_t *)P.q1, m, ptiles,
-                       piters, out);
+    const size_t lds = scatter_lds_bytes<K>(NB);
+    const dim3 grid(iters < one ? iters : one);
+    if (q_hi)
+        hipLaunchKernelGGL((k_part_scatter<K, true>), grid, dim3(kPartThreads), lds, s, q, q_hi, m, (const K *)B.split,
+                           NB, tiles, iters, B.hist, B.total, (K *)B.q2, (K *)B.q2_hi, B.place, B.starts);
+    else
+        hipLaunchKernelGGL((k_part_scatter<K, false>), grid, dim3(kPartThreads), lds, s, q, (const K *)nullptr, m,
+                           (const K *)B.split, NB, tiles, iters, B.hist, B.total, (K *)B.q2, (K *)nullptr, B.place,
+                           B.starts);
     IDX_LAUNCH_CHECK();
     return IDX_OK;
 }
 
-template <typename K>
-int partition_chunk(idx_index *h, const K *q, uint64_t m, uint32_t *out, uint32_t B, const PartBufs &P,
-                    hipStream_t s) {
-    int rc = partition_fwd<K>(h, q, m, B, P, s);
+template <typename K, bool AOS>
+int build_tables(const idx_index *h, const PartGeo &P, const PartBufs &B, hipStream_t s) {
+    const uint64_t entries = (uint64_t)P.NB << P.L;
+    hipLaunchKernelGGL((k_part_tables<K, AOS>), dim3((uint32_t)((entries + 255) / 256)), dim3(256), 0, s,
+                       make_load<K, AOS>(h), h->n, P, (K *)B.tab);
+    IDX_LAUNCH_CHECK();
+    return IDX_OK;
+}
+
+uint64_t spans_of(uint64_t m) { return (m + kSpan - 1) / kSpan; }
+dim3 span_grid(uint64_t spans) { return dim3((uint32_t)((spans + kXcds - 1) / kXcds * kXcds)); }
+
+template <typename K, bool AOS>
+int chunk_t(idx_index *h, const K *q, uint64_t m, uint32_t *out, const PartGeo &P, const PartBufs &B, hipStream_t s) {
+    int rc = partition_t<K, AOS>(h, q, (const K *)nullptr, m, P, B, s);
     if (rc != IDX_OK) return rc;
-    // answers in partitioned order go to p1 (free after the fine pass), or
-    // (reorder = 3) straight to their positions in out; the sorted array's
-    // search starts inside each lookup's bucket
-    const bool direct = h->params.reorder == 3;
-    PointIO io{P.q2, m, direct ? out : P.p1, false, true};
-    if (direct) io.pos = P.p2;
-    if (h->layout == IDX_BS && !(h->learned && h->params.model != 2)) {
-        io.bkt = P.bkt;
-        io.bstep = h->n / B;
-        io.bspan = bucket_span(h->n, B);
+    const uint64_t spans = spans_of(m);
+    const bool model = h->learned && h->params.model != 2;
+    uint32_t *ans = (uint32_t *)B.ans;
+    if (h->layout == IDX_BS && !model) {
+        rc = build_tables<K, AOS>(h, P, B, s);
+        if (rc != IDX_OK) return rc;
+        hipLaunchKernelGGL((k_part_bs<K, AOS>), span_grid(spans), dim3(kLookThreads), sizeof(K) << P.L, s,
+                           make_load<K, AOS>(h), h->n, (const K *)B.q2, m, B.starts, P, (const K *)B.tab, spans, ans);
+        IDX_LAUNCH_CHECK();
+    } else if (h->layout == IDX_EBS) {
+        hipLaunchKernelGGL((k_part_ebs<K, AOS>), span_grid(spans), dim3(kLookThreads), sizeof(K) << P.L, s,
+                           make_load<K, AOS>(h), h->n, h->geo.m, (const K *)B.q2, m, B.starts, P, spans, ans);
+        IDX_LAUNCH_CHECK();
+    } else {  // the handle's own lookup kernel over the partitioned batch
+        rc = point_run(h, PointIO{B.q2, m, ans, false, true}, s);
+        if (rc != IDX_OK) return rc;
     }
-    rc = point_run(h, io, s);
-    if (rc != IDX_OK || direct) return rc;
-    return place_back(h, P, m, P.p1, out, s);
+    const uint64_t gt = (m + 2047) / 2048;
+    hipLaunchKernelGGL(k_part_gather<uint32_t>, dim3((uint32_t)((gt + kXcds - 1) / kXcds * kXcds)), dim3(256), 0, s,
+                       (const uint32_t *)ans, (const uint32_t *)B.place, m, gt, out);
+    IDX_LAUNCH_CHECK();
+    return IDX_OK;
+}
+
+template <typename K, bool AOS>
+int range_chunk_t(idx_index *h, const K *lo, const K *hi, uint64_t m, const PartGeo &P, char *scratch, RangePart *out,
+                  hipStream_t s) {
+    const PartBufs B = carve(scratch, m, sizeof(K), P, true);
+    int rc = partition_t<K, AOS>(h, lo, hi, m, P, B, s);
+    if (rc != IDX_OK) return rc;
+    out->lo = B.q2;
+    out->hi = B.q2_hi;
+    out->packed = (uint64_t *)B.ans;
+    out->place = B.place;
+    out->counted = h->layout == IDX_BS;
+    if (!out->counted) return IDX_OK;
+    rc = build_tables<K, AOS>(h, P, B, s);
+    if (rc != IDX_OK) return rc;
+    const uint64_t spans = spans_of(m);
+    hipLaunchKernelGGL((k_part_range_bs<K, AOS>), span_grid(spans), dim3(kLookThreads), sizeof(K) << P.L, s,
+                       make_load<K, AOS>(h), h->n, (const K *)B.q2, (const K *)B.q2_hi, m, B.starts, P,
+                       (const K *)B.tab, spans, out->packed);
+    IDX_LAUNCH_CHECK();
+    return IDX_OK;
 }
 
 }  // namespace
 
-// ---- the partition as a service for other lookups (range counts): the
-// forward passes and the answer placement of one chunk, on scratch the
-// caller provides.
-size_t partition_scratch_bytes(const idx_index *h, uint64_t m) { return part_bytes(m, h->u64 ? 8 : 4); }
+// ---- the partition for range counts
+bool range_partition_pays(const idx_index *h, uint64_t m) { return m >= kPartMin && part_geo(h, m).NB > 1; }
 
-int partition_forward(idx_index *h, const void *q, uint64_t m, void *scratch, PartView *out, hipStream_t s) {
-    if (m == 0 || m > kChunk) return IDX_ERR_ARG;
-    const uint32_t B = buckets_for(h);
-    int rc = build_splitters(h, B, s);
-    if (rc != IDX_OK) return rc;
-    const size_t kb = h->u64 ? 8 : 4;
-    const PartBufs P = carve((char *)scratch, m, kb);
-    rc = h->u64 ? partition_fwd<uint64_t>(h, (const uint64_t *)q, m, B, P, s)
-                : partition_fwd<uint32_t>(h, (const uint32_t *)q, m, B, P, s);
-    if (rc != IDX_OK) return rc;
-    out->q = P.q2;
-    out->pos = P.p2;
-    out->m = m;
-    out->scratch = scratch;
-    out->bkt = P.bkt;
-    out->bstep = h->n / B;
-    out->bspan = bucket_span(h->n, B);
+size_t range_partition_bytes(const idx_index *h, uint64_t m) {
+    return part_bytes(m, h->u64 ? 8 : 4, part_geo(h, m), true);
+}
+
+int range_partition(idx_index *h, const void *lo, const void *hi, uint64_t m, void *scratch, RangePart *out,
+                    hipStream_t s) {
+    if (m == 0 || m > kPartChunk) return IDX_ERR_ARG;
+    const PartGeo P = part_geo(h, m);
+    char *t = (char *)scratch;
+    if (h->u64)
+        return h->aos ? range_chunk_t<uint64_t, true>(h, (const uint64_t *)lo, (const uint64_t *)hi, m, P, t, out, s)
+                      : range_chunk_t<uint64_t, false>(h, (const uint64_t *)lo, (const uint64_t *)hi, m, P, t, out, s);
+    return h->aos ? range_chunk_t<uint32_t, true>(h, (const uint32_t *)lo, (const uint32_t *)hi, m, P, t, out, s)
+                  : range_chunk_t<uint32_t, false>(h, (const uint32_t *)lo, (const uint32_t *)hi, m, P, t, out, s);
+}
+
+int range_partition_back(const RangePart &v, uint64_t m, uint64_t *packed, hipStream_t s) {
+    const uint64_t gt = (m + 2047) / 2048;
+    hipLaunchKernelGGL(k_part_gather<uint64_t>, dim3((uint32_t)((gt + kXcds - 1) / kXcds * kXcds)), dim3(256), 0, s,
+                       (const uint64_t *)v.packed, v.place, m, gt, packed);
+    IDX_LAUNCH_CHECK();
     return IDX_OK;
 }
 
-void drop_splitters(idx_index *h, hipStream_t s) {
-    if (h->split) h->alloc.put(h->split, s);
-    h->split = nullptr;
-    h->split_buckets = 0;
-}
-
 int point_partitioned(idx_index *h, const void *q, uint64_t m, uint32_t *out, hipStream_t s) {
-    if (h->n < 4) {
-        PointIO io{q, m, out, false, false};
-        return point_run(h, io, s);
-    }
-    const uint32_t B = buckets_for(h);
-    int rc = build_splitters(h, B, s);
-    if (rc != IDX_OK) return rc;
+    const uint64_t chunk = m < kPartChunk ? m : kPartChunk;
+    const PartGeo P = part_geo(h, chunk);
+    if (m < kPartMin || P.NB == 1) return point_run(h, PointIO{q, m, out, false, false}, s);
     const size_t kb = h->u64 ? 8 : 4;
-    const uint64_t chunk = m < kChunk ? m : kChunk;
-    char *tmp = (char *)h->alloc.get(part_bytes(chunk, kb), s);
+    char *tmp = (char *)h->alloc.get(part_bytes(chunk, kb, P, false), s);
     if (!tmp) return IDX_ERR_NOMEM;
-    const PartBufs P = carve(tmp, chunk, kb);
+    int rc = IDX_OK;
     for (uint64_t c0 = 0; c0 < m && rc == IDX_OK; c0 += chunk) {
         const uint64_t mc = (m - c0) < chunk ? (m - c0) : chunk;
-        // positions of this chunk are relative to its own start
+        const PartBufs B = carve(tmp, mc, kb, P, false);
+        // places of this chunk are relative to its own start
         if (h->u64)
-            rc = partition_chunk<uint64_t>(h, (const uint64_t *)q + c0, mc, out + c0, B, P, s);
+            rc = h->aos ? chunk_t<uint64_t, true>(h, (const uint64_t *)q + c0, mc, out + c0, P, B, s)
+                        : chunk_t<uint64_t, false>(h, (const uint64_t *)q + c0, mc, out + c0, P, B, s);
         else
-            rc = partition_chunk<uint32_t>(h, (const uint32_t *)q + c0, mc, out + c0, B, P, s);
+            rc = h->aos ? chunk_t<uint32_t, true>(h, (const uint32_t *)q + c0, mc, out + c0, P, B, s)
+                        : chunk_t<uint32_t, false>(h, (const uint32_t *)q + c0, mc, out + c0, P, B, s);
     }
     h->alloc.put(tmp, s);
     return rc;
