@@ -23,6 +23,7 @@
 // theta -= H^-1 g, which for this quadratic loss reaches the least-squares
 // fit in one step from zero, the second step correcting FP32 rounding.
 #include <climits>
+#include <cstddef>
 
 #include <new>
 
@@ -38,139 +39,491 @@ namespace {
 constexpr int LT = 256;  // threads per block in the training kernels
 constexpr int CHUNK = 32;  // consecutive keys per thread in the per-leaf passes
 
-template <typename K, bool AOS>
-__global__ __launch_bounds__(LT) void k_root_accum(Load<K, AOS> keys, uint64_t n, const RootRec *Rp,
-                                                   double *__restrict__ acc) {
-    __shared__ double s[LT / kWave][NACC];
-    const RootRec R = *Rp;
-    double a[NACC] = {0, 0, 0, 0, 0, 0};
-    const double scale = (double)R.L / (double)n;
-    for (uint64_t i = (uint64_t)blockIdx.x * LT + threadIdx.x; i < n; i += (uint64_t)gridDim.x * LT) {
-        const uint64_t key = (uint64_t)keys.key(i);
-        const float t = (float)((double)i * scale);
-        float x, pred;
-        if (R.mode == IDX_FEATURE_SPLINE) {
-            x = 0.f;  // no parameters to fit: only the loss is wanted
-            (void)spline_leaf(R, key, &pred);
-        } else {
-            x = key_feature(key, R.mode);
-            pred = __fadd_rn(__fmul_rn(R.a1, x), R.a0);
+// Root candidates of one training, by index: linear roots over the LINEAR and
+// LOG feature, spline roots with LINEAR and LOG bins.
+constexpr int kRoots = 4;
+constexpr int kSpline0 = 2;  // the first spline candidate
+
+// What a root pass sums for the linear candidates (accumulator layout at
+// NACC): the feature sums depend on the keys alone, so that the first pass
+// takes them for all steps, and the loss is wanted once.
+constexpr uint32_t kSumX = 1, kSumGrad = 2, kSumLoss = 4;
+
+// Sums of every candidate in `mask` over all keys, in one read of them (a
+// spline root has no parameters to fit: only its loss).  Bound by vector
+// instructions (conversions and FP64), so each pass leaves out the sums it
+// does not need: 2^26 64-bit keys in 126, 108 and 275 us for the first, second
+// and last pass of the four candidates, where each candidate took 136 us a
+// pass and the training eight passes.
+template <typename K, bool AOS, uint32_t SUMS, bool SPLINES>
+__global__ __launch_bounds__(LT) void k_root_accum(Load<K, AOS> keys, uint64_t n, const RootRec *__restrict__ roots,
+                                                   uint32_t mask, double *__restrict__ acc) {
+    __shared__ double s[LT / kWave][kRoots][NACC];
+    double a[kRoots][NACC] = {};
+    const double scale = (double)roots[__builtin_ctz(mask)].L / (double)n;
+    const RootRec R0 = roots[0], R1 = roots[1], R2 = roots[2], R3 = roots[3];
+    constexpr int U = 2;  // keys loaded together
+    const uint64_t step = (uint64_t)gridDim.x * LT;
+    for (uint64_t i0 = (uint64_t)blockIdx.x * LT + threadIdx.x; i0 < n; i0 += U * step) {
+        uint64_t kk[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) kk[u] = i0 + u * step < n ? (uint64_t)keys.key(i0 + u * step) : 0ull;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const uint64_t i = i0 + u * step, key = kk[u];
+            if (i >= n) continue;
+            const float t = (float)((double)(uint32_t)i * scale);
+            auto linear = [&](const RootRec &R, double (&v)[NACC]) {
+                const float x = key_feature(key, R.mode);
+                const float r = __fsub_rn(__fadd_rn(__fmul_rn(R.a1, x), R.a0), t);  // forward residual
+                if constexpr (SUMS & kSumX) {
+                    v[1] += x;
+                    v[2] += (double)x * x;
+                }
+                if constexpr (SUMS & kSumGrad) {
+                    v[3] += r;
+                    v[4] += (double)r * x;
+                }
+                if constexpr (SUMS & kSumLoss) v[5] += (double)r * r;
+            };
+            auto spline = [&](const RootRec &R, double (&v)[NACC]) {
+                float pred;
+                (void)spline_leaf(R, key, &pred);
+                const float r = __fsub_rn(pred, t);
+                v[5] += (double)r * r;
+            };
+            if (mask & 1u) linear(R0, a[0]);
+            if (mask & 2u) linear(R1, a[1]);
+            if constexpr (SPLINES) {
+                spline(R2, a[2]);
+                spline(R3, a[3]);
+            }
         }
-        const float r = __fsub_rn(pred, t);  // forward residual
-        a[0] += 1.0;
-        a[1] += x;
-        a[2] += (double)x * x;
-        a[3] += r;
-        a[4] += (double)r * x;
-        a[5] += (double)r * r;
     }
     const uint32_t lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
 #pragma unroll
-    for (int j = 0; j < NACC; ++j) {
-        const double v = wave_sum(a[j]);
-        if (lane == 0) s[wave][j] = v;
+    for (int c = 0; c < kRoots; ++c) {
+        if (!((mask >> c) & 1u)) continue;
+#pragma unroll
+        for (int j = 1; j < NACC; ++j) {
+            const double v = wave_sum(a[c][j]);
+            if (lane == 0) s[wave][c][j] = v;
+        }
     }
     __syncthreads();
-    if (threadIdx.x < NACC) {
-        double v = 0;
-        for (int w = 0; w < LT / kWave; ++w) v += s[w][threadIdx.x];
-        atomicAdd(&acc[threadIdx.x], v);
+    if (threadIdx.x < kRoots * NACC && ((mask >> (threadIdx.x / NACC)) & 1u)) {
+        const int c = threadIdx.x / NACC, j = threadIdx.x % NACC;
+        if (j == 0) {
+            if (blockIdx.x == 0) acc[threadIdx.x] = (double)n;
+        } else {
+            double v = 0;
+            for (int w = 0; w < LT / kWave; ++w) v += s[w][c][j];
+            if (v != 0.0) atomicAdd(&acc[threadIdx.x], v);
+        }
     }
 }
 
-__global__ void k_root_update(RootRec *R, const double *acc) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) newton_linear(acc, R->a0, R->a1);
+// The Newton step of the linear candidates in `mask`; their residual sums
+// start over.
+__global__ void k_root_update(RootRec *roots, uint32_t mask, double *acc) {
+    const uint32_t c = threadIdx.x;
+    if (c >= (uint32_t)kSpline0 || !((mask >> c) & 1u)) return;
+    newton_linear(acc + c * NACC, roots[c].a0, roots[c].a1);
+    acc[c * NACC + 3] = acc[c * NACC + 4] = 0.0;
 }
 
-__global__ void k_fill_u32(uint32_t *p, uint64_t count, uint32_t v) {
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < count; i += (uint64_t)gridDim.x * blockDim.x)
-        p[i] = v;
-}
+// First rank of every leaf, base[0, L], base[L] = n.  The root is
+// non-decreasing along the keys, so leaf l starts at the first rank whose
+// leaf is l or more: the rank where the leaf rises past it writes it, with no
+// counts, atomics or scan (0.53 ms for those and the leaf records of 2^24
+// leaves, 0.10 to 0.15 ms for this).  Runs of more than kGapInline empty leaves go to a
+// list in pieces, filled by k_leaf_gaps.  A linear root given with a negative
+// slope (learn_eval only) is non-increasing: its leaves are counted from the
+// last key down, so that base[l] is still the number of keys below leaf l.
+constexpr uint32_t kGapInline = 64, kGapPiece = 4096;
 
-__global__ void k_fill_u64(uint64_t *p, uint64_t count) {
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < count; i += (uint64_t)gridDim.x * blockDim.x)
-        p[i] = 0;
-}
+struct Gap {
+    uint32_t first, last, value;  // base[first..last] = value
+};
 
-__global__ void k_fill_f64(double *p, uint64_t count) {
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < count; i += (uint64_t)gridDim.x * blockDim.x)
-        p[i] = 0.0;
-}
+// Gap pieces that L leaves can make.
+inline size_t gap_capacity(uint32_t L) { return (size_t)L / kGapInline + L / kGapPiece + 4; }
 
-// Keys per leaf: each wave counts the leaf runs of its 64 * CHUNK
-// consecutive keys, one atomic per run and step.
 template <typename K, bool AOS>
-__global__ __launch_bounds__(LT) void k_leaf_count(Load<K, AOS> keys, uint64_t n, const RootRec *Rp,
-                                                   unsigned long long *__restrict__ count) {
+__global__ __launch_bounds__(LT) void k_leaf_bounds(Load<K, AOS> keys, uint64_t n, const RootRec *Rp,
+                                                    uint32_t *__restrict__ base, Gap *__restrict__ gaps,
+                                                    uint32_t *__restrict__ ngaps) {
     const RootRec R = *Rp;
-    const uint64_t b = ((uint64_t)blockIdx.x * LT + (threadIdx.x & ~(uint32_t)(kWave - 1))) * CHUNK;
-    const uint64_t e = b + (uint64_t)kWave * CHUNK < n ? b + (uint64_t)kWave * CHUNK : n;
-    wave_leaf_counts(
-        b, e, [&](uint64_t i) { return leaf_of(R, (uint64_t)keys.key(i)); },
-        [&](uint32_t l, uint32_t c) { atomicAdd(&count[l], (unsigned long long)c); });
+    const bool down = R.mode != IDX_FEATURE_SPLINE && R.a1 < 0.f;
+    const uint32_t lane = threadIdx.x & (kWave - 1);
+    auto key_at = [&](uint64_t i) { return (uint64_t)keys.key(down ? n - 1 - i : i); };
+    constexpr int U = 8;  // steps of 64 keys per wave, loaded together
+    const uint64_t b = ((uint64_t)blockIdx.x * LT + (threadIdx.x & ~(uint32_t)(kWave - 1))) * U;
+    auto set = [&](uint32_t first, uint32_t last, uint32_t value) {
+        if (last - first < kGapInline) {
+            for (uint32_t l = first; l <= last; ++l) base[l] = value;
+            return;
+        }
+        const uint32_t pieces = (last - first) / kGapPiece + 1;
+        uint32_t g = atomicAdd(ngaps, pieces);
+        for (uint32_t p = 0; p < pieces; ++p, ++g) {
+            const uint32_t f = first + p * kGapPiece;
+            gaps[g] = Gap{f, last - f < kGapPiece ? last : f + kGapPiece - 1, value};
+        }
+    };
+    uint64_t kk[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const uint64_t i = b + (uint64_t)u * kWave + lane;
+        kk[u] = i < n ? key_at(i) : 0ull;
+    }
+    uint32_t carry = ~0u;  // leaf of the rank before the wave's step; none before rank 0
+    if (b > 0 && b < n) carry = leaf_of(R, key_at(b - 1));
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const uint64_t i = b + (uint64_t)u * kWave + lane;
+        const uint32_t l = leaf_of(R, kk[u]);
+        const uint32_t before = __shfl_up(l, 1);
+        const uint32_t prev = lane == 0 ? carry : before;
+        carry = __shfl(l, kWave - 1);
+        if (i >= n) continue;
+        if (l + 1 > prev + 1) set(prev + 1, l, (uint32_t)i);
+        if (i == n - 1) set(l + 1, R.L, (uint32_t)n);
+    }
 }
 
-// Leaf records from the exclusive scan of the per-leaf counts (base[l] =
-// keys before leaf l, base[L] = n): base rank, size, first key; parameters
-// start at zero and error bounds empty.
-template <typename K, bool AOS>
-__global__ void k_leaf_init(Load<K, AOS> keys, const unsigned long long *__restrict__ base, uint32_t L,
-                            LeafRec *__restrict__ leaves) {
-    const uint32_t l = blockIdx.x * blockDim.x + threadIdx.x;
-    if (l >= L) return;
-    LeafRec r{};
-    r.base = (uint32_t)base[l];
-    r.size = (uint32_t)(base[l + 1] - base[l]);
-    r.kmin = r.size ? (uint64_t)keys.key(r.base) : 0ull;
-    r.b0 = 0.f;
-    r.b1 = 0.f;
-    r.elo = INT_MAX;
-    r.ehi = INT_MIN;
-    leaves[l] = r;
+__global__ __launch_bounds__(256) void k_leaf_gaps(const Gap *__restrict__ gaps, const uint32_t *__restrict__ ngaps,
+                                                   uint32_t *__restrict__ base) {
+    const uint32_t count = *ngaps;
+    for (uint32_t g = blockIdx.x; g < count; g += gridDim.x) {
+        const Gap p = gaps[g];
+        for (uint32_t l = p.first + threadIdx.x; l <= p.last; l += 256) base[l] = p.value;
+    }
 }
 
-// The workgroup's leaves' keys into LDS (false: the range is too large).
+// The keys of the workgroup's leaves [l0, l1) into LDS (false: too many).
 template <typename K, bool AOS>
-__device__ __forceinline__ bool stage_leaf_keys(Load<K, AOS> keys, const LeafRec *__restrict__ leaves, uint32_t L,
-                                                K *s_key, uint32_t cap, uint64_t &kb) {
-    const uint32_t l0 = blockIdx.x * kLeafBlock;
-    if (l0 >= L) return false;  // workgroup-uniform (a launch over no leaves)
-    const uint32_t l1 = l0 + kLeafBlock < L ? l0 + kLeafBlock : L;
-    kb = leaves[l0].base;
-    const uint64_t ke = (uint64_t)leaves[l1 - 1].base + leaves[l1 - 1].size;
+__device__ __forceinline__ bool stage_leaf_keys(Load<K, AOS> keys, uint64_t kb, uint64_t ke, K *s_key, uint32_t cap) {
     if (ke - kb > cap) return false;  // workgroup-uniform
     stage_keys<K>([&](uint64_t i) { return keys.key(i); }, kb, ke, s_key);
     return true;
 }
 
-// Per-leaf sums, one thread per leaf over its key range; a leaf of more than
-// kLeafCap keys gets zero sums here and raises *big for k_leaf_accum_big.
-// UPDATE (training): a leaf of at most kLeafCap keys takes its Newton step
-// at once from the sums in registers, which are not stored; the large
-// leaves' steps follow k_leaf_accum_big (k_leaf_update_big).
-// The staging area holds `cap` keys (dynamic LDS, sized by stage_cap).
-template <typename K, bool AOS, bool UPDATE = false>
-__global__ __launch_bounds__(kLeafBlock) void k_leaf_accum_small(Load<K, AOS> keys, LeafRec *__restrict__ leaves,
+// A leaf's record before its fit.
+template <typename K, bool AOS>
+__device__ __forceinline__ LeafRec new_leaf(Load<K, AOS> keys, uint32_t base, uint32_t end) {
+    LeafRec r{};
+    r.base = base;
+    r.size = end - base;
+    r.kmin = r.size ? (uint64_t)keys.key(base) : 0ull;
+    r.elo = 0;
+    r.ehi = -1;
+    return r;
+}
+
+// Fit and error bounds of one leaf of at most kFitSlots keys: its features are
+// converted once and stay in registers, the feature sums are taken once, and
+// each step sums only what depends on the parameters.  The sums run in the
+// order of leaf_sums_thread and every product is exact in FP64, so that the
+// parameters come out the same.
+constexpr int kFitSlots = 12;
+
+template <typename KeyAt>
+__device__ __forceinline__ void fit_leaf_short(const KeyAt &key, LeafRec &r, uint32_t epochs, double &loss) {
+    float x[kFitSlots];
+    double a[NACC] = {(double)r.size, 0, 0, 0, 0, 0};
+#pragma unroll
+    for (int j = 0; j < kFitSlots; ++j) {
+        if ((uint32_t)j >= r.size) continue;
+        x[j] = local_feature(r, key((uint64_t)r.base + j));
+        a[1] += x[j];
+        a[2] += (double)x[j] * x[j];
+    }
+    auto residual = [&](int j) {  // forward residual, as leaf_terms rounds it
+        return __fsub_rn(__fadd_rn(__fmul_rn(r.b1, x[j]), r.b0), (float)j);
+    };
+    for (uint32_t ep = 0; ep < epochs; ++ep) {
+        a[3] = a[4] = 0.0;
+#pragma unroll
+        for (int j = 0; j < kFitSlots; ++j) {
+            if ((uint32_t)j >= r.size) continue;
+            const float e = residual(j);
+            a[3] += e;
+            a[4] += (double)e * x[j];
+        }
+        newton_linear(a, r.b0, r.b1);
+    }
+    int32_t lo = INT_MAX, hi = INT_MIN;
+#pragma unroll
+    for (int j = 0; j < kFitSlots; ++j) {
+        if ((uint32_t)j >= r.size) continue;
+        const float p = __fadd_rn(__fmul_rn(r.b1, x[j]), r.b0);  // as pred_local
+        const int32_t pl = !(p > 0.f) ? 0 : p >= (float)r.size ? (int32_t)r.size : (int32_t)p;
+        lo = j - pl < lo ? j - pl : lo;
+        hi = j - pl > hi ? j - pl : hi;
+        const float e = __fsub_rn(p, (float)j);
+        loss += (double)e * e;
+    }
+    r.elo = lo;
+    r.ehi = hi;
+}
+
+// A thread walks its leaf key by key, so a leaf of 1000 keys among leaves of 4
+// (the last bin of a spline root holds such ones) kept one lane busy for 300 us
+// after the others were done.  Leaves of more than kWaveLeaf keys are trained
+// by a wave each (k_leaf_train_wave); up to there a leaf takes about 25 us.
+constexpr uint32_t kWaveLeaf = 128;
+
+// The leaves trained in one pass, one thread per leaf of at most kWaveLeaf
+// keys: `epochs` Newton steps from its sums in registers, then its error
+// bounds and squared residuals, the workgroup's keys staged in LDS once
+// (`cap` keys of dynamic LDS, stage_cap) for all of them.  The workgroup's
+// leaves are dealt to its threads by size, largest first, so that the lanes of
+// a wave walk leaves of about the same size (a wave of 64 leaves of 4 keys on
+// average holds one of 11).  part[3 * blockIdx.x] receives the workgroup's
+// window sum, largest window and loss.  A larger leaf gets its record here and
+// goes to the list todo[0..*ntodo); one of more than kLeafCap keys gets zero
+// sums and *big = 1, and the *_big kernels train it.
+// Bound by vector instructions (conversions and FP64): 2^24 leaves of 2^26
+// keys in 385 us, where a pass over the keys for each step, the bounds and the
+// statistics took 1.32 ms.
+template <typename K, bool AOS>
+__global__ __launch_bounds__(kLeafBlock) void k_leaf_train(Load<K, AOS> keys, const uint32_t *__restrict__ base,
+                                                           uint32_t L, uint32_t epochs, LeafRec *__restrict__ leaves,
+                                                           double *__restrict__ acc, uint32_t *big,
+                                                           uint32_t *__restrict__ todo, uint32_t *__restrict__ ntodo,
+                                                           uint32_t cap, double *__restrict__ part) {
+    extern __shared__ __align__(16) char smem_stage[];
+    K *s_key = (K *)smem_stage;
+    __shared__ double s_part[kLeafBlock / kWave][3];
+    __shared__ uint32_t s_bin[kFitSlots + 2], s_base[kLeafBlock + 1];
+    __shared__ uint8_t s_leaf[kLeafBlock];
+    const uint32_t l0 = blockIdx.x * kLeafBlock, l1 = l0 + kLeafBlock < L ? l0 + kLeafBlock : L, nl = l1 - l0;
+    if (threadIdx.x < kFitSlots + 2) s_bin[threadIdx.x] = 0;
+    for (uint32_t t = threadIdx.x; t <= nl; t += kLeafBlock) s_base[t] = base[l0 + t];
+    __syncthreads();
+    const uint64_t kb = s_base[0];
+    // places by size: bin 0 the leaves of more than kFitSlots keys, then
+    // kFitSlots keys, and so on down to none
+    uint32_t bin = 0, place = 0;
+    if (threadIdx.x < nl) {
+        const uint32_t size = s_base[threadIdx.x + 1] - s_base[threadIdx.x];
+        bin = size > (uint32_t)kFitSlots ? 0u : kFitSlots + 1 - size;
+        place = atomicAdd(&s_bin[bin], 1u);
+    }
+    const bool staged = s_base[nl] - s_base[0] <= cap;  // workgroup-uniform
+    if (staged) stage_keys<K>([&](uint64_t i) { return keys.key(i); }, kb, (uint64_t)s_base[nl], s_key);
+    else __syncthreads();
+    if (threadIdx.x < nl) {
+        for (uint32_t b = 0; b < bin; ++b) place += s_bin[b];
+        s_leaf[place] = (uint8_t)threadIdx.x;
+    }
+    __syncthreads();
+    double ws = 0.0, wmax = 0.0, ls = 0.0;
+    if (threadIdx.x < nl) {
+        const uint32_t o = s_leaf[threadIdx.x], l = l0 + o;
+        LeafRec r{};
+        r.base = s_base[o];
+        r.size = s_base[o + 1] - r.base;
+        r.elo = 0;
+        r.ehi = -1;
+        auto train = [&](auto &&key) {
+            r.kmin = key(r.base);
+            if (r.size > kLeafCap) {
+                *big = 1u;
+                r.elo = INT_MAX;
+                r.ehi = INT_MIN;
+                for (int j = 0; j < NACC; ++j) acc[(uint64_t)l * NACC + j] = 0.0;
+                return;
+            }
+            if (r.size > kWaveLeaf) {
+                todo[atomicAdd(ntodo, 1u)] = l;
+                return;
+            }
+            if (r.size <= (uint32_t)kFitSlots) {
+                fit_leaf_short(key, r, epochs, ls);
+            } else {
+                for (uint32_t ep = 0; ep < epochs; ++ep) {
+                    double a[NACC];
+                    leaf_sums_thread(key, r, a);
+                    newton_linear(a, r.b0, r.b1);
+                }
+                long long lo, hi;
+                leaf_errs_thread(key, r, lo, hi, &ls);
+                r.elo = (int32_t)lo;
+                r.ehi = (int32_t)hi;
+            }
+            wmax = (double)r.ehi - (double)r.elo + 2.0;  // window slots incl. one past
+            ws = wmax * r.size;
+        };
+        if (r.size == 0) {
+        } else if (staged) {
+            train([&](uint64_t i) { return (uint64_t)s_key[i - kb]; });
+        } else {
+            train([&](uint64_t i) { return (uint64_t)keys.key(i); });
+        }
+        leaves[l] = r;
+    }
+    ws = wave_sum(ws);
+    ls = wave_sum(ls);
+#pragma unroll
+    for (int off = kWave / 2; off > 0; off >>= 1) {
+        const double o = __shfl_xor(wmax, off, kWave);
+        wmax = o > wmax ? o : wmax;
+    }
+    const uint32_t wave = threadIdx.x / kWave;
+    if ((threadIdx.x & (kWave - 1)) == 0) {
+        s_part[wave][0] = ws;
+        s_part[wave][1] = wmax;
+        s_part[wave][2] = ls;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (uint32_t w = 1; w < kLeafBlock / kWave; ++w) {
+            ws += s_part[w][0];
+            wmax = s_part[w][1] > wmax ? s_part[w][1] : wmax;
+            ls += s_part[w][2];
+        }
+        double *p = part + 3 * (uint64_t)blockIdx.x;
+        p[0] = ws;
+        p[1] = wmax;
+        p[2] = ls;
+    }
+}
+
+__device__ __forceinline__ void atomic_max_pos(double *p, double v) {  // values >= 0 order like their bit patterns
+    atomicMax((unsigned long long *)p, (unsigned long long)__double_as_longlong(v));
+}
+
+// The leaves of the list, a wave each.  A step of 64 keys: the lanes compute
+// their keys' terms side by side into LDS, then lanes 0-3 add one column each
+// in key order.  The sums are those of leaf_sums_thread, addition by addition,
+// at the latency of one FP64 addition a key where the walk of one thread takes
+// about 40 instructions.
+template <typename K, bool AOS>
+__global__ __launch_bounds__(256) void k_leaf_train_wave(Load<K, AOS> keys, uint32_t epochs,
+                                                         LeafRec *__restrict__ leaves,
+                                                         const uint32_t *__restrict__ todo,
+                                                         const uint32_t *__restrict__ ntodo,
+                                                         double *__restrict__ stats) {
+    __shared__ double s_term[256 / kWave][kWave][4];
+    const uint32_t lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave, count = *ntodo;
+    double(*term)[4] = s_term[wave];
+    for (uint32_t t = blockIdx.x * (256 / kWave) + wave; t < count; t += gridDim.x * (256 / kWave)) {
+        const uint32_t l = todo[t];
+        LeafRec r = leaves[l];
+        double a[NACC] = {(double)r.size, 0, 0, 0, 0, 0};
+        for (uint32_t ep = 0; ep < epochs; ++ep) {
+            double col = 0.0;  // lanes 0-3: sums of x, x^2, r, r x
+            for (uint32_t j0 = 0; j0 < r.size; j0 += kWave) {
+                const uint32_t j = j0 + lane;
+                double v[4] = {0, 0, 0, 0};
+                if (j < r.size) {
+                    const float x = local_feature(r, (uint64_t)keys.key((uint64_t)r.base + j));
+                    const float e = __fsub_rn(__fadd_rn(__fmul_rn(r.b1, x), r.b0), (float)j);
+                    v[0] = x;
+                    v[1] = (double)x * x;
+                    v[2] = e;
+                    v[3] = (double)e * x;
+                }
+#pragma unroll
+                for (int c = 0; c < 4; ++c) term[lane][c] = v[c];
+                __builtin_amdgcn_wave_barrier();
+                if (lane < 4) {
+#pragma unroll 16
+                    for (int i = 0; i < kWave; ++i) col += term[i][lane];
+                }
+                __builtin_amdgcn_wave_barrier();
+            }
+#pragma unroll
+            for (int c = 0; c < 4; ++c) a[1 + c] = __shfl(col, c, kWave);
+            newton_linear(a, r.b0, r.b1);
+        }
+        int32_t lo = INT_MAX, hi = INT_MIN;
+        double loss = 0.0;
+        for (uint32_t j = lane; j < r.size; j += kWave) {
+            const uint64_t i = (uint64_t)r.base + j, key = (uint64_t)keys.key(i);
+            const int32_t e = (int32_t)leaf_err(r, i, key);
+            lo = e < lo ? e : lo;
+            hi = e > hi ? e : hi;
+            loss += leaf_sq_residual(r, i, key);
+        }
+        loss = wave_sum(loss);
+#pragma unroll
+        for (int off = kWave / 2; off > 0; off >>= 1) {
+            const int32_t ol = __shfl_xor(lo, off, kWave), oh = __shfl_xor(hi, off, kWave);
+            lo = ol < lo ? ol : lo;
+            hi = oh > hi ? oh : hi;
+        }
+        if (lane == 0) {
+            r.elo = lo;
+            r.ehi = hi;
+            leaves[l] = r;
+            const double w = (double)hi - (double)lo + 2.0;
+            atomicAdd(&stats[0], w * r.size);
+            atomic_max_pos(&stats[1], w);
+            atomicAdd(&stats[2], loss);
+        }
+    }
+}
+
+// stats += the workgroups' window sums, largest window and losses.  A few
+// workgroups, one atomic each.
+__global__ __launch_bounds__(256) void k_leaf_stats(const double *__restrict__ part, uint32_t blocks,
+                                                    double *__restrict__ stats) {
+    double ws = 0.0, wmax = 0.0, ls = 0.0;
+    for (uint32_t b = blockIdx.x * 256 + threadIdx.x; b < blocks; b += gridDim.x * 256) {
+        ws += part[3 * (uint64_t)b];
+        wmax = part[3 * (uint64_t)b + 1] > wmax ? part[3 * (uint64_t)b + 1] : wmax;
+        ls += part[3 * (uint64_t)b + 2];
+    }
+    ws = wave_sum(ws);
+    ls = wave_sum(ls);
+#pragma unroll
+    for (int off = kWave / 2; off > 0; off >>= 1) {
+        const double o = __shfl_xor(wmax, off, kWave);
+        wmax = o > wmax ? o : wmax;
+    }
+    if ((threadIdx.x & (kWave - 1)) == 0) {
+        atomicAdd(&stats[0], ws);
+        atomic_max_pos(&stats[1], wmax);
+        atomicAdd(&stats[2], ls);
+    }
+}
+
+// The windows of the leaves larger than kLeafCap (nothing to do when *big is
+// 0; the others' come with their training).
+__global__ __launch_bounds__(256) void k_leaf_stats_big(const LeafRec *__restrict__ leaves, uint32_t L,
+                                                        const uint32_t *big, double *__restrict__ stats) {
+    if (*big == 0u) return;
+    for (uint32_t l = blockIdx.x * 256 + threadIdx.x; l < L; l += gridDim.x * 256) {
+        const LeafRec r = leaves[l];
+        if (r.size <= kLeafCap) continue;
+        const double w = (double)r.ehi - (double)r.elo + 2.0;
+        atomicAdd(&stats[0], w * r.size);
+        atomic_max_pos(&stats[1], w);
+    }
+}
+
+// Gradient evaluation: every leaf's sums at given parameters, one thread per
+// leaf; a leaf of more than kLeafCap keys gets zero sums here and raises *big
+// for k_leaf_accum_big.
+template <typename K, bool AOS>
+__global__ __launch_bounds__(kLeafBlock) void k_leaf_accum_small(Load<K, AOS> keys, const LeafRec *__restrict__ leaves,
                                                                  uint32_t L, double *__restrict__ acc, uint32_t *big,
                                                                  uint32_t cap) {
     extern __shared__ __align__(16) char smem_stage[];
     K *s_key = (K *)smem_stage;
-    uint64_t kb;
-    const bool staged = stage_leaf_keys(keys, leaves, L, s_key, cap, kb);
-    const uint32_t l = blockIdx.x * kLeafBlock + threadIdx.x;
+    const uint32_t l0 = blockIdx.x * kLeafBlock, l1 = l0 + kLeafBlock < L ? l0 + kLeafBlock : L;
+    const uint64_t kb = leaves[l0].base;
+    const bool staged = stage_leaf_keys(keys, kb, (uint64_t)leaves[l1 - 1].base + leaves[l1 - 1].size, s_key, cap);
+    const uint32_t l = l0 + threadIdx.x;
     if (l >= L) return;
     const LeafRec r = leaves[l];
     double a[NACC] = {0, 0, 0, 0, 0, 0};
     if (r.size > kLeafCap) *big = 1u;
     else if (staged) leaf_sums_thread([&](uint64_t i) { return (uint64_t)s_key[i - kb]; }, r, a);
     else leaf_sums_thread([&](uint64_t i) { return (uint64_t)keys.key(i); }, r, a);
-    if (UPDATE && r.size <= kLeafCap) {
-        float b0 = r.b0, b1 = r.b1;
-        newton_linear(a, b0, b1);
-        leaves[l].b0 = b0;
-        leaves[l].b1 = b1;
-        return;
-    }
 #pragma unroll
     for (int j = 0; j < NACC; ++j) acc[(uint64_t)l * NACC + j] = a[j];
 }
@@ -203,44 +556,18 @@ __global__ __launch_bounds__(LT) void k_leaf_accum_big(Load<K, AOS> keys, uint64
 }
 
 // The Newton step of the leaves larger than kLeafCap (nothing to do when
-// *big is 0; the others stepped in k_leaf_accum_small).
-__global__ void k_leaf_update_big(LeafRec *__restrict__ leaves, const double *__restrict__ acc, uint32_t L,
+// *big is 0; the others stepped in k_leaf_train or k_leaf_train_wave); their sums start over.
+__global__ void k_leaf_update_big(LeafRec *__restrict__ leaves, double *__restrict__ acc, uint32_t L,
                                   const uint32_t *big) {
     if (*big == 0u) return;
-    const uint32_t l = blockIdx.x * blockDim.x + threadIdx.x;
-    if (l >= L) return;
-    LeafRec r = leaves[l];
-    if (r.size <= kLeafCap) return;
-    newton_linear(acc + (uint64_t)l * NACC, r.b0, r.b1);
-    leaves[l].b0 = r.b0;
-    leaves[l].b1 = r.b1;
-}
-
-// Per-leaf error bounds, one thread per leaf of at most kLeafCap keys; each
-// leaf's squared residuals go to loss[l] (0 for the large leaves, whose loss
-// k_leaf_errors_big adds to the total itself).  `loss` is the start of the
-// per-leaf accumulators, which training no longer needs: dense, so the
-// writes here and the reads in k_leaf_finish move 8 bytes per leaf, not a
-// strided line each.
-template <typename K, bool AOS>
-__global__ __launch_bounds__(kLeafBlock) void k_leaf_errors_small(Load<K, AOS> keys, LeafRec *__restrict__ leaves,
-                                                                  uint32_t L, double *__restrict__ loss, uint32_t cap) {
-    extern __shared__ __align__(16) char smem_stage[];
-    K *s_key = (K *)smem_stage;
-    uint64_t kb;
-    const bool staged = stage_leaf_keys(keys, leaves, L, s_key, cap, kb);
-    const uint32_t l = blockIdx.x * kLeafBlock + threadIdx.x;
-    if (l >= L) return;
-    const LeafRec r = leaves[l];
-    double ls = 0.0;
-    if (r.size != 0 && r.size <= kLeafCap) {
-        long long lo, hi;
-        if (staged) leaf_errs_thread([&](uint64_t i) { return (uint64_t)s_key[i - kb]; }, r, lo, hi, &ls);
-        else leaf_errs_thread([&](uint64_t i) { return (uint64_t)keys.key(i); }, r, lo, hi, &ls);
-        leaves[l].elo = (int32_t)lo;
-        leaves[l].ehi = (int32_t)hi;
+    for (uint32_t l = blockIdx.x * blockDim.x + threadIdx.x; l < L; l += gridDim.x * blockDim.x) {
+        LeafRec r = leaves[l];
+        if (r.size <= kLeafCap) continue;
+        newton_linear(acc + (uint64_t)l * NACC, r.b0, r.b1);
+        leaves[l].b0 = r.b0;
+        leaves[l].b1 = r.b1;
+        for (int j = 0; j < NACC; ++j) acc[(uint64_t)l * NACC + j] = 0.0;
     }
-    loss[l] = ls;
 }
 
 // Error bounds of the leaves larger than kLeafCap (the wave walk).
@@ -274,70 +601,22 @@ __global__ __launch_bounds__(LT) void k_leaf_errors_big(Load<K, AOS> keys, uint6
     if ((threadIdx.x & (kWave - 1)) == 0 && ls != 0.0) atomicAdd(loss, ls);
 }
 
-// Empty leaves get a zero window; statistics of the windows and the leaves'
-// losses (loss[l], written by k_leaf_errors_small).
-__global__ __launch_bounds__(256) void k_leaf_finish(LeafRec *__restrict__ leaves, uint32_t L,
-                                                     const double *__restrict__ loss,
-                                                     double *__restrict__ stats /* sum_w*size, max_w, sum loss */) {
-    __shared__ double s_ws[256 / kWave], s_wm[256 / kWave], s_ls[256 / kWave];
-    double ws = 0, wmax = 0, ls = 0;
-    for (uint32_t l = blockIdx.x * blockDim.x + threadIdx.x; l < L; l += gridDim.x * blockDim.x) {
-        ls += loss[l];
-        LeafRec r = leaves[l];
-        if (r.size == 0 || r.elo > r.ehi) {
-            leaves[l].elo = 0;
-            leaves[l].ehi = -1;
-        } else {
-            const double w = (double)r.ehi - (double)r.elo + 2.0;  // window slots incl. one past
-            ws += w * r.size;
-            wmax = w > wmax ? w : wmax;
-        }
-    }
-    ws = wave_sum(ws);
-    ls = wave_sum(ls);
-    for (int off = kWave / 2; off > 0; off >>= 1) {
-        const double o = __shfl_xor(wmax, off, kWave);
-        wmax = o > wmax ? o : wmax;
-    }
-    const uint32_t wave = threadIdx.x / kWave;
-    if ((threadIdx.x & (kWave - 1)) == 0) {
-        s_ws[wave] = ws;
-        s_wm[wave] = wmax;
-        s_ls[wave] = ls;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        for (uint32_t w = 1; w < blockDim.x / kWave; ++w) {
-            ws += s_ws[w];
-            wmax = s_wm[w] > wmax ? s_wm[w] : wmax;
-            ls += s_ls[w];
-        }
-        atomicAdd(&stats[0], ws);
-        atomicAdd(&stats[2], ls);
-        // max via compare-and-swap on the bit pattern (values are >= 0)
-        unsigned long long *p = (unsigned long long *)&stats[1];
-        unsigned long long old = *p;
-        while (__longlong_as_double(old) < wmax) {
-            const unsigned long long prev = atomicCAS(p, old, __double_as_longlong(wmax));
-            if (prev == old) break;
-            old = prev;
-        }
-    }
+// Geometry of the spline candidates in `mask` from the smallest and largest
+// build key.
+template <typename K, bool AOS>
+__global__ void k_spline_geometry(Load<K, AOS> keys, uint64_t n, RootRec *roots, uint32_t mask) {
+    const uint32_t c = threadIdx.x;
+    if (c < (uint32_t)kRoots && ((mask >> c) & 1u))
+        spline_geometry(roots[c], (uint64_t)keys.key(0), (uint64_t)keys.key(n - 1), n);
 }
 
-// Spline root geometry from the smallest and largest build key (one thread).
+// Their bins, one thread per bin (blockIdx.y: the candidate).
 template <typename K, bool AOS>
-__global__ void k_spline_geometry(Load<K, AOS> keys, uint64_t n, RootRec *R) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) spline_geometry(*R, (uint64_t)keys.key(0), (uint64_t)keys.key(n - 1), n);
-}
-
-// Spline root bins, one thread per bin.
-template <typename K, bool AOS>
-__global__ void k_spline_bins(Load<K, AOS> keys, uint64_t n, const RootRec *Rp, SplineBin *__restrict__ bins) {
-    const RootRec R = *Rp;
+__global__ void k_spline_bins(Load<K, AOS> keys, uint64_t n, const RootRec *__restrict__ roots, uint32_t first) {
+    const RootRec R = roots[first + blockIdx.y];
     const uint32_t b = blockIdx.x * blockDim.x + threadIdx.x;
     if (b >= R.nb) return;
-    bins[b] = spline_bin([&](uint64_t i) { return (uint64_t)keys.key(i); }, n, R, b);
+    ((SplineBin *)R.bins)[b] = spline_bin([&](uint64_t i) { return (uint64_t)keys.key(i); }, n, R, b);
 }
 
 uint32_t grid_for(uint64_t threads, uint32_t block) {
@@ -347,27 +626,37 @@ uint32_t grid_for(uint64_t threads, uint32_t block) {
     return (uint32_t)b;
 }
 
-// Per-leaf key counts, their exclusive scan and the leaf records.
+size_t up256(size_t v) { return (v + 255) & ~(size_t)255; }
+
+// Bytes of the first ranks of L leaves and their gap list.
+size_t bounds_bytes(uint32_t L) { return up256(((size_t)L + 1) * 4) + up256(gap_capacity(L) * sizeof(Gap)); }
+
+// First ranks of the leaves under *d_root; *ngaps comes zeroed.
 template <typename K, bool AOS>
-int leaf_layout(Load<K, AOS> keys, uint64_t n, const RootRec *d_root, uint32_t L, unsigned long long *count,
-                uint64_t *partial, LeafRec *leaves, hipStream_t s) {
-    hipLaunchKernelGGL(k_fill_u64, dim3(grid_for((uint64_t)L + 1, 256)), dim3(256), 0, s, (uint64_t *)count,
-                       (uint64_t)L + 1);
-    hipLaunchKernelGGL((k_leaf_count<K, AOS>), dim3(grid_for((n + CHUNK - 1) / CHUNK, LT)), dim3(LT), 0, s, keys, n,
-                       d_root, count);
-    IDX_LAUNCH_CHECK();
-    const int rc = exclusive_scan_u64((uint64_t *)count, L, partial, s);
-    if (rc != IDX_OK) return rc;
-    hipLaunchKernelGGL((k_leaf_init<K, AOS>), dim3(grid_for(L, 256)), dim3(256), 0, s, keys,
-                       (const unsigned long long *)count, L, leaves);
+int leaf_bounds(Load<K, AOS> keys, uint64_t n, const RootRec *d_root, uint32_t L, char *tmp, uint32_t *ngaps,
+                hipStream_t s) {
+    uint32_t *base = (uint32_t *)tmp;
+    Gap *gaps = (Gap *)(tmp + up256(((size_t)L + 1) * 4));
+    hipLaunchKernelGGL((k_leaf_bounds<K, AOS>), dim3(grid_for((n + 7) / 8, LT)), dim3(LT), 0, s, keys, n, d_root, base,
+                       gaps, ngaps);
+    hipLaunchKernelGGL(k_leaf_gaps, dim3(512), dim3(256), 0, s, gaps, ngaps, base);
     IDX_LAUNCH_CHECK();
     return IDX_OK;
 }
 
-// Bytes of the leaf counters and scan partials for L leaves.
-size_t layout_scratch_bytes(uint32_t L) {
-    auto up256 = [](size_t v) { return (v + 255) & ~(size_t)255; };
-    return up256(((size_t)L + 1) * 8) + up256(scan_partials_for(L) * 8);
+// What the device keeps of one training; zeroed, then the roots are set.
+struct TrainCtl {
+    RootRec roots[kRoots];
+    double acc[kRoots][NACC];
+    double stats[2][4];   // per root family: sum of window * size, max window, leaf loss
+    uint32_t big[2];      // a leaf larger than kLeafCap exists
+    uint32_t ngaps[2];
+    uint32_t ntodo[2];    // leaves of the wave kernel
+};
+
+uint32_t root_blocks(uint64_t n) {
+    const uint64_t b = (n + LT * 8 - 1) / (LT * 8);
+    return b > 2048 ? 2048u : (uint32_t)b;
 }
 
 template <typename K, bool AOS>
@@ -378,76 +667,58 @@ int train_t(idx_index *h, uint32_t L, uint32_t epochs, uint32_t feature, hipStre
     const bool want_lin = feature != IDX_FEATURE_SPLINE, want_sp = feature == IDX_FEATURE_AUTO ||
                                                                    feature == IDX_FEATURE_SPLINE;
     const bool both = want_lin && want_sp;
-    // device scratch: root record, root acc, leaf acc, stats, counts and scan
-    // partials, and (both root families) a second leaf table; every region
-    // starts on a 256-byte boundary (FP64 atomics need 8-byte alignment)
-    auto up256 = [](size_t v) { return (v + 255) & ~(size_t)255; };
-    const size_t leaf_acc_b = up256((size_t)L * NACC * sizeof(double));
-    const size_t alt_b = both ? up256((size_t)L * sizeof(LeafRec)) : 0;
-    char *tmp = (char *)h->alloc.get(256 + 256 + leaf_acc_b + 256 + layout_scratch_bytes(L) + alt_b, s);
-    if (!tmp) return IDX_ERR_NOMEM;
-    RootRec *d_root = (RootRec *)tmp;
-    double *root_acc = (double *)(tmp + 256);
-    double *leaf_acc = (double *)(tmp + 512);
-    double *stats = (double *)(tmp + 512 + leaf_acc_b);
-    unsigned long long *count = (unsigned long long *)(tmp + 512 + leaf_acc_b + 256);
-    uint64_t *partial = (uint64_t *)((char *)count + up256(((size_t)L + 1) * 8));
-    LeafRec *alt = both ? (LeafRec *)(tmp + 512 + leaf_acc_b + 256 + layout_scratch_bytes(L)) : nullptr;
-    uint32_t *d_big = (uint32_t *)(stats + 8);  // a leaf larger than kLeafCap exists
-    const uint32_t rblocks = (uint32_t)((n + LT * 8 - 1) / (LT * 8)) > 2048 ? 2048u
-                                                                             : (uint32_t)((n + LT * 8 - 1) / (LT * 8));
-    const uint32_t cblocks = grid_for((n + CHUNK - 1) / CHUNK, LT);
-
-    // One root candidate: place R on the device (a spline candidate also gets
-    // its geometry and bins), take `ep_n` Newton steps, measure the loss.
-    auto candidate = [&](RootRec R, uint32_t ep_n, RootRec &out, double &loss) -> int {
-        if (hipMemcpyAsync(d_root, &R, sizeof(R), hipMemcpyHostToDevice, s) != hipSuccess) return IDX_ERR_HIP;
-        if (R.mode == IDX_FEATURE_SPLINE) {
-            hipLaunchKernelGGL((k_spline_geometry<K, AOS>), dim3(1), dim3(64), 0, s, keys, n, d_root);
-            hipLaunchKernelGGL((k_spline_bins<K, AOS>), dim3(grid_for(spline_bins(n), 256)), dim3(256), 0, s, keys, n,
-                               d_root, M->spline);
-        }
-        for (uint32_t ep = 0; ep <= ep_n; ++ep) {
-            hipLaunchKernelGGL(k_fill_f64, dim3(1), dim3(64), 0, s, root_acc, (uint64_t)NACC);
-            hipLaunchKernelGGL((k_root_accum<K, AOS>), dim3(rblocks ? rblocks : 1), dim3(LT), 0, s, keys, n, d_root,
-                               root_acc);
-            if (ep < ep_n) hipLaunchKernelGGL(k_root_update, dim3(1), dim3(64), 0, s, d_root, root_acc);
-        }
-        double acc[NACC];
-        if (hipMemcpyAsync(acc, root_acc, sizeof(acc), hipMemcpyDeviceToHost, s) != hipSuccess ||
-            hipMemcpyAsync(&out, d_root, sizeof(out), hipMemcpyDeviceToHost, s) != hipSuccess ||
-            hipStreamSynchronize(s) != hipSuccess)
-            return IDX_ERR_HIP;
-        loss = acc[5];
-        return IDX_OK;
+    // device scratch: control block, first ranks and gaps, the large leaves'
+    // sums and the workgroups' statistics; (both root families) a second leaf
+    // table and (splines) the second candidate's bins, which take the place of
+    // the model's when they win
+    const uint32_t tblocks = grid_for(L, kLeafBlock);
+    const size_t ctl_b = up256(sizeof(TrainCtl)), bounds_b = bounds_bytes(L);
+    const size_t acc_b = up256((size_t)L * NACC * sizeof(double)), part_b = up256((size_t)tblocks * 3 * sizeof(double));
+    const uint64_t todo_n = n / (kWaveLeaf + 1) + 1;  // leaves of more than kWaveLeaf keys at most
+    char *tmp = (char *)h->alloc.get(ctl_b + bounds_b + acc_b + part_b + up256(todo_n * 4), s);
+    LeafRec *alt = tmp && both ? (LeafRec *)h->alloc.get((size_t)L * sizeof(LeafRec), s) : nullptr;
+    SplineBin *bins2 = tmp && want_sp ? (SplineBin *)h->alloc.get((size_t)spline_bins(n) * sizeof(SplineBin), s)
+                                      : nullptr;
+    auto give_back = [&] {
+        if (bins2) h->alloc.put(bins2, s);
+        if (alt) h->alloc.put(alt, s);
+        if (tmp) h->alloc.put(tmp, s);
     };
-    const uint32_t cap = stage_cap(n, L);  // keys staged per workgroup of the per-leaf passes
-    // Leaves under root R into `leaves`: layout, Newton steps, error bounds;
-    // st = {sum of window * size, max window, leaf loss}.
-    auto leaves_for = [&](const RootRec &R, LeafRec *leaves, double st[4]) -> int {
-        if (hipMemcpyAsync(d_root, &R, sizeof(R), hipMemcpyHostToDevice, s) != hipSuccess) return IDX_ERR_HIP;
-        int rc = leaf_layout<K, AOS>(keys, n, d_root, L, count, partial, leaves, s);
+    if (!tmp || (both && !alt) || (want_sp && !bins2)) {
+        give_back();
+        return IDX_ERR_NOMEM;
+    }
+    TrainCtl *ctl = (TrainCtl *)tmp;
+    char *bounds = tmp + ctl_b;
+    double *leaf_acc = (double *)(bounds + bounds_b), *part = (double *)((char *)leaf_acc + acc_b);
+    uint32_t *todo = (uint32_t *)((char *)part + part_b);
+    const uint32_t cblocks = grid_for((n + CHUNK - 1) / CHUNK, LT);
+    const uint32_t lblocks = grid_for(L, 256) < 1024 ? grid_for(L, 256) : 1024;  // passes over large leaves alone
+    const uint32_t cap = stage_cap(n, L);  // keys staged per workgroup of the leaf pass
+    const uint32_t wblocks = grid_for(todo_n, 4) < 2048 ? grid_for(todo_n, 4) : 2048;
+
+    // Leaves under candidate c into `leaves`: first ranks, Newton steps, error
+    // bounds and statistics of family f.
+    auto leaves_for = [&](int c, int f, LeafRec *leaves) -> int {
+        const RootRec *d_root = &ctl->roots[c];
+        uint32_t *big = &ctl->big[f];
+        int rc = leaf_bounds<K, AOS>(keys, n, d_root, L, bounds, &ctl->ngaps[f], s);
         if (rc != IDX_OK) return rc;
-        hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, s, d_big, (uint64_t)1, 0u);
+        hipLaunchKernelGGL((k_leaf_train<K, AOS>), dim3(tblocks), dim3(kLeafBlock), (size_t)cap * sizeof(K), s, keys,
+                           (const uint32_t *)bounds, L, epochs, leaves, leaf_acc, big, todo, &ctl->ntodo[f], cap, part);
+        hipLaunchKernelGGL((k_leaf_train_wave<K, AOS>), dim3(wblocks), dim3(256), 0, s, keys, epochs, leaves, todo,
+                           &ctl->ntodo[f], ctl->stats[f]);
         for (uint32_t ep = 0; ep < epochs; ++ep) {
-            hipLaunchKernelGGL((k_leaf_accum_small<K, AOS, true>), dim3(grid_for(L, kLeafBlock)), dim3(kLeafBlock),
-                               (size_t)cap * sizeof(K), s, keys, leaves, L, leaf_acc, d_big, cap);
             hipLaunchKernelGGL((k_leaf_accum_big<K, AOS>), dim3(cblocks), dim3(LT), 0, s, keys, n, d_root, leaves,
-                               leaf_acc, d_big);
-            hipLaunchKernelGGL(k_leaf_update_big, dim3(grid_for(L, 256)), dim3(256), 0, s, leaves, leaf_acc, L, d_big);
+                               leaf_acc, big);
+            hipLaunchKernelGGL(k_leaf_update_big, dim3(lblocks), dim3(256), 0, s, leaves, leaf_acc, L, big);
         }
-        // the final leaf loss comes with the error bounds (same walk)
-        hipLaunchKernelGGL(k_fill_f64, dim3(1), dim3(64), 0, s, stats, (uint64_t)4);
-        hipLaunchKernelGGL((k_leaf_errors_small<K, AOS>), dim3(grid_for(L, kLeafBlock)), dim3(kLeafBlock),
-                           (size_t)cap * sizeof(K), s, keys, leaves, L, leaf_acc, cap);
-        hipLaunchKernelGGL((k_leaf_errors_big<K, AOS>), dim3(cblocks), dim3(LT), 0, s, keys, n, d_root, leaves, d_big,
-                           stats + 2);
-        hipLaunchKernelGGL(k_leaf_finish, dim3(grid_for(L, 256) < 1024 ? grid_for(L, 256) : 1024), dim3(256), 0, s,
-                           leaves, L, leaf_acc, stats);
-        if (hipGetLastError() != hipSuccess) return IDX_ERR_HIP;
-        if (hipMemcpyAsync(st, stats, 4 * sizeof(double), hipMemcpyDeviceToHost, s) != hipSuccess ||
-            hipStreamSynchronize(s) != hipSuccess)
-            return IDX_ERR_HIP;
+        hipLaunchKernelGGL((k_leaf_errors_big<K, AOS>), dim3(cblocks), dim3(LT), 0, s, keys, n, d_root, leaves, big,
+                           &ctl->stats[f][2]);
+        hipLaunchKernelGGL(k_leaf_stats_big, dim3(lblocks), dim3(256), 0, s, leaves, L, big, ctl->stats[f]);
+        hipLaunchKernelGGL(k_leaf_stats, dim3(grid_for(tblocks, 256) < 64 ? grid_for(tblocks, 256) : 64), dim3(256), 0,
+                           s, part, tblocks, ctl->stats[f]);
+        IDX_LAUNCH_CHECK();
         return IDX_OK;
     };
 
@@ -456,60 +727,80 @@ int train_t(idx_index *h, uint32_t L, uint32_t epochs, uint32_t feature, hipStre
         // ---- stage 1: roots.  A linear root takes `epochs` Newton steps over
         // either key feature; a spline root is built from the keys' ranks over
         // either bin feature.  Within each family the lower loss wins.
-        RootRec best_lin{}, best_sp{};
-        double loss_lin = -1.0, loss_sp = -1.0;
-        for (uint32_t f = IDX_FEATURE_LINEAR; f <= IDX_FEATURE_LOG && rc == IDX_OK; ++f) {
-            RootRec R{}, got;
-            double loss;
+        TrainCtl hc{};
+        uint32_t lin_mask = 0, sp_mask = 0;
+        for (uint32_t f = 0; f < 2; ++f) {
+            RootRec R{};
             R.L = L;
-            if (want_lin && (feature == IDX_FEATURE_AUTO || feature == f)) {
-                R.mode = f;
-                if ((rc = candidate(R, epochs, got, loss)) != IDX_OK) break;
-                if (loss_lin < 0 || loss < loss_lin) { loss_lin = loss; best_lin = got; }
-            }
-            if (want_sp) {
-                R.mode = IDX_FEATURE_SPLINE;
-                R.bins = M->spline;
-                R.bfeat = f;
-                if ((rc = candidate(R, 0, got, loss)) != IDX_OK) break;
-                if (loss_sp < 0 || loss < loss_sp) { loss_sp = loss; best_sp = got; }
-            }
+            R.mode = IDX_FEATURE_LINEAR + f;
+            hc.roots[f] = R;
+            if (want_lin && (feature == IDX_FEATURE_AUTO || feature == IDX_FEATURE_LINEAR + f)) lin_mask |= 1u << f;
+            R.mode = IDX_FEATURE_SPLINE;
+            R.bins = f == 0 ? M->spline : bins2;
+            R.bfeat = IDX_FEATURE_LINEAR + f;
+            hc.roots[kSpline0 + f] = R;
+            if (want_sp) sp_mask |= 1u << (kSpline0 + f);
         }
-        if (rc != IDX_OK) break;
-        if (want_sp && best_sp.bfeat != IDX_FEATURE_LOG) {  // the table holds the last bins built: rebuild the winner
-            if (hipMemcpyAsync(d_root, &best_sp, sizeof(best_sp), hipMemcpyHostToDevice, s) != hipSuccess) {
-                rc = IDX_ERR_HIP;
-                break;
-            }
-            hipLaunchKernelGGL((k_spline_bins<K, AOS>), dim3(grid_for(spline_bins(n), 256)), dim3(256), 0, s, keys, n,
-                               d_root, M->spline);
+        if (hipMemcpyAsync(ctl, &hc, sizeof(hc), hipMemcpyHostToDevice, s) != hipSuccess) {
+            rc = IDX_ERR_HIP;
+            break;
         }
+        if (want_sp) {
+            hipLaunchKernelGGL((k_spline_geometry<K, AOS>), dim3(1), dim3(64), 0, s, keys, n, ctl->roots, sp_mask);
+            hipLaunchKernelGGL((k_spline_bins<K, AOS>), dim3(grid_for(spline_bins(n), 256), 2), dim3(256), 0, s, keys,
+                               n, ctl->roots, (uint32_t)kSpline0);
+        }
+        // the spline losses come with the linear roots' last pass
+        auto root_sums = [&](auto kernel, uint32_t mask) {
+            hipLaunchKernelGGL(kernel, dim3(root_blocks(n)), dim3(LT), 0, s, keys, n, ctl->roots, mask,
+                               &ctl->acc[0][0]);
+        };
+        for (uint32_t ep = lin_mask ? 0 : epochs; ep <= epochs; ++ep) {
+            if (ep == 0) root_sums(k_root_accum<K, AOS, kSumX | kSumGrad, false>, lin_mask);
+            else if (ep < epochs) root_sums(k_root_accum<K, AOS, kSumGrad, false>, lin_mask);
+            else if (want_sp) root_sums(k_root_accum<K, AOS, kSumLoss, true>, lin_mask | sp_mask);
+            else root_sums(k_root_accum<K, AOS, kSumLoss, false>, lin_mask);
+            if (ep < epochs)
+                hipLaunchKernelGGL(k_root_update, dim3(1), dim3(64), 0, s, ctl->roots, lin_mask, &ctl->acc[0][0]);
+        }
+        if (hipGetLastError() != hipSuccess ||
+            hipMemcpyAsync(&hc, ctl, offsetof(TrainCtl, stats), hipMemcpyDeviceToHost, s) != hipSuccess ||
+            hipStreamSynchronize(s) != hipSuccess) {
+            rc = IDX_ERR_HIP;
+            break;
+        }
+        auto pick = [&](uint32_t mask, int c0) {  // the lower loss of a family's candidates
+            int best = -1;
+            for (int c = c0; c < c0 + 2; ++c)
+                if (((mask >> c) & 1u) && (best < 0 || hc.acc[c][5] < hc.acc[best][5])) best = c;
+            return best;
+        };
+        const int lin = pick(lin_mask, 0), spl = pick(sp_mask, kSpline0);
 
         // ---- stage 2: leaves under each family's root; with both, the lower
         // estimated lookup cost wins
-        double st[4], st2[4];
-        bool sp = !want_lin;
-        if ((rc = leaves_for(want_lin ? best_lin : best_sp, M->leaves, st)) != IDX_OK) break;
-        if (both) {
-            if ((rc = leaves_for(best_sp, alt, st2)) != IDX_OK) break;
-            if (window_cost(st2[0] / (double)n, true) < window_cost(st[0] / (double)n, false)) {
-                sp = true;
-                for (int j = 0; j < 4; ++j) st[j] = st2[j];
-                if (hipMemcpyAsync(M->leaves, alt, (size_t)L * sizeof(LeafRec), hipMemcpyDeviceToDevice, s) !=
-                        hipSuccess ||
-                    hipStreamSynchronize(s) != hipSuccess) {
-                    rc = IDX_ERR_HIP;
-                    break;
-                }
-            }
+        const int first = want_lin ? lin : spl;
+        if ((rc = leaves_for(first, 0, M->leaves)) != IDX_OK) break;
+        if (both && (rc = leaves_for(spl, 1, alt)) != IDX_OK) break;
+        if (hipMemcpyAsync(hc.stats, ctl->stats, sizeof(hc.stats), hipMemcpyDeviceToHost, s) != hipSuccess ||
+            hipStreamSynchronize(s) != hipSuccess) {
+            rc = IDX_ERR_HIP;
+            break;
         }
-        M->root = sp ? best_sp : best_lin;
-        M->stats.root_loss = sp ? loss_sp : loss_lin;
-        M->stats.leaf_loss = st[2];
-        M->stats.mean_window = n ? st[0] / (double)n : 0.0;
-        M->stats.max_window = st[1];
+        int won = first, fam = 0;
+        if (both && window_cost(hc.stats[1][0] / (double)n, true) < window_cost(hc.stats[0][0] / (double)n, false)) {
+            won = spl;
+            fam = 1;
+            std::swap(M->leaves, alt);
+        }
+        if (won == kSpline0 + 1) std::swap(M->spline, bins2);
+        M->root = hc.roots[won];
+        M->stats.root_loss = hc.acc[won][5];
+        M->stats.leaf_loss = hc.stats[fam][2];
+        M->stats.mean_window = n ? hc.stats[fam][0] / (double)n : 0.0;
+        M->stats.max_window = hc.stats[fam][1];
     } while (0);
-    h->alloc.put(tmp, s);
+    give_back();
     return rc;
 }
 
@@ -818,40 +1109,66 @@ __global__ __launch_bounds__(1024) void k_point_learned(Load<K, AOS> keys, uint6
 // ------------------------------------------------------------- leaf lines
 
 // The leaf lines (line layout at line_scan), one thread per 16-byte chunk,
-// so that a wave writes eight whole lines.  A workgroup writes kLinesGroups
-// groups of 32 leaves in turn; a group's leaves cover one contiguous rank
-// range, and when it is short enough its keys and row IDs are first copied
-// to LDS with consecutive loads.
-constexpr uint32_t kLinesBlock = 256;                         // threads: 32 leaves x 8 chunks
-constexpr uint32_t kLinesStage = 1024;                        // keys staged per group at most
-constexpr uint32_t kLinesGroups = 8;  // groups of 32 leaves per workgroup (fewer workgroups to dispatch)
+// so that a wave writes eight whole lines.  A workgroup writes 256 leaves,
+// which cover one contiguous rank range.  Its keys and row IDs are first
+// copied to LDS with consecutive loads, all of them when they fit, else those
+// of 128, 64 or 32 leaves at a time.  Bound by HBM: 2^24 lines over 2^26
+// 64-bit keys (2 GiB written, 1.3 GB read) in 620 us; 32 leaves at a time
+// through a chain of dependent loads and two barriers took 880.
+constexpr uint32_t kLinesBlock = 256;   // threads, and leaves per workgroup
+constexpr uint32_t kLinesStage = 1536;  // keys staged at most: eight workgroups per CU
 template <typename K, bool AOS>
 __global__ __launch_bounds__(kLinesBlock) void k_leaf_lines(Load<K, AOS> keys, const LeafRec *__restrict__ leaves,
                                                             uint32_t L, uint4 *__restrict__ lines) {
     __shared__ K s_key[kLinesStage];
-    __shared__ uint32_t s_row[kLinesStage];
-    constexpr uint32_t GL = kLinesBlock / kLineChunks;  // leaves per group
-    for (uint32_t gi = 0; gi < kLinesGroups; ++gi) {
-        const uint64_t l0 = ((uint64_t)blockIdx.x * kLinesGroups + gi) * GL;
-        if (l0 >= L) return;  // workgroup-uniform
-        const uint64_t l1 = l0 + GL < L ? l0 + GL : L;
-        const uint64_t kb = leaves[l0].base, ke = (uint64_t)leaves[l1 - 1].base + leaves[l1 - 1].size;
-        const bool staged = ke - kb <= kLinesStage;  // workgroup-uniform
+    __shared__ uint32_t s_row[kLinesStage], s_base[kLinesBlock + 1];
+    const uint32_t l0 = blockIdx.x * kLinesBlock, nl = L - l0 < kLinesBlock ? L - l0 : kLinesBlock;
+    if (threadIdx.x < nl) {
+        const uint2 bs = *(const uint2 *)&leaves[l0 + threadIdx.x].base;
+        s_base[threadIdx.x] = bs.x;
+        if (threadIdx.x == nl - 1) s_base[nl] = bs.x + bs.y;
+    }
+    __syncthreads();
+    uint32_t step = kLinesBlock;  // leaves staged together
+    for (uint64_t t = s_base[nl] - s_base[0]; t > kLinesStage && step > 32; t >>= 1) step >>= 1;
+    for (uint32_t a = 0; a < nl; a += step) {
+        const uint32_t b = a + step < nl ? a + step : nl;
+        const uint32_t kb = s_base[a], count = s_base[b] - kb;
+        const bool staged = count <= kLinesStage;  // workgroup-uniform
+        if (a) __syncthreads();  // the keys before are written out
         if (staged) {
-            for (uint64_t i = kb + threadIdx.x; i < ke; i += kLinesBlock) {
-                s_key[i - kb] = keys.key(i);
-                s_row[i - kb] = keys.row(i);
+            constexpr int U = 4;
+            for (uint32_t i0 = 0; i0 < count; i0 += U * kLinesBlock) {
+                K k[U];
+                uint32_t r[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const uint32_t i = i0 + u * kLinesBlock + threadIdx.x;
+                    if (i < count) {
+                        k[u] = keys.key((uint64_t)kb + i);
+                        r[u] = keys.row((uint64_t)kb + i);
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const uint32_t i = i0 + u * kLinesBlock + threadIdx.x;
+                    if (i < count) {
+                        s_key[i] = k[u];
+                        s_row[i] = r[u];
+                    }
+                }
             }
             __syncthreads();
         }
-        const uint64_t t = l0 * kLineChunks + threadIdx.x;
-        if (t < (uint64_t)L * kLineChunks) {
-            const uint32_t l = (uint32_t)(t / kLineChunks), c = (uint32_t)(t % kLineChunks);
-            const LeafRec r = leaves[l];
-            auto key_at = [&](uint64_t i) -> uint64_t {
-                return staged ? (uint64_t)s_key[i - kb] : (uint64_t)keys.key(i);
+        for (uint32_t t = a * kLineChunks + threadIdx.x; t < b * kLineChunks; t += kLinesBlock) {
+            const uint32_t l = t / kLineChunks, c = t % kLineChunks;
+            const uint32_t base = s_base[l], size = s_base[l + 1] - base;
+            auto key_at = [&](uint32_t j) -> uint64_t {
+                return staged ? (uint64_t)s_key[base + j - kb] : (uint64_t)keys.key((uint64_t)base + j);
             };
-            auto row_at = [&](uint64_t i) -> uint32_t { return staged ? s_row[i - kb] : keys.row(i); };
+            auto row_at = [&](uint32_t j) -> uint32_t {
+                return staged ? s_row[base + j - kb] : keys.row((uint64_t)base + j);
+            };
             constexpr uint32_t C = line_slots<K>();
             constexpr uint32_t KW = sizeof(K) / 4;  // words per key
             uint32_t v[4];
@@ -860,24 +1177,23 @@ __global__ __launch_bounds__(kLinesBlock) void k_leaf_lines(Load<K, AOS> keys, c
                 const uint32_t wi = 4 * c + i;
                 uint32_t x = 0;
                 if (wi == 0) {
-                    x = r.base;
+                    x = base;
                 } else if (wi == 1) {
-                    x = r.size;
+                    x = size;
                 } else if (wi < 2 + C * KW) {
                     const uint32_t j = (wi - 2) / KW;
-                    if (j < r.size) {
-                        const uint64_t k = key_at((uint64_t)r.base + j);
+                    if (j < size) {
+                        const uint64_t k = key_at(j);
                         x = (KW == 2 && ((wi - 2) & 1u)) ? (uint32_t)(k >> 32) : (uint32_t)k;
                     }
                 } else {
                     const uint32_t j = wi - 2 - C * KW;
-                    if (j < r.size) x = row_at((uint64_t)r.base + j);
+                    if (j < size) x = row_at(j);
                 }
                 v[i] = x;
             }
-            lines[t] = make_uint4(v[0], v[1], v[2], v[3]);
+            lines[(uint64_t)l0 * kLineChunks + t] = make_uint4(v[0], v[1], v[2], v[3]);
         }
-        __syncthreads();  // the next group restages
     }
 }
 
@@ -1078,8 +1394,7 @@ int ensure_lines(idx_index *h, hipStream_t s) {
     h->spare_lines = nullptr;
     h->spare_lines_bytes = 0;
     if (!lines) return IDX_ERR_NOMEM;
-    const uint64_t groups = ((uint64_t)L + kLinesBlock / kLineChunks - 1) / (kLinesBlock / kLineChunks);
-    const uint32_t g = (uint32_t)((groups + kLinesGroups - 1) / kLinesGroups);
+    const uint32_t g = grid_for(L, kLinesBlock);
     if (h->u64) {
         if (h->aos) hipLaunchKernelGGL((k_leaf_lines<uint64_t, true>), dim3(g), dim3(256), 0, s, make_load<uint64_t, true>(h), M->leaves, L, lines);
         else hipLaunchKernelGGL((k_leaf_lines<uint64_t, false>), dim3(g), dim3(256), 0, s, make_load<uint64_t, false>(h), M->leaves, L, lines);
@@ -1398,12 +1713,16 @@ int range_count_learned(idx_index *h, const void *lo, const void *hi, uint64_t m
 // ----------------------------------------------------- gradient evaluation
 
 namespace {
-// leaf parameters given as (b0, b1) pairs
-__global__ void k_set_leaf_params(LeafRec *leaves, const float *ab, uint32_t L) {
+// leaf records with parameters given as (b0, b1) pairs
+template <typename K, bool AOS>
+__global__ void k_set_leaf_params(Load<K, AOS> keys, const uint32_t *__restrict__ base, LeafRec *leaves,
+                                  const float *ab, uint32_t L) {
     const uint32_t l = blockIdx.x * blockDim.x + threadIdx.x;
     if (l >= L) return;
-    leaves[l].b0 = ab[2 * l];
-    leaves[l].b1 = ab[2 * l + 1];
+    LeafRec r = new_leaf(keys, base[l], base[l + 1]);
+    r.b0 = ab[2 * l];
+    r.b1 = ab[2 * l + 1];
+    leaves[l] = r;
 }
 
 template <typename K, bool AOS>
@@ -1411,35 +1730,31 @@ int eval_t(idx_index *h, uint32_t mode, const float *root_ab, uint32_t L, const 
            double *leaf_acc_d, hipStream_t s) {
     const uint64_t n = h->n;
     const Load<K, AOS> keys = make_load<K, AOS>(h);
-    auto up256 = [](size_t v) { return (v + 255) & ~(size_t)255; };
-    const size_t leaf_b = up256((size_t)L * sizeof(LeafRec));
-    char *tmp = (char *)h->alloc.get(512 + leaf_b + layout_scratch_bytes(L), s);
+    const size_t leaf_b = up256((size_t)L * sizeof(LeafRec)), ctl_b = up256(sizeof(TrainCtl));
+    char *tmp = (char *)h->alloc.get(ctl_b + leaf_b + bounds_bytes(L), s);
     if (!tmp) return IDX_ERR_NOMEM;
-    RootRec *d_root = (RootRec *)tmp;
-    double *racc = (double *)(tmp + 256);
-    LeafRec *leaves = (LeafRec *)(tmp + 512);
-    unsigned long long *count = (unsigned long long *)(tmp + 512 + leaf_b);
-    uint64_t *partial = (uint64_t *)((char *)count + up256(((size_t)L + 1) * 8));
+    TrainCtl *ctl = (TrainCtl *)tmp;
+    LeafRec *leaves = (LeafRec *)(tmp + ctl_b);
+    char *bounds = tmp + ctl_b + leaf_b;
+    double *racc = ctl->acc[0];
     int rc = IDX_OK;
     do {
-        RootRec R{root_ab[0], root_ab[1], mode, L};
-        if (hipMemcpyAsync(d_root, &R, sizeof(R), hipMemcpyHostToDevice, s) != hipSuccess) { rc = IDX_ERR_HIP; break; }
-        hipLaunchKernelGGL(k_fill_f64, dim3(1), dim3(64), 0, s, racc, (uint64_t)NACC);
-        const uint32_t rblocks = grid_for((n + LT * 8 - 1) / (LT * 8), 1) > 2048 ? 2048u
-                                                                                : grid_for((n + LT * 8 - 1) / (LT * 8), 1);
-        hipLaunchKernelGGL((k_root_accum<K, AOS>), dim3(rblocks), dim3(LT), 0, s, keys, n, d_root, racc);
+        TrainCtl hc{};
+        hc.roots[0] = RootRec{root_ab[0], root_ab[1], mode, L};
+        if (hipMemcpyAsync(ctl, &hc, sizeof(hc), hipMemcpyHostToDevice, s) != hipSuccess) { rc = IDX_ERR_HIP; break; }
+        hipLaunchKernelGGL((k_root_accum<K, AOS, kSumX | kSumGrad | kSumLoss, false>), dim3(root_blocks(n)), dim3(LT), 0,
+                           s, keys, n, ctl->roots, 1u, racc);
         if (leaf_ab && leaf_acc_d) {
             const uint32_t cblocks = grid_for((n + CHUNK - 1) / CHUNK, LT);
-            rc = leaf_layout<K, AOS>(keys, n, d_root, L, count, partial, leaves, s);
+            rc = leaf_bounds<K, AOS>(keys, n, ctl->roots, L, bounds, ctl->ngaps, s);
             if (rc != IDX_OK) break;
-            uint32_t *d_big = (uint32_t *)(tmp + 256 + 128);
-            hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, s, d_big, (uint64_t)1, 0u);
-            hipLaunchKernelGGL(k_set_leaf_params, dim3(grid_for(L, 256)), dim3(256), 0, s, leaves, leaf_ab, L);
+            hipLaunchKernelGGL((k_set_leaf_params<K, AOS>), dim3(grid_for(L, 256)), dim3(256), 0, s, keys,
+                               (const uint32_t *)bounds, leaves, leaf_ab, L);
             const uint32_t cap = stage_cap(n, L);
             hipLaunchKernelGGL((k_leaf_accum_small<K, AOS>), dim3(grid_for(L, kLeafBlock)), dim3(kLeafBlock),
-                               (size_t)cap * sizeof(K), s, keys, leaves, L, leaf_acc_d, d_big, cap);
-            hipLaunchKernelGGL((k_leaf_accum_big<K, AOS>), dim3(cblocks), dim3(LT), 0, s, keys, n, d_root, leaves,
-                               leaf_acc_d, d_big);
+                               (size_t)cap * sizeof(K), s, keys, leaves, L, leaf_acc_d, ctl->big, cap);
+            hipLaunchKernelGGL((k_leaf_accum_big<K, AOS>), dim3(cblocks), dim3(LT), 0, s, keys, n, ctl->roots, leaves,
+                               leaf_acc_d, ctl->big);
         }
         if (hipGetLastError() != hipSuccess) { rc = IDX_ERR_HIP; break; }
         if (hipMemcpyAsync(root_acc_h, racc, NACC * sizeof(double), hipMemcpyDeviceToHost, s) != hipSuccess ||
