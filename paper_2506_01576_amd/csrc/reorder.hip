@@ -53,16 +53,40 @@ constexpr uint64_t kBucketQueries = 1024;              // queries per bucket at 
 // lookups 21-68 us; at 2^20 they take 65-221 and 59-271 us.  Range calls: 114-
 // 236 and 71-128 us at 2^18, 143-405 and 164-402 us at 2^20.
 constexpr uint64_t kPartMin = 3ull << 18;
+// k-ary layouts: an unpartitioned lookup reads few lines, so the partition pays
+// later, and the later the larger its tables (a ninth of the keys): 64-bit keys,
+// k = 9, 2^20 and 2^22 lookups, unpartitioned against partitioned: n = 2^21 52
+// and 172 us against 64 and 116; n = 2^23 67 and 222 against 89 and 141; n = 2^26
+// 90 and 309 against 220 and 348 (2^24 lookups: 1183 against 725).
+inline uint64_t part_min(const idx_index *h) { return h->layout == IDX_EKS ? (3ull << 19) + h->n / 12 : kPartMin; }
 
 // How a call is partitioned.
 struct PartGeo {
     uint32_t NB;    // buckets (1: not worth a partition)
     uint32_t L;     // levels of a bucket's table in LDS
     uint32_t D;     // sorted array: a table entry for every 2^D keys, at least a run of them
-    uint32_t top;   // Eytzinger layouts: the splitters are the keys of the top `top` levels
+    uint32_t top;   // binary Eytzinger layout: the splitters are the keys of the top `top` levels
     uint64_t step;  // sorted array: ranks per bucket, 2^(L + D); bucket b's keys have their lower bounds in
                     //   [b * step, (b + 1) * step), or at n
+
+    // k-ary Eytzinger layout: buckets of up to `entries` neighbouring nodes of
+    // one level.  Cut the tree above level c: its top c levels are k^c - 1 keys
+    // in key order, and node j of level c holds the root of what lies between
+    // keys j - 1 and j.  The first `left` nodes of level cut_l make the first
+    // NB_l buckets, the nodes of level cut_r after them, [right, gaps), the
+    // others: where the partial level ends, so that every bucket spans about as
+    // many keys.
+    uint32_t entries, cut_l, cut_r, NB_l, left, right, gaps;
 };
+
+// Bucket b of the k-ary Eytzinger layout: nodes [j0, j1) of level `cut`.
+__host__ __device__ inline void bucket_nodes(const PartGeo &P, uint32_t b, uint32_t &cut, uint32_t &j0, uint32_t &j1) {
+    const bool l = b < P.NB_l;
+    const uint32_t end = l ? P.left : P.gaps;
+    cut = l ? P.cut_l : P.cut_r;
+    j0 = l ? b * P.entries : P.right + (b - P.NB_l) * P.entries;
+    j1 = end - j0 < P.entries ? end : j0 + P.entries;
+}
 
 // Splitters of the sorted array: the last key of every bucket's ranks.
 template <typename K, bool AOS>
@@ -72,24 +96,32 @@ __global__ void k_split_sorted(Load<K, AOS> L, uint64_t step, uint32_t NB, K *__
     split[j] = (j + 1 < NB) ? L.key((uint64_t)(j + 1) * step - 1) : key_max_v<K>();
 }
 
-// Splitters of an Eytzinger layout: the keys of its top levels in key order
-// (a full tree of NB - 1 keys), so that bucket b is the subtree of the b-th
-// node below them.  Key j of that tree: j + 1 = k^e u with u not a multiple
-// of k puts it on level top - 1 - e, at position (u - 1) - (u - 1) / k.
-template <typename K, bool AOS>
-__global__ void k_split_eyt(Load<K, AOS> L, Geo G, uint64_t off, uint32_t top, uint32_t NB, K *__restrict__ split) {
-    const uint32_t j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= NB) return;
-    if (j + 1 == NB) {
-        split[j] = key_max_v<K>();
-        return;
-    }
+// Key j, in key order, of a full tree of `levels` levels: its level and its
+// position on that level.  j + 1 = k^e u with u not a multiple of k puts it on
+// level levels - 1 - e, at (u - 1) - (u - 1) / k.
+__device__ __forceinline__ uint64_t key_slot(const Geo &G, uint32_t j, uint32_t levels) {
     uint32_t u = j + 1, e = 0;
     while (u % G.k == 0) {
         u /= G.k;
         ++e;
     }
-    split[j] = L.key(off + G.start[top - 1 - e] + (u - 1) - (u - 1) / G.k);
+    return G.start[levels - 1 - e] + (u - 1) - (u - 1) / G.k;
+}
+
+// Splitters of an Eytzinger layout.  Binary: the keys of its top levels in key
+// order (a full tree of NB - 1 keys), so that bucket b is the subtree of the
+// b-th node below them.  k-ary: the key after each bucket's last node.
+template <typename K, bool AOS>
+__global__ void k_split_eyt(Load<K, AOS> L, Geo G, uint64_t off, PartGeo P, K *__restrict__ split) {
+    const uint32_t b = blockIdx.x * blockDim.x + threadIdx.x;
+    if (b >= P.NB) return;
+    if (b + 1 == P.NB) {
+        split[b] = key_max_v<K>();
+        return;
+    }
+    uint32_t cut = P.top, j0, j1 = b + 1;
+    if (P.entries) bucket_nodes(P, b, cut, j0, j1);
+    split[b] = L.key(off + key_slot(G, j1 - 1, cut));
 }
 
 // Bucket table: the key range from the first splitter to the second-largest
@@ -465,6 +497,26 @@ __global__ __launch_bounds__(256) void k_part_tables(Load<K, AOS> A, uint64_t n,
     tab[t] = at < n ? A.key(at) : key_max_v<K>();
 }
 
+// Tables of the k-ary Eytzinger layout: entry i in key order is the key after
+// the bucket's i-th node, in the same heap order; rows has their row IDs.  With
+// c entries below x, the descent goes on at node c, and entry c is the only one
+// that can equal x.
+template <typename K>
+__global__ __launch_bounds__(256) void k_part_tables_eks(Load<K, false> A, Geo G, PartGeo P, K *__restrict__ tab,
+                                                         uint32_t *__restrict__ rows) {
+    const uint64_t t = (uint64_t)blockIdx.x * 256 + threadIdx.x;
+    const uint32_t b = (uint32_t)(t >> P.L), v = (uint32_t)(t & ((1u << P.L) - 1u));
+    if (b >= P.NB || v == 0) return;
+    const uint32_t lv = 31u - (uint32_t)__clz((int)v);
+    const uint32_t i = ((2u * (v - (1u << lv)) + 1) << (P.L - 1 - lv)) - 1;
+    uint32_t cut, j0, j1;
+    bucket_nodes(P, b, cut, j0, j1);
+    const bool real = i < j1 - j0 && j0 + i < G.start[cut];  // (no key follows the level's last node)
+    const uint64_t at = real ? key_slot(G, j0 + i, cut) : 0ull;
+    tab[t] = real ? A.key(at) : key_max_v<K>();
+    rows[t] = real ? A.row(at) : kMiss;
+}
+
 template <typename K>
 __device__ __forceinline__ void fill_table(const K *__restrict__ tab, uint32_t b, uint32_t L, K *s_tab) {
     const uint4 *src = (const uint4 *)(tab + ((uint64_t)b << L));
@@ -472,42 +524,50 @@ __device__ __forceinline__ void fill_table(const K *__restrict__ tab, uint32_t b
     for (uint32_t v = threadIdx.x; v < chunks; v += kLookThreads) ((uint4 *)s_tab)[v] = src[v];
 }
 
+// Table entries below each x.
+template <typename K, int R>
+__device__ __forceinline__ void table_count(const K *s_tab, uint32_t L, const K (&x)[R], uint32_t (&c)[R]) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) c[r] = 1;
+    for (uint32_t l = 0; l < L; ++l) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) c[r] = 2 * c[r] + (s_tab[c[r]] < x[r] ? 1u : 0u);
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) c[r] -= 1u << L;
+}
+
 // Start rank (relative to the bucket) of the 2^D ranks that hold each x.
 template <typename K, int R>
 __device__ __forceinline__ void table_find(const K *s_tab, const PartGeo &P, const K (&x)[R], uint32_t (&rel)[R]) {
+    table_count<K, R>(s_tab, P.L, x, rel);
 #pragma unroll
-    for (int r = 0; r < R; ++r) rel[r] = 1;
-    for (uint32_t l = 0; l < P.L; ++l) {
-#pragma unroll
-        for (int r = 0; r < R; ++r) rel[r] = 2 * rel[r] + (s_tab[rel[r]] < x[r] ? 1u : 0u);
-    }
-#pragma unroll
-    for (int r = 0; r < R; ++r) rel[r] = (rel[r] - (1u << P.L)) << P.D;
+    for (int r = 0; r < R; ++r) rel[r] <<= P.D;
 }
 
-// Value of lane k of each group of kRunLanes lanes.
-template <int k>
+// Value of lane k of each group of NL lanes.
+template <uint32_t NL, int k>
 __device__ __forceinline__ uint32_t run_lane(uint32_t v) {
-    return (uint32_t)__builtin_amdgcn_ds_swizzle((int)v, (0x20 - (int)kRunLanes) | (k << 5));
+    return (uint32_t)__builtin_amdgcn_ds_swizzle((int)v, (0x20 - (int)NL) | (k << 5));
 }
-template <int k>
+template <uint32_t NL, int k>
 __device__ __forceinline__ uint64_t run_lane(uint64_t v) {
-    return ((uint64_t)run_lane<k>((uint32_t)(v >> 32)) << 32) | run_lane<k>((uint32_t)v);
+    return ((uint64_t)run_lane<NL, k>((uint32_t)(v >> 32)) << 32) | run_lane<NL, k>((uint32_t)v);
 }
 
-// Lanes k and k + 1 of each group have their queries' runs (from rank `run` of
-// the bucket, a multiple of the run's keys) read by the group, 16 bytes a
-// lane: keys below x into below, and whether one equals x.  Ranks from `have`
-// on are past the array.
-template <typename K, int k>
+// Lanes k and k + 1 of each group of NL lanes have their queries' runs (from
+// rank `run` of the bucket, a multiple of the run's keys) read by the group, 16
+// bytes a lane: keys below x into below, and whether one equals x.  Ranks from
+// `have` on are past the array.
+template <typename K, uint32_t NL, int k>
 __device__ __forceinline__ void run_pair(const K *__restrict__ keys, uint32_t have, uint32_t run, K x,
                                          uint32_t &below, bool &equal) {
     constexpr int V = 16 / sizeof(K);
-    constexpr uint32_t MASK = (1u << kRunLanes) - 1u;
-    const uint32_t lane = threadIdx.x & (kWave - 1), sub = lane & (kRunLanes - 1), shift = lane & (32u - kRunLanes);
+    constexpr uint32_t MASK = (1u << NL) - 1u;
+    const uint32_t lane = threadIdx.x & (kWave - 1), sub = lane & (NL - 1), shift = lane & (32u - NL);
     const bool upper = lane >= 32;
-    const K xs[2] = {run_lane<k>(x), run_lane<k + 1>(x)};
-    uint32_t at[2] = {run_lane<k>(run), run_lane<k + 1>(run)};
+    const K xs[2] = {run_lane<NL, k>(x), run_lane<NL, k + 1>(x)};
+    uint32_t at[2] = {run_lane<NL, k>(run), run_lane<NL, k + 1>(run)};
     uint4 w[2];
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
@@ -530,9 +590,10 @@ __device__ __forceinline__ void run_pair(const K *__restrict__ keys, uint32_t ha
         bool e = false;
 #pragma unroll
         for (int v = 0; v < V; ++v) {
-            const uint64_t lt = __ballot(at[u] + v < have && kk[v] < xs[u]);
+            const bool in = at[u] + v < have;  // what lies past the keys is anything
+            const uint64_t lt = __ballot(in && kk[v] < xs[u]);
             c += (uint32_t)__popc((upper ? (uint32_t)(lt >> 32) : (uint32_t)lt) >> shift & MASK);
-            e |= kk[v] == xs[u];
+            e |= in && kk[v] == xs[u];
         }
         const uint64_t eq = __ballot(e);
         const bool hit = ((upper ? (uint32_t)(eq >> 32) : (uint32_t)eq) >> shift & MASK) != 0;
@@ -540,6 +601,18 @@ __device__ __forceinline__ void run_pair(const K *__restrict__ keys, uint32_t ha
             below = c;
             equal = hit;
         }
+    }
+}
+
+// The same for every lane of the group.
+template <typename K, uint32_t NL>
+__device__ __forceinline__ void run_all(const K *__restrict__ keys, uint32_t have, uint32_t run, K x, uint32_t &below,
+                                        bool &equal) {
+    run_pair<K, NL, 0>(keys, have, run, x, below, equal);
+    if constexpr (NL >= 4) run_pair<K, NL, 2>(keys, have, run, x, below, equal);
+    if constexpr (NL >= 8) {
+        run_pair<K, NL, 4>(keys, have, run, x, below, equal);
+        run_pair<K, NL, 6>(keys, have, run, x, below, equal);
     }
 }
 
@@ -572,14 +645,9 @@ __device__ __forceinline__ void settle(const Load<K, AOS> &A, uint64_t n, uint64
         for (int r = 0; r < R; ++r) {
             uint32_t below = 0;
             bool equal = false;
-            run_pair<K, 0>(keys, have, rel[r], x[r], below, equal);
-            run_pair<K, 2>(keys, have, rel[r], x[r], below, equal);
-            if constexpr (kRunLanes == 8) {
-                run_pair<K, 4>(keys, have, rel[r], x[r], below, equal);
-                run_pair<K, 6>(keys, have, rel[r], x[r], below, equal);
-            }
+            run_all<K, kRunLanes>(keys, have, rel[r], x[r], below, equal);
             rel[r] += below;
-            hit[r] = equal && rel[r] < have;
+            hit[r] = equal;
         }
     }
 }
@@ -720,6 +788,70 @@ __global__ __launch_bounds__(kLookThreads) void k_part_ebs(Load<K, AOS> A, uint6
     });
 }
 
+// k-ary Eytzinger layout of nodes of 16 * NL bytes: the bucket's table, then the
+// nodes below it (one, unless the tree is too large for that), each read by NL
+// lanes with one load.  Bound by L2 requests and vector work like k_part_bs.
+// Per 2^27 lookups at n = 2^26, k = 9, 64-bit keys: 1.53 ms (with whole subtrees
+// for buckets, the left ones larger than the L2 and two nodes below the table,
+// 2.48), 3.3 ms with the partition; a walk over all levels of the batch as it
+// comes takes 9.3.
+template <typename K, uint32_t NL>
+__global__ __launch_bounds__(kLookThreads, 8) void k_part_eks(Load<K, false> A, Geo G, const K *__restrict__ q,
+                                                              uint64_t m, const uint32_t *__restrict__ starts,
+                                                              PartGeo P, const K *__restrict__ tab,
+                                                              const uint32_t *__restrict__ rows, uint64_t spans,
+                                                              uint32_t *__restrict__ ans) {
+    extern __shared__ __align__(16) char smem[];
+    K *s_tab = (K *)smem;
+    constexpr int R = kLookPer;
+    constexpr uint32_t g = NL * 16 / sizeof(K);
+    for_pieces(m, starts, P.NB, spans, [&](uint32_t b, uint32_t p0, uint32_t p1) {
+        K x[R];  // a piece is at most one round of the workgroup's queries
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const uint32_t i = p0 + (uint32_t)r * kLookThreads + threadIdx.x;
+            x[r] = q[i < p1 ? i : p0];
+        }
+        fill_table(tab, b, P.L, s_tab);
+        __syncthreads();
+        uint32_t cut, j0, j1;
+        bucket_nodes(P, b, cut, j0, j1);
+        uint32_t c[R], res[R];  // node on the level, counted from the bucket's first; answer
+        table_count<K, R>(s_tab, P.L, x, c);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const uint32_t e = (uint32_t)__builtin_ctz(c[r] + 1), v = (1u << (P.L - 1 - e)) + (c[r] >> (e + 1));
+            const bool real = j0 + c[r] < G.start[cut];  // (c < j1 - j0: the splitter is not below x)
+            res[r] = kMiss;
+            if (real && s_tab[v] == x[r]) res[r] = rows[(b << P.L) + v];  // NB << L < 2^24
+        }
+        uint64_t first = (uint64_t)j0 * g, width = (uint64_t)(j1 - j0) * g;  // the bucket's keys on the level
+        for (uint32_t l = cut; l < G.levels; ++l, first *= G.k, width *= G.k) {
+            const uint64_t base = G.start[l] + first;
+            if (base >= G.n) break;  // workgroup-uniform
+            const uint32_t have = G.n - base < width ? (uint32_t)(G.n - base) : (uint32_t)width;
+            const K *keys = A.k + base;
+            const uint32_t *ids = A.r + base;
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const bool in = c[r] < (have + g - 1) / g;
+                const uint32_t at = in ? c[r] * g : 0u;
+                uint32_t below = 0;
+                bool equal = false;
+                run_all<K, NL>(keys, have, at, x[r], below, equal);
+                if (in && equal) res[r] = ids[at + below];
+                c[r] = in ? c[r] * G.k + below : ~0u;
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const uint32_t i = p0 + (uint32_t)r * kLookThreads + threadIdx.x;
+            if (i < p1) ans[i] = res[r];
+        }
+        __syncthreads();
+    });
+}
+
 // Both ranks of every range on the sorted array, as one packed word (first
 // rank << 32 | count) in partitioned order.  The range's lower bound names
 // the bucket; an upper bound past the bucket is searched in the rest of the
@@ -778,6 +910,45 @@ __global__ __launch_bounds__(kLookThreads, 8) void k_part_range_bs(Load<K, AOS> 
     });
 }
 
+// Buckets of the k-ary Eytzinger layout.  Cut just above the last level: the
+// nodes of the partial level, then those of the last full one past it, 2^13 - 1
+// to a bucket, leave one node to read below the table.  When that makes more
+// than kMaxBuckets, or few queries per bucket or table entry, the cut goes up,
+// level by level.
+void eks_geo(const Geo &G, uint64_t m, PartGeo &P) {
+    P.NB = 1;
+    if (G.m < 2) return;
+    uint64_t gaps[kMaxLevels];  // k^c, the nodes of full level c
+    gaps[0] = 1;
+    for (uint32_t c = 1; c < G.m; ++c) gaps[c] = gaps[c - 1] * G.k;
+    const uint64_t nodes = (G.b + G.g - 1) / G.g;  // of the partial level
+    auto plan = [&](uint32_t cr, bool two, uint32_t L) -> uint64_t {
+        const uint64_t E = (1ull << L) - 1, over = two ? (nodes + G.k - 1) / G.k : 0;
+        P.L = L;
+        P.entries = (uint32_t)E;
+        P.cut_l = cr + 1;
+        P.cut_r = cr;
+        P.gaps = (uint32_t)gaps[cr];
+        P.right = (uint32_t)over;
+        P.left = (uint32_t)(over * G.k);
+        P.NB_l = (uint32_t)((over * G.k + E - 1) / E);
+        return P.NB_l + (gaps[cr] - over + E - 1) / E;
+    };
+    uint32_t cr = G.m - 1;
+    bool two = nodes > 0;
+    uint64_t NB;
+    for (;;) {
+        const uint64_t all = gaps[cr] + (two ? nodes : 0);  // table entries in all
+        NB = all < (1ull << 32) ? plan(cr, two, kMaxLevels1) : ~0ull;
+        if (NB <= kMaxBuckets && NB * kBucketQueries <= m && all <= 8 * m) break;
+        if (two) two = false;
+        else if (cr > 1) --cr;
+        else return;
+    }
+    while (NB < 8 && P.L > kMinLevels) NB = plan(cr, two, P.L - 1);
+    P.NB = (uint32_t)NB;
+}
+
 // The buckets of a batch of m queries: at most kMaxBuckets, no fewer than
 // kBucketQueries queries each on average (they share the cost of the
 // bucket's table), and otherwise as small as a table of up to 13 levels over
@@ -801,6 +972,10 @@ PartGeo part_geo(const idx_index *h, uint64_t m) {
         }
         P.step = 1ull << (P.L + P.D);
         P.NB = (uint32_t)buckets();
+        return P;
+    }
+    if (h->layout == IDX_EKS) {
+        eks_geo(h->geo, m, P);
         return P;
     }
     const uint64_t bytes = h->n * ((h->u64 ? 8 : 4) + 4);
@@ -830,14 +1005,18 @@ struct PartBufs {
     uint32_t *total;    // NB
     uint32_t *starts;   // NB + 1
     void *split;        // NB keys
-    void *tab;          // the buckets' tables: NB << L keys (sorted array)
+    void *tab;          // the buckets' tables: NB << L keys
+    uint32_t *rows;     // their row IDs (k-ary Eytzinger layout)
 };
+
+// Row IDs of the tables' entries (k-ary Eytzinger layout).
+size_t row_entries(const PartGeo &P) { return P.entries ? (size_t)P.NB << P.L : 0; }
 
 size_t part_bytes(uint64_t m, size_t kb, const PartGeo &P, bool range) {
     const uint32_t NB = P.NB;
     return up256(m * kb) * (range ? 2 : 1) + up256(m * 4) + up256(m * (range ? 8 : 4)) +
            up256((size_t)NB * part_tiles(m) * 4) + up256((size_t)NB * 4) + up256(((size_t)NB + 1) * 4) +
-           up256((size_t)NB * kb) + up256(((size_t)NB << P.L) * kb);
+           up256((size_t)NB * kb) + up256(((size_t)NB << P.L) * kb) + up256(row_entries(P) * 4);
 }
 
 PartBufs carve(char *t, uint64_t m, size_t kb, const PartGeo &P, bool range) {
@@ -857,6 +1036,7 @@ PartBufs carve(char *t, uint64_t m, size_t kb, const PartGeo &P, bool range) {
     p.starts = (uint32_t *)take(((size_t)NB + 1) * 4);
     p.split = take((size_t)NB * kb);
     p.tab = take(((size_t)NB << P.L) * kb);
+    p.rows = (uint32_t *)take(row_entries(P) * 4);
     return p;
 }
 
@@ -871,7 +1051,7 @@ int partition_t(idx_index *h, const K *q, const K *q_hi, uint64_t m, const PartG
                            (K *)B.split);
     else
         hipLaunchKernelGGL((k_split_eyt<K, AOS>), dim3((NB + 255) / 256), dim3(256), 0, s, A, h->geo,
-                           (uint64_t)(h->layout == IDX_EBS ? 1 : 0), P.top, NB, (K *)B.split);
+                           (uint64_t)(h->layout == IDX_EBS ? 1 : 0), P, (K *)B.split);
     IDX_LAUNCH_CHECK();
     const uint32_t tiles = (uint32_t)part_tiles(m);
     const uint32_t iters = (tiles + kXcds - 1) / kXcds * kXcds;
@@ -914,6 +1094,7 @@ int chunk_t(idx_index *h, const K *q, uint64_t m, uint32_t *out, const PartGeo &
     const uint64_t spans = spans_of(m);
     const bool model = h->learned && h->params.model != 2;
     uint32_t *ans = (uint32_t *)B.ans;
+    const uint64_t node = h->geo.g * sizeof(K);
     if (h->layout == IDX_BS && !model) {
         rc = build_tables<K, AOS>(h, P, B, s);
         if (rc != IDX_OK) return rc;
@@ -923,6 +1104,21 @@ int chunk_t(idx_index *h, const K *q, uint64_t m, uint32_t *out, const PartGeo &
     } else if (h->layout == IDX_EBS) {
         hipLaunchKernelGGL((k_part_ebs<K, AOS>), span_grid(spans), dim3(kLookThreads), sizeof(K) << P.L, s,
                            make_load<K, AOS>(h), h->n, h->geo.m, (const K *)B.q2, m, B.starts, P, spans, ans);
+        IDX_LAUNCH_CHECK();
+    } else if (!AOS && h->layout == IDX_EKS && (node == 32 || node == 64 || node == 128)) {
+        const Load<K, false> A = make_load<K, false>(h);
+        hipLaunchKernelGGL(k_part_tables_eks<K>, dim3((uint32_t)((((uint64_t)P.NB << P.L) + 255) / 256)), dim3(256), 0,
+                           s, A, h->geo, P, (K *)B.tab, B.rows);
+        IDX_LAUNCH_CHECK();
+        auto look = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, span_grid(spans), dim3(kLookThreads), sizeof(K) << P.L, s, A, h->geo,
+                               (const K *)B.q2, m, B.starts, P, (const K *)B.tab, (const uint32_t *)B.rows, spans, ans);
+        };
+        switch (node) {
+            case 32: look(k_part_eks<K, 2>); break;
+            case 64: look(k_part_eks<K, 4>); break;
+            default: look(k_part_eks<K, 8>); break;
+        }
         IDX_LAUNCH_CHECK();
     } else {  // the handle's own lookup kernel over the partitioned batch
         rc = point_run(h, PointIO{B.q2, m, ans, false, true}, s);
@@ -960,7 +1156,13 @@ int range_chunk_t(idx_index *h, const K *lo, const K *hi, uint64_t m, const Part
 }  // namespace
 
 // ---- the partition for range counts
-bool range_partition_pays(const idx_index *h, uint64_t m) { return m >= kPartMin && part_geo(h, m).NB > 1; }
+// (On the k-ary layout the count over the partitioned batch gains less than the
+// partition costs: 2^24 ranges of 16 rows, n = 2^21, 2^23 and 2^26, 64-bit keys
+// 1.85, 2.04 and 2.64 ms unpartitioned and 1.92, 2.08 and 2.48 partitioned,
+// 32-bit keys 1.92, 1.95 and 2.37 against 2.14, 2.34 and 2.72.)
+bool range_partition_pays(const idx_index *h, uint64_t m) {
+    return h->layout != IDX_EKS && m >= kPartMin && part_geo(h, m).NB > 1;
+}
 
 size_t range_partition_bytes(const idx_index *h, uint64_t m) {
     return part_bytes(m, h->u64 ? 8 : 4, part_geo(h, m), true);
@@ -989,7 +1191,7 @@ int range_partition_back(const RangePart &v, uint64_t m, uint64_t *packed, hipSt
 int point_partitioned(idx_index *h, const void *q, uint64_t m, uint32_t *out, hipStream_t s) {
     const uint64_t chunk = m < kPartChunk ? m : kPartChunk;
     const PartGeo P = part_geo(h, chunk);
-    if (m < kPartMin || P.NB == 1) return point_run(h, PointIO{q, m, out, false, false}, s);
+    if (m < part_min(h) || P.NB == 1) return point_run(h, PointIO{q, m, out, false, false}, s);
     const size_t kb = h->u64 ? 8 : 4;
     char *tmp = (char *)h->alloc.get(part_bytes(chunk, kb, P, false), s);
     if (!tmp) return IDX_ERR_NOMEM;

@@ -17,6 +17,7 @@ if not torch.cuda.is_available():  # pragma: no cover
     pytest.skip("no GPU", allow_module_level=True)
 
 M = 3 << 18  # the smallest batch that is partitioned
+M_KARY = (3 << 19) + (1 << 18)  # and of the k-ary layouts for the sizes here
 
 
 def _set(n, bits, kind):
@@ -81,3 +82,20 @@ def test_partition_few_queries_per_bucket():
         with ix.relayout("ebs") as eb:
             eb.set_params(reorder=2)
             assert torch.equal(eb.point(to_dev(q)), to_dev(expect))
+
+
+@pytest.mark.parametrize("kind", ["unique", "copies"])
+@pytest.mark.parametrize("bits,k", [(64, 5), (64, 9), (64, 17), (32, 9), (32, 17), (32, 33), (64, 4)])
+@pytest.mark.parametrize("n", [300, 9 ** 4 - 1, 9 ** 5, 9 ** 5 - 9, 17 ** 4 + 5, 17 ** 4 - 2, (1 << 21) + 17])
+def test_partition_eks_tables(n, bits, k, kind):
+    """k-ary tables: nodes of 32, 64 and 128 bytes and one that is none of
+    these, trees of full levels only and with a partial one."""
+    keys, rows, sk, sr, rs, dt = _set(n, bits, kind)
+    q = _bounds(sk, rs, dt, M_KARY + 5)
+    at = np.minimum(np.searchsorted(sk, q), n - 1)
+    want = np.where(sk[at] == q, sr[at], np.uint32(0xFFFFFFFF))
+    with idx.Index(to_dev(keys), to_dev(rows), layout="eks", k=k) as ix:
+        ix.set_params(reorder=2)
+        got = ix.point(to_dev(q)).cpu().numpy().view(np.uint32)
+    bad = np.nonzero(got != want)[0]
+    assert len(bad) == 0, (len(bad), q[bad[0]], got[bad[0]], want[bad[0]])
