@@ -143,14 +143,14 @@ constexpr uint64_t kPartChunk = 1ull << 31;
 struct RangePart {
     const void *lo, *hi;  // bounds in partitioned order
     uint64_t *packed;
-    const uint32_t *place;
     bool counted;
 };
 bool range_partition_pays(const idx_index *h, uint64_t m);  // m: ranges of one chunk
 size_t range_partition_bytes(const idx_index *h, uint64_t m);
 int range_partition(idx_index *h, const void *lo, const void *hi, uint64_t m, void *scratch, RangePart *out,
                     hipStream_t s);
-int range_partition_back(const RangePart &v, uint64_t m, uint64_t *packed, hipStream_t s);
+int range_partition_back(const idx_index *h, const RangePart &v, void *scratch, uint64_t m, uint64_t *packed,
+                         hipStream_t s);
 
 // ---- range.hip --------------------------------------------------------------
 // Exclusive scan of v[0..m) in place, v[m] = total; partial holds

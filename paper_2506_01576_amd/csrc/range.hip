@@ -229,7 +229,7 @@ int range_count_partitioned(idx_index *h, const RangeArgs<K, AOS> &a, hipStream_
                 break;
             }
         }
-        rc = range_partition_back(v, mc, a.offsets + c0, s);
+        rc = range_partition_back(h, v, t, mc, a.offsets + c0, s);
     }
     h->alloc.put(t, s);
     return rc;

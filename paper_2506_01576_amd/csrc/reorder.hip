@@ -18,19 +18,17 @@
 //      query's cell), as a matrix;
 //   3. scan of the matrix along each bucket;
 //   4. scatter: each tile's queries, put in bucket order in LDS, leave in one
-//      piece per bucket; every query's place goes to `place`, in the caller's
-//      order;
+//      piece per bucket; every query's place within its tile goes to `place`,
+//      in the caller's order;
 //   5. lookup: spans of the partitioned batch, walked XCD by XCD so that the
 //      buckets one XCD has in flight fit its L2;
-//   6. gather: out[i] = answer[place[i]].
+//   6. gather: each tile reads its answers, a piece per bucket, back into LDS
+//      in bucket order, and its queries' places give them out in order.
 //
-// Step 6 is why one pass suffices in both directions: a tile's answers sit in
-// NB pieces of some tens of bytes to a few hundred, which one XCD's L2 holds
-// for the tiles it works on, so the gather reads every line once and writes
-// the output in order.  Writing the answers to their positions instead costs
-// a 32-byte memory write per 4-byte answer (L2 does not merge the writes of
-// different waves), with a second pass to narrow them 3.2 ms per 2^27
-// lookups against 0.54 ms here.
+// Step 6 is why one pass suffices in both directions.  Writing the answers to
+// their positions instead costs a 32-byte memory write per 4-byte answer (L2
+// does not merge the writes of different waves), with a second pass to narrow
+// them 3.2 ms per 2^27 lookups against 0.38 ms here.
 //
 // The partition is a pure function of the call: no state stays in the handle.
 #include <type_traits>
@@ -303,8 +301,8 @@ __global__ __launch_bounds__(kScanThreads) void k_part_scan(uint32_t *__restrict
 // tables; the next tile's queries are loaded while this one's leave.
 // RANGE: a second key per query (the ranges' upper bounds) moves along.
 // starts[b] (NB + 1 entries) receives the buckets' starts.
-// Bound by memory: 20 B per 64-bit query, 0.70 ms per 2^27 (two passes of 28
-// and 30 B took 2.57 ms).
+// Bound by memory: 18 B per 64-bit query, 0.67 ms per 2^27 (two passes of 28 and
+// 30 B took 2.57 ms).
 template <typename K>
 size_t scatter_lds_bytes(uint32_t NB) {
     return (size_t)NB * sizeof(K) + kCellBytes + (size_t)NB * 12 + (size_t)kPartTile * (sizeof(K) + 2) + 16;
@@ -317,7 +315,7 @@ __global__ __launch_bounds__(kPartThreads) void k_part_scatter(const K *__restri
                                                                const uint32_t *__restrict__ hist,
                                                                const uint32_t *__restrict__ total,
                                                                K *__restrict__ q2, K *__restrict__ q2_hi,
-                                                               uint32_t *__restrict__ place,
+                                                               uint16_t *__restrict__ place,
                                                                uint32_t *__restrict__ starts) {
     extern __shared__ __align__(16) char smem[];
     K *s_q = (K *)smem;
@@ -381,7 +379,7 @@ __global__ __launch_bounds__(kPartThreads) void k_part_scatter(const K *__restri
                 const uint32_t b = at[u] >> 16, pos = s_start[b] + (at[u] & 0xFFFFu);
                 s_q[pos] = x[u];
                 s_run[pos] = (uint16_t)b;
-                place[t0 + j] = s_off[b] + pos;
+                place[t0 + j] = (uint16_t)pos;
                 at[u] = pos;
             }
             if constexpr (RANGE) {
@@ -421,28 +419,114 @@ __global__ __launch_bounds__(kPartThreads) void k_part_scatter(const K *__restri
     }
 }
 
-// 6. out[i] = ans[place[i]], tiles walked XCD by XCD like the scatter's, so
-// the pieces that a stretch of tiles reads stay in one L2.
+// 6. A tile's answers sit in one piece per bucket: they are read piece by piece,
+// consecutive threads on consecutive answers, into LDS in bucket order, and
+// out[i] = the tile's answer place[i].  Tiles are walked XCD by XCD like the
+// scatter's, so that the lines two tiles' pieces share are read once.  Bound by
+// memory: 0.38 ms per 2^27 answers of 4 bytes from 512 buckets, 0.61 from 910
+// (a read per answer at its 32-bit place in the whole batch, as many L2
+// requests, took 0.55 and 0.61).
 template <typename T>
-__global__ __launch_bounds__(256) void k_part_gather(const T *__restrict__ ans, const uint32_t *__restrict__ place,
-                                                     uint64_t m, uint64_t tiles, T *__restrict__ out) {
-    constexpr int U = 8;
-    const uint64_t tile = tile_of(blockIdx.x, tiles, 1);
-    if (tile >= tiles) return;
-    const uint64_t t0 = tile * (256 * U);
-    uint32_t at[U];
+__global__ __launch_bounds__(kPartThreads) void k_part_gather(const T *__restrict__ ans,
+                                                              const uint16_t *__restrict__ place, uint64_t m,
+                                                              uint32_t NB, uint32_t tiles, uint32_t iters,
+                                                              const uint32_t *__restrict__ hist,
+                                                              const uint32_t *__restrict__ total,
+                                                              const uint32_t *__restrict__ starts,
+                                                              T *__restrict__ out) {
+    __shared__ T s_ans[kPartTile];
+    __shared__ uint16_t s_run[kPartTile];  // bucket of every place
+    __shared__ uint32_t s_off[kMaxBuckets];  // place in ans minus place in the tile
+    __shared__ uint32_t s_wave[kPartThreads / kWave];
+    const uint32_t tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+    const uint32_t mine = tid < NB ? starts[tid] : 0u, in_all = tid < NB ? total[tid] : 0u;
+    uint32_t first = 0, count = 0;  // the tile's answers in bucket tid
+    uint16_t at[kPartPer];
+    auto load = [&](uint32_t tile) {
+        if (tid < NB) {
+            const uint32_t *row = hist + (uint64_t)tid * tiles + tile;
+            first = row[0];
+            count = (tile + 1 < tiles ? row[1] : in_all) - first;
+        }
+        const uint64_t t0 = (uint64_t)tile * kPartTile;
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-        const uint64_t i = t0 + (uint32_t)u * 256 + threadIdx.x;
-        at[u] = i < m ? place[i] : 0u;
-    }
-    T v[U];
+        for (int u = 0; u < kPartPer; ++u) {
+            const uint64_t i = t0 + (uint32_t)u * kPartThreads + tid;
+            at[u] = i < m ? __builtin_nontemporal_load(place + i) : (uint16_t)0;
+        }
+    };
+    static_assert(kPartPer == 8, "a thread's places are one 16-byte word of s_run");
+    uint32_t it = blockIdx.x;
+    uint32_t tile = it < iters ? (uint32_t)tile_of(it, tiles, 1) : tiles;
+    if (tile < tiles) load(tile);
+    while (it < iters) {
+        const uint32_t next = it + gridDim.x;
+        const uint32_t next_tile = next < iters ? (uint32_t)tile_of(next, tiles, 1) : tiles;
+        if (tile < tiles) {  // workgroup-uniform
+            const uint64_t t0 = (uint64_t)tile * kPartTile;
+            const uint32_t cnt = m - t0 < kPartTile ? (uint32_t)(m - t0) : kPartTile;
+            ((uint4 *)s_run)[tid] = make_uint4(0, 0, 0, 0);
+            uint32_t all;
+            const uint32_t start = part_scan(count, s_wave, &all);
+            if (count) {
+                s_run[start] = (uint16_t)tid;
+                s_off[tid] = mine + first - start;
+            }
+            __syncthreads();
+            // every place's bucket: the largest marked at or before it
+            uint32_t b[kPartPer], last = 0;
+            const uint4 w = ((const uint4 *)s_run)[tid];
+            const uint32_t ww[4] = {w.x, w.y, w.z, w.w};
 #pragma unroll
-    for (int u = 0; u < U; ++u) v[u] = ans[at[u]];
+            for (int j = 0; j < kPartPer; ++j) {
+                const uint32_t v = (ww[j / 2] >> (16 * (j & 1))) & 0xFFFFu;
+                last = v > last ? v : last;
+                b[j] = last;
+            }
+            uint32_t before = last;
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-        const uint64_t i = t0 + (uint32_t)u * 256 + threadIdx.x;
-        if (i < m) out[i] = v[u];
+            for (int off = 1; off < kWave; off <<= 1) {
+                const uint32_t o = (uint32_t)__shfl_up((int)before, off, kWave);
+                if (lane >= (uint32_t)off) before = o > before ? o : before;
+            }
+            if (lane == kWave - 1) s_wave[wave] = before;
+            before = (uint32_t)__shfl_up((int)before, 1, kWave);
+            if (lane == 0) before = 0;
+            __syncthreads();
+            for (uint32_t v = 0; v < wave; ++v) before = s_wave[v] > before ? s_wave[v] : before;
+            uint32_t packed[4];
+#pragma unroll
+            for (int j = 0; j < kPartPer; ++j) b[j] = b[j] > before ? b[j] : before;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) packed[j] = b[2 * j] | (b[2 * j + 1] << 16);
+            ((uint4 *)s_run)[tid] = make_uint4(packed[0], packed[1], packed[2], packed[3]);
+            __syncthreads();
+            T v[kPartPer];
+#pragma unroll
+            for (int u = 0; u < kPartPer; ++u) {
+                const uint32_t j = (uint32_t)u * kPartThreads + tid;
+                if (j < cnt) v[u] = ans[s_off[s_run[j]] + j];
+            }
+            uint16_t from[kPartPer];
+#pragma unroll
+            for (int u = 0; u < kPartPer; ++u) from[u] = at[u];
+            if (next_tile < tiles) load(next_tile);
+#pragma unroll
+            for (int u = 0; u < kPartPer; ++u) {
+                const uint32_t j = (uint32_t)u * kPartThreads + tid;
+                if (j < cnt) s_ans[j] = v[u];
+            }
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < kPartPer; ++u) {
+                const uint32_t j = (uint32_t)u * kPartThreads + tid;
+                if (j < cnt) __builtin_nontemporal_store(s_ans[from[u]], out + t0 + j);
+            }
+        } else if (next_tile < tiles) {
+            load(next_tile);
+        }
+        it = next;
+        tile = next_tile;
     }
 }
 
@@ -460,8 +544,9 @@ __global__ __launch_bounds__(256) void k_part_gather(const T *__restrict__ ans, 
 // lookups at n = 2^26: 11 probes and a short-window scan from the bucket's
 // rank interval 4.74 ms; 12 levels in LDS and 5 probes 3.92 ms (7 requests a
 // lookup); 13 levels in LDS, then the one line that holds the lower bound,
-// read by eight lanes with one load, 1.67 ms (2.2 requests; VALU work now
-// weighs as much).
+// read by eight lanes with one load, 1.55 ms (2.1 requests a lookup; half of the
+// waves' time is waiting: two workgroups a compute unit, 64 KiB of LDS each,
+// overlap the table's copy, the walk and the lines only so far).
 constexpr uint32_t kLookThreads = 1024;
 constexpr int kLookPer = 4;        // queries per lane at once
 constexpr uint32_t kSpan = kLookThreads * kLookPer;  // queries per workgroup: two workgroups per compute unit keep
@@ -472,7 +557,7 @@ constexpr uint32_t kMinLevels = 6;
 
 // The last step of a search reads a run of keys with kRunLanes lanes, 16 bytes
 // each, one request: a whole line.  (Half a line halves the lanes' work, 1.53
-// against 1.67 ms per 2^27 lookups, but needs twice the buckets at n = 2^26,
+// against 1.67 ms per 2^27 lookups when tried, but needs twice the buckets at n = 2^26,
 // and the count, scatter and gather lose 0.26 ms to their shorter pieces.)
 constexpr uint32_t kRunLanes = 8;
 
@@ -555,65 +640,83 @@ __device__ __forceinline__ uint64_t run_lane(uint64_t v) {
     return ((uint64_t)run_lane<NL, k>((uint32_t)(v >> 32)) << 32) | run_lane<NL, k>((uint32_t)v);
 }
 
-// Lanes k and k + 1 of each group of NL lanes have their queries' runs (from
-// rank `run` of the bucket, a multiple of the run's keys) read by the group, 16
-// bytes a lane: keys below x into below, and whether one equals x.  Ranks from
-// `have` on are past the array.
-template <typename K, uint32_t NL, int k>
-__device__ __forceinline__ void run_pair(const K *__restrict__ keys, uint32_t have, uint32_t run, K x,
-                                         uint32_t &below, bool &equal) {
-    constexpr int V = 16 / sizeof(K);
-    constexpr uint32_t MASK = (1u << NL) - 1u;
-    const uint32_t lane = threadIdx.x & (kWave - 1), sub = lane & (NL - 1), shift = lane & (32u - NL);
-    const bool upper = lane >= 32;
-    const K xs[2] = {run_lane<NL, k>(x), run_lane<NL, k + 1>(x)};
-    uint32_t at[2] = {run_lane<NL, k>(run), run_lane<NL, k + 1>(run)};
-    uint4 w[2];
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-        at[u] += sub * V;
-        w[u] = *(const uint4 *)((const char *)keys + at[u] * (uint32_t)sizeof(K));
-    }
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-        K kk[V];
-        if constexpr (sizeof(K) == 8) {
-            kk[0] = ((uint64_t)w[u].y << 32) | w[u].x;
-            kk[1] = ((uint64_t)w[u].w << 32) | w[u].z;
-        } else {
-            kk[0] = w[u].x;
-            kk[1] = w[u].y;
-            kk[2] = w[u].z;
-            kk[3] = w[u].w;
-        }
-        uint32_t c = 0;
-        bool e = false;
-#pragma unroll
-        for (int v = 0; v < V; ++v) {
-            const bool in = at[u] + v < have;  // what lies past the keys is anything
-            const uint64_t lt = __ballot(in && kk[v] < xs[u]);
-            c += (uint32_t)__popc((upper ? (uint32_t)(lt >> 32) : (uint32_t)lt) >> shift & MASK);
-            e |= in && kk[v] == xs[u];
-        }
-        const uint64_t eq = __ballot(e);
-        const bool hit = ((upper ? (uint32_t)(eq >> 32) : (uint32_t)eq) >> shift & MASK) != 0;
-        if (sub == (uint32_t)(k + u)) {
-            below = c;
-            equal = hit;
-        }
-    }
+// Sum of v over each group of NL lanes, in all of them.
+template <uint32_t NL>
+__device__ __forceinline__ uint32_t run_sum(uint32_t v) {
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, true);  // lane ^ 1
+    if constexpr (NL >= 4) v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, true);   // lane ^ 2
+    if constexpr (NL >= 8) v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xF, 0xF, true);  // 7 - lane
+    return v;
 }
 
-// The same for every lane of the group.
-template <typename K, uint32_t NL>
+// Every lane's run (from rank `run` of the bucket, a multiple of the run's
+// keys) is read by its group of NL lanes, 16 bytes a lane: keys below x into
+// below, and whether one equals x.  FULL: no run ends past `have` ranks; what
+// lies there is anything.  The lanes' counts of a group's queries are summed
+// as bytes, four queries to a word (a run has at most 32 keys): 171 vector
+// instructions per 64 lookups of k_part_bs with 64-bit keys, where counting bits
+// of ballots took 277; 1.55 ms per 2^27 either way, 1.42 against 1.70 with 32-bit
+// keys.
+template <typename K, uint32_t NL, bool FULL>
 __device__ __forceinline__ void run_all(const K *__restrict__ keys, uint32_t have, uint32_t run, K x, uint32_t &below,
                                         bool &equal) {
-    run_pair<K, NL, 0>(keys, have, run, x, below, equal);
-    if constexpr (NL >= 4) run_pair<K, NL, 2>(keys, have, run, x, below, equal);
-    if constexpr (NL >= 8) {
-        run_pair<K, NL, 4>(keys, have, run, x, below, equal);
-        run_pair<K, NL, 6>(keys, have, run, x, below, equal);
+    constexpr int V = 16 / sizeof(K), W = (NL + 3) / 4, U = NL < 4 || sizeof(K) == 8 ? 2 : 4;
+    const uint32_t sub = threadIdx.x & (NL - 1);
+    uint32_t lt[W] = {}, eq[W] = {};
+    auto some = [&]<int k0>(std::integral_constant<int, k0>) {  // U queries from k0 on, loaded together
+        uint32_t at[U];
+        uint4 w[U];
+        at[0] = run_lane<NL, k0>(run) + sub * V;
+        at[1] = run_lane<NL, k0 + 1>(run) + sub * V;
+        if constexpr (U == 4) {
+            at[2] = run_lane<NL, k0 + 2>(run) + sub * V;
+            at[3] = run_lane<NL, k0 + 3>(run) + sub * V;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) w[u] = *(const uint4 *)((const char *)keys + at[u] * (uint32_t)sizeof(K));
+        K xs[U];
+        xs[0] = run_lane<NL, k0>(x);
+        xs[1] = run_lane<NL, k0 + 1>(x);
+        if constexpr (U == 4) {
+            xs[2] = run_lane<NL, k0 + 2>(x);
+            xs[3] = run_lane<NL, k0 + 3>(x);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            K kk[V];
+            if constexpr (sizeof(K) == 8) {
+                kk[0] = ((uint64_t)w[u].y << 32) | w[u].x;
+                kk[1] = ((uint64_t)w[u].w << 32) | w[u].z;
+            } else {
+                kk[0] = w[u].x;
+                kk[1] = w[u].y;
+                kk[2] = w[u].z;
+                kk[3] = w[u].w;
+            }
+            uint32_t c = 0;
+            bool e = false;
+#pragma unroll
+            for (int v = 0; v < V; ++v) {
+                const bool in = FULL || at[u] + v < have;
+                c += in && kk[v] < xs[u] ? 1u : 0u;
+                e |= in && kk[v] == xs[u];
+            }
+            lt[k0 / 4] += c << (8 * (k0 % 4 + u));
+            eq[k0 / 4] += e ? 1u << (8 * (k0 % 4 + u)) : 0u;
+        }
+    };
+    some(std::integral_constant<int, 0>{});
+    if constexpr (U == 2 && NL >= 4) some(std::integral_constant<int, 2>{});
+    if constexpr (NL == 8) some(std::integral_constant<int, 4>{});
+    if constexpr (U == 2 && NL == 8) some(std::integral_constant<int, 6>{});
+#pragma unroll
+    for (int j = 0; j < W; ++j) {
+        lt[j] = run_sum<NL>(lt[j]);
+        eq[j] = run_sum<NL>(eq[j]);
     }
+    const uint32_t l = W == 2 && sub >= 4 ? lt[W - 1] : lt[0], q = W == 2 && sub >= 4 ? eq[W - 1] : eq[0];
+    below = (l >> (8 * (sub & 3u))) & 0xFFu;
+    equal = ((q >> (8 * (sub & 3u))) & 0xFFu) != 0;
 }
 
 // Lower bounds of x[R] from rank `base` on: rel[r] comes as the start of the
@@ -641,14 +744,16 @@ __device__ __forceinline__ void settle(const Load<K, AOS> &A, uint64_t n, uint64
         }
     } else {
         const K *keys = A.k + base;
+        auto runs = [&](auto full) {
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-            uint32_t below = 0;
-            bool equal = false;
-            run_all<K, kRunLanes>(keys, have, rel[r], x[r], below, equal);
-            rel[r] += below;
-            hit[r] = equal;
-        }
+            for (int r = 0; r < R; ++r) {
+                uint32_t below;
+                run_all<K, kRunLanes, decltype(full)::value>(keys, have, rel[r], x[r], below, hit[r]);
+                rel[r] += below;
+            }
+        };
+        if (have >= P.step) runs(std::true_type{});  // workgroup-uniform
+        else runs(std::false_type{});
     }
 }
 
@@ -832,16 +937,20 @@ __global__ __launch_bounds__(kLookThreads, 8) void k_part_eks(Load<K, false> A, 
             const uint32_t have = G.n - base < width ? (uint32_t)(G.n - base) : (uint32_t)width;
             const K *keys = A.k + base;
             const uint32_t *ids = A.r + base;
+            auto nodes = [&](auto full) {
 #pragma unroll
-            for (int r = 0; r < R; ++r) {
-                const bool in = c[r] < (have + g - 1) / g;
-                const uint32_t at = in ? c[r] * g : 0u;
-                uint32_t below = 0;
-                bool equal = false;
-                run_all<K, NL>(keys, have, at, x[r], below, equal);
-                if (in && equal) res[r] = ids[at + below];
-                c[r] = in ? c[r] * G.k + below : ~0u;
-            }
+                for (int r = 0; r < R; ++r) {
+                    const bool in = c[r] < (have + g - 1) / g;
+                    const uint32_t at = in ? c[r] * g : 0u;
+                    uint32_t below;
+                    bool equal;
+                    run_all<K, NL, decltype(full)::value>(keys, have, at, x[r], below, equal);
+                    if (in && equal) res[r] = ids[at + below];
+                    c[r] = in ? c[r] * G.k + below : ~0u;
+                }
+            };
+            if (have == width) nodes(std::true_type{});  // workgroup-uniform
+            else nodes(std::false_type{});
         }
 #pragma unroll
         for (int r = 0; r < R; ++r) {
@@ -999,7 +1108,7 @@ uint64_t part_tiles(uint64_t m) { return (m + kPartTile - 1) / kPartTile; }
 // Scratch of one chunk of m queries (256-byte aligned regions).
 struct PartBufs {
     void *q2, *q2_hi;   // queries (and upper bounds) in partitioned order
-    uint32_t *place;    // place of every query in that order
+    uint16_t *place;    // place of every query within its tile, in bucket order
     void *ans;          // answers in partitioned order: u32, or u64 for ranges
     uint32_t *hist;     // NB x tiles
     uint32_t *total;    // NB
@@ -1014,7 +1123,7 @@ size_t row_entries(const PartGeo &P) { return P.entries ? (size_t)P.NB << P.L : 
 
 size_t part_bytes(uint64_t m, size_t kb, const PartGeo &P, bool range) {
     const uint32_t NB = P.NB;
-    return up256(m * kb) * (range ? 2 : 1) + up256(m * 4) + up256(m * (range ? 8 : 4)) +
+    return up256(m * kb) * (range ? 2 : 1) + up256(m * 2) + up256(m * (range ? 8 : 4)) +
            up256((size_t)NB * part_tiles(m) * 4) + up256((size_t)NB * 4) + up256(((size_t)NB + 1) * 4) +
            up256((size_t)NB * kb) + up256(((size_t)NB << P.L) * kb) + up256(row_entries(P) * 4);
 }
@@ -1029,7 +1138,7 @@ PartBufs carve(char *t, uint64_t m, size_t kb, const PartGeo &P, bool range) {
     };
     p.q2 = take(m * kb);
     p.q2_hi = range ? take(m * kb) : nullptr;
-    p.place = (uint32_t *)take(m * 4);
+    p.place = (uint16_t *)take(m * 2);
     p.ans = take(m * (range ? 8 : 4));
     p.hist = (uint32_t *)take((size_t)NB * part_tiles(m) * 4);
     p.total = (uint32_t *)take((size_t)NB * 4);
@@ -1084,6 +1193,18 @@ int build_tables(const idx_index *h, const PartGeo &P, const PartBufs &B, hipStr
     return IDX_OK;
 }
 
+// Step 6.
+template <typename T>
+int gather(const idx_index *h, const PartBufs &B, uint64_t m, uint32_t NB, const T *ans, T *out, hipStream_t s) {
+    const uint32_t tiles = (uint32_t)part_tiles(m), iters = (tiles + kXcds - 1) / kXcds * kXcds;
+    const uint32_t cus = (uint32_t)h->cu_count / kXcds * kXcds, two = 2 * (cus ? cus : kXcds);
+    hipLaunchKernelGGL(k_part_gather<T>, dim3(iters < two ? iters : two), dim3(kPartThreads), 0, s, ans,
+                       (const uint16_t *)B.place, m, NB, tiles, iters, (const uint32_t *)B.hist,
+                       (const uint32_t *)B.total, (const uint32_t *)B.starts, out);
+    IDX_LAUNCH_CHECK();
+    return IDX_OK;
+}
+
 uint64_t spans_of(uint64_t m) { return (m + kSpan - 1) / kSpan; }
 dim3 span_grid(uint64_t spans) { return dim3((uint32_t)((spans + kXcds - 1) / kXcds * kXcds)); }
 
@@ -1124,11 +1245,7 @@ int chunk_t(idx_index *h, const K *q, uint64_t m, uint32_t *out, const PartGeo &
         rc = point_run(h, PointIO{B.q2, m, ans, false, true}, s);
         if (rc != IDX_OK) return rc;
     }
-    const uint64_t gt = (m + 2047) / 2048;
-    hipLaunchKernelGGL(k_part_gather<uint32_t>, dim3((uint32_t)((gt + kXcds - 1) / kXcds * kXcds)), dim3(256), 0, s,
-                       (const uint32_t *)ans, (const uint32_t *)B.place, m, gt, out);
-    IDX_LAUNCH_CHECK();
-    return IDX_OK;
+    return gather(h, B, m, P.NB, (const uint32_t *)ans, out, s);
 }
 
 template <typename K, bool AOS>
@@ -1140,7 +1257,6 @@ int range_chunk_t(idx_index *h, const K *lo, const K *hi, uint64_t m, const Part
     out->lo = B.q2;
     out->hi = B.q2_hi;
     out->packed = (uint64_t *)B.ans;
-    out->place = B.place;
     out->counted = h->layout == IDX_BS;
     if (!out->counted) return IDX_OK;
     rc = build_tables<K, AOS>(h, P, B, s);
@@ -1180,12 +1296,11 @@ int range_partition(idx_index *h, const void *lo, const void *hi, uint64_t m, vo
                   : range_chunk_t<uint32_t, false>(h, (const uint32_t *)lo, (const uint32_t *)hi, m, P, t, out, s);
 }
 
-int range_partition_back(const RangePart &v, uint64_t m, uint64_t *packed, hipStream_t s) {
-    const uint64_t gt = (m + 2047) / 2048;
-    hipLaunchKernelGGL(k_part_gather<uint64_t>, dim3((uint32_t)((gt + kXcds - 1) / kXcds * kXcds)), dim3(256), 0, s,
-                       (const uint64_t *)v.packed, v.place, m, gt, packed);
-    IDX_LAUNCH_CHECK();
-    return IDX_OK;
+int range_partition_back(const idx_index *h, const RangePart &v, void *scratch, uint64_t m, uint64_t *packed,
+                         hipStream_t s) {
+    const PartGeo P = part_geo(h, m);
+    const PartBufs B = carve((char *)scratch, m, h->u64 ? 8 : 4, P, true);
+    return gather(h, B, m, P.NB, (const uint64_t *)v.packed, packed, s);
 }
 
 int point_partitioned(idx_index *h, const void *q, uint64_t m, uint32_t *out, hipStream_t s) {
