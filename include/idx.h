@@ -295,15 +295,18 @@ typedef struct idx_lookup_params {
     uint32_t group;      /* EKS lanes per lookup: 1 = EKS (single), else a power of
                             two >= k - 1 (EKS (group)); ignored for BS/EBS */
     uint32_t block;      /* threads per workgroup: 64, 128, 256, 512 or 1024 */
-    uint32_t per_lane;   /* lookups held per lane (group) at once: 1, 2, 4 or 8 */
+    uint32_t per_lane;   /* lookups held per lane (group) at once: 1, 2, 4 or 8.  One lane per lookup:
+                            batches of up to 2^22 lookups may hold fewer, those of up to 2^17 pin no
+                            levels and use smaller workgroups, so that they spread over the chip */
     uint32_t lds_levels; /* top tree levels served from LDS (cache pinning); 0 = none */
     uint32_t persistent; /* 0 = one workgroup per tile of lookups; c > 0 = persistent
                             grid of c workgroups per compute unit (limited concurrency) */
     uint32_t reorder;    /* 1 = sort each workgroup's point lookups locally before searching;
                             2 = partition the batch by rank bucket of the index first (point
                             lookups, and the count phase of range lookups by their lower bounds)
-                            and gather the answers back; batches of under 3 * 2^18 (EKS: 3 * 2^19
-                            + n / 12), and EKS range lookups, are looked up as they come.  Plain
+                            and gather the answers back; batches too small for their index (of
+                            under 3 * 2^18 in any case), and EKS range lookups, are looked up as
+                            they come.  Plain
                             BS and EBS lookups, and EKS ones on separate arrays with nodes of 32,
                             64 or 128 bytes, then search each bucket through a table in LDS and
                             use none of the launch parameters above;

@@ -896,7 +896,7 @@ __global__ __launch_bounds__(BT) void k_batch_mixed_fill(const Desc *__restrict_
                                 uint64_t slot = rank;
                                 if (EYT && s_mode[w][lo] == MAP_BINARY) slot = 1 + rank_slot_binary(*s_geo[w][lo], rank);
                                 else if (EYT && s_mode[w][lo] == MAP_KARY)
-                                    slot = rank_slot_general(*s_geo[w][lo], rank, s_kinv[w][lo]);
+                                    slot = rank_slot_general(*s_geo[w][lo], (uint32_t)rank, s_kinv[w][lo]);
                                 v[u] = s_rows[w][lo][slot];
                             }
                         }

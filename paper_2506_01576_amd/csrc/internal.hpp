@@ -183,7 +183,7 @@ int learn_stats(const idx_index *h, idx_learn_stats *out);
 int learn_export(const idx_index *h, void *leaves_out, hipStream_t s);
 int learn_eval(idx_index *h, uint32_t feature, const float *root_ab, uint32_t leaves, const float *leaf_ab,
                double *root_acc, double *leaf_acc, hipStream_t s);
-int point_learned(idx_index *h, const PointIO &io, hipStream_t s);
+int point_learned(idx_index *h, const idx_lookup_params &p, const PointIO &io, hipStream_t s);
 // The attached model's leaf lines, written unless they are there.
 int ensure_lines(idx_index *h, hipStream_t s);
 // first-match ranks and counts of ranges through the model
@@ -269,32 +269,30 @@ __host__ __device__ inline uint64_t rank_slot_binary(const Geo &G, uint64_t r) {
     return G.start[l] + ((v >> e) >> 1);
 }
 
-// floor(x / k) for x < 2^32 and 2 <= k < 2^32, given kinv = ceil(2^64 / k):
-// the high half of x * kinv (exact, since x * (kinv * k - 2^64) < 2^64).
-__host__ __device__ inline uint64_t div_small(uint64_t x, uint64_t kinv) {
-    return (uint64_t)(((unsigned __int128)x * kinv) >> 64);
+// floor(x / k) for 2 <= k < 2^32, given kinv = ceil(2^64 / k): the high half of
+// x * kinv (exact, since x * (kinv * k - 2^64) < 2^64), from two 32-bit products.
+__host__ __device__ inline uint32_t div_small(uint32_t x, uint64_t kinv) {
+    const uint64_t low = ((uint64_t)x * (uint32_t)kinv) >> 32;
+    return (uint32_t)(((uint64_t)x * (uint32_t)(kinv >> 32) + low) >> 32);
 }
 
 // The inverse of slot_rank for any k (n < 2^32).  Ranks come in groups of k
 // while bottom-level keys last: k - 1 bottom entries, then one upper-level
 // key.  An upper-level key has perfect-tree rank p (p = r / k in a group,
 // p = r - b after the groups); p + 1 = k^e * u with u not a multiple of k
-// puts it on level m - 1 - e at position (u - 1) - (u - 1) / k.
-__host__ __device__ inline uint64_t rank_slot_general(const Geo &G, uint64_t r, uint64_t kinv) {
-    const uint64_t q = div_small(r, kinv);
-    const uint64_t j = r - q * G.k;
-    if (j < G.g && q * G.g + j < G.b) return G.start[G.m] + q * G.g + j;
-    const uint64_t p = (j == G.g && G.g * (q + 1) <= G.b) ? q : r - G.b;
-    uint64_t v = p + 1;
-    uint32_t e = 0;
-    for (;;) {
-        const uint64_t w = div_small(v, kinv);
-        if (w * G.k != v) break;
+// puts it on level m - 1 - e at position (u - 1) - (u - 1) / k.  32-bit
+// arithmetic throughout, and a uniform level per step: a gather of 64 M row IDs
+// of a k = 17 layout by rank took @@ us, with 64-bit products @@.
+__host__ __device__ inline uint32_t rank_slot_general(const Geo &G, uint32_t r, uint64_t kinv) {
+    const uint32_t q = div_small(r, kinv), t = r - q, b = (uint32_t)G.b;  // t = q (k - 1) + r mod k
+    const bool upper = t - q * G.g == G.g;                                // the key after the group's node
+    if (!upper && t < b) return (uint32_t)G.start[G.m] + t;
+    uint32_t v = (upper && t <= b ? q : r - b) + 1;
+    for (uint32_t l = G.m - 1;; --l) {
+        const uint32_t w = div_small(v, kinv);
+        if (w * G.k != v) return (uint32_t)G.start[l] + v - 1 - w;  // w = (v - 1) / k too
         v = w;
-        ++e;
     }
-    const uint32_t l = G.m - 1 - e;
-    return G.start[l] + (v - 1) - div_small(v - 1, kinv);
 }
 
 }  // namespace idx

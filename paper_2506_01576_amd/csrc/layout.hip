@@ -75,7 +75,7 @@ __global__ __launch_bounds__(256) void k_permute_rank(const K *__restrict__ sk, 
     const uint32_t blk = x * per + (x < rem ? x : rem) + i;  // a bijection of [0, gridDim.x)
     const uint64_t r = (uint64_t)blk * blockDim.x + threadIdx.x;
     if (r >= G.n) return;
-    dst.put(rank_slot_general(G, r, kinv), sk[r], sr[r]);
+    dst.put(rank_slot_general(G, (uint32_t)r, kinv), sk[r], sr[r]);
 }
 
 template <typename K, bool AOS>

@@ -1413,7 +1413,7 @@ int ensure_lines(idx_index *h, hipStream_t s) {
 namespace {
 // Query IO of a leaf-line launch over tiles of `tile` lookups, and its grid.
 template <typename KT>
-QueryIO<KT> lines_io(const idx_index *h, const PointIO &pio, uint64_t tile, uint32_t &grid) {
+QueryIO<KT> lines_io(const idx_index *h, const idx_lookup_params &p, const PointIO &pio, uint64_t tile, uint32_t &grid) {
     QueryIO<KT> io{};
     io.q = (const KT *)pio.q;
     io.out = pio.out;
@@ -1421,11 +1421,11 @@ QueryIO<KT> lines_io(const idx_index *h, const PointIO &pio, uint64_t tile, uint
     io.local_sort = pio.local_sort ? 1u : 0u;
     io.xcd = pio.xcd ? 1u : 0u;
     io.sort_off = 0;
-    io.rounds = h->params.window_rounds == 1 ? 1u : 2u;
+    io.rounds = p.window_rounds == 1 ? 1u : 2u;
     set_tiles(io, tile);
     uint64_t g = io.iters;
-    if (h->params.persistent) {
-        uint64_t cap = (uint64_t)h->cu_count * h->params.persistent;
+    if (p.persistent) {
+        uint64_t cap = (uint64_t)h->cu_count * p.persistent;
         if (io.xcd && cap >= kXcds) cap -= cap % kXcds;
         if (g > cap) g = cap;
     }
@@ -1434,13 +1434,14 @@ QueryIO<KT> lines_io(const idx_index *h, const PointIO &pio, uint64_t tile, uint
 }
 
 template <typename KT, int RR>
-void launch_lines(idx_index *h, const PointIO &pio, uint32_t block, hipStream_t s) {
+void launch_lines(idx_index *h, const idx_lookup_params &p, const PointIO &pio, hipStream_t s) {
     const LearnedModel *M = h->learned;
+    const uint32_t block = p.block > 256 ? 256u : p.block;
     uint32_t g;
     if (pio.local_sort) {  // one lane per lookup, at most 4 lookups per lane
         constexpr int RS = RR > 4 ? 4 : RR;
         const uint64_t tile = (uint64_t)block * RS;
-        const QueryIO<KT> io = lines_io<KT>(h, pio, tile, g);
+        const QueryIO<KT> io = lines_io<KT>(h, p, pio, tile, g);
         const size_t smem = sort_lds_bytes((uint32_t)tile, sizeof(KT));
         if (h->aos && io.rounds == 2)
             hipLaunchKernelGGL((k_point_lines<KT, RS, true, true, true>), dim3(g), dim3(block), smem, s,
@@ -1456,7 +1457,7 @@ void launch_lines(idx_index *h, const PointIO &pio, uint32_t block, hipStream_t 
                                make_load<KT, false>(h), h->n, M->root, M->lines, io);
         return;
     }
-    const QueryIO<KT> io = lines_io<KT>(h, pio, (uint64_t)(block / 2) * RR, g);
+    const QueryIO<KT> io = lines_io<KT>(h, p, pio, (uint64_t)(block / 2) * RR, g);
     if (h->aos && io.rounds == 2)
         hipLaunchKernelGGL((k_point_lines_pair<KT, RR, true, true>), dim3(g), dim3(block), 0, s,
                            make_load<KT, true>(h), h->n, M->root, M->lines, io);
@@ -1472,22 +1473,21 @@ void launch_lines(idx_index *h, const PointIO &pio, uint32_t block, hipStream_t 
 }
 
 // Point lookups through the leaf lines: at most 256 threads per workgroup.
-int point_lines(idx_index *h, const PointIO &pio, hipStream_t s) {
-    const uint32_t block = h->params.block > 256 ? 256u : h->params.block;
-    const uint32_t R = h->params.per_lane;
+int point_lines(idx_index *h, const idx_lookup_params &p, const PointIO &pio, hipStream_t s) {
+    const uint32_t R = p.per_lane;
     if (h->u64) {
         switch (R) {
-            case 1: launch_lines<uint64_t, 1>(h, pio, block, s); break;
-            case 2: launch_lines<uint64_t, 2>(h, pio, block, s); break;
-            case 4: launch_lines<uint64_t, 4>(h, pio, block, s); break;
-            default: launch_lines<uint64_t, 8>(h, pio, block, s); break;
+            case 1: launch_lines<uint64_t, 1>(h, p, pio, s); break;
+            case 2: launch_lines<uint64_t, 2>(h, p, pio, s); break;
+            case 4: launch_lines<uint64_t, 4>(h, p, pio, s); break;
+            default: launch_lines<uint64_t, 8>(h, p, pio, s); break;
         }
     } else {
         switch (R) {
-            case 1: launch_lines<uint32_t, 1>(h, pio, block, s); break;
-            case 2: launch_lines<uint32_t, 2>(h, pio, block, s); break;
-            case 4: launch_lines<uint32_t, 4>(h, pio, block, s); break;
-            default: launch_lines<uint32_t, 8>(h, pio, block, s); break;
+            case 1: launch_lines<uint32_t, 1>(h, p, pio, s); break;
+            case 2: launch_lines<uint32_t, 2>(h, p, pio, s); break;
+            case 4: launch_lines<uint32_t, 4>(h, p, pio, s); break;
+            default: launch_lines<uint32_t, 8>(h, p, pio, s); break;
         }
     }
     IDX_LAUNCH_CHECK();
@@ -1496,14 +1496,14 @@ int point_lines(idx_index *h, const PointIO &pio, hipStream_t s) {
 
 }  // namespace
 
-int point_learned(idx_index *h, const PointIO &pio, hipStream_t s) {
-    if (h->params.leaf_lines == 1) {
+int point_learned(idx_index *h, const idx_lookup_params &p, const PointIO &pio, hipStream_t s) {
+    if (p.leaf_lines == 1) {
         const int rc = ensure_lines(h, s);
-        return rc != IDX_OK ? rc : point_lines(h, pio, s);
+        return rc != IDX_OK ? rc : point_lines(h, p, pio, s);
     }
     const LearnedModel *M = h->learned;
-    const uint32_t block = h->params.block;
-    const uint32_t R = h->params.per_lane;
+    const uint32_t block = p.block;
+    const uint32_t R = p.per_lane;
     const uint64_t tile = (uint64_t)block * R;
 #define IDX_LEARNED_KERNELS(KT, RR, TW)                                                                     \
     do {                                                                                                    \
@@ -1529,11 +1529,11 @@ int point_learned(idx_index *h, const PointIO &pio, hipStream_t s) {
         io.local_sort = pio.local_sort ? 1u : 0u;                                                           \
         io.xcd = pio.xcd ? 1u : 0u;                                                                         \
         io.sort_off = 0;                                                                                    \
-        io.rounds = h->params.window_rounds == 1 ? 1u : 2u;                                                 \
+        io.rounds = p.window_rounds == 1 ? 1u : 2u;                                                 \
         set_tiles(io, tile);                                                                                \
         uint64_t grid = io.iters;                                                                           \
-        if (h->params.persistent) {                                                                         \
-            uint64_t cap = (uint64_t)h->cu_count * h->params.persistent;                                    \
+        if (p.persistent) {                                                                         \
+            uint64_t cap = (uint64_t)h->cu_count * p.persistent;                                    \
             if (io.xcd && cap >= kXcds) cap -= cap % kXcds;                                                 \
             if (grid > cap) grid = cap;                                                                     \
         }                                                                                                   \

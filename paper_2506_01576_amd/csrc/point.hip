@@ -667,9 +667,44 @@ int resolve_params(const idx_index *h, const idx_lookup_params *in, idx_lookup_p
     return IDX_OK;
 }
 
+// A call is fitted to its batch: with the tuned shape of large batches, 1024
+// threads, 4 lookups a lane and a copy of the top levels per workgroup, 2^15
+// lookups run on 8 of 256 compute units, one after the other in each lane.
+//  - lookups per lane: one as long as that leaves lanes idle, and beyond for the
+//    forms that it suits longer (64-bit keys, us at 1 / 2 / 4 a lane: BS n = 2^20
+//    110 / 122 / 129 at 2^21 lookups; EKS n = 2^23 111 / 112 / 119 at 2^21 and
+//    equal at 2^22; EBS n = 2^23 31.7 / 31.6 / 32.2 at 2^18 and 61 / 61 / 55 at
+//    2^19, pinned n = 2^16 11.9 / 11.9 / 14.9 at 2^19; BS pinned n = 2^16 14.6 /
+//    13.2 / 18.3 at 2^19, 32-bit keys 18.4 / - / 17.8 at 2^20; learned n = 2^20
+//    18.1 / 18.7 / 19.8 at 2^19, 49 / 47 / 49 at 2^21, 91 / 83 / 85 at 2^22);
+//  - pinned levels: none up to 2^17 lookups, which do not pay for a copy per
+//    compute unit (EKS n = 2^23: 12.9 against 16.2 us at 2^17, 20.7 and 20.8 at
+//    2^18; BS n = 2^16: 8.0 and 7.6 at 2^17, 6.1 and 7.1 at 2^16);
+//  - threads: a wave per workgroup up to 2^14 lookups, so that they spread over
+//    the compute units (BS n = 2^26, 1024 lookups: 7.0 against 10.1 us).
+// In all, EKS n = 2^23: 36 -> 7 us at 2^15 lookups, 48 -> 21 at 2^18; EBS n =
+// 2^26, 32-bit keys: 34 -> 5.3 at 2^13.
+idx_lookup_params fit_params(const idx_index *h, const PointIO &io) {
+    idx_lookup_params p = h->params;
+    if (io.local_sort || p.group > 1) return p;  // tiles as asked for; groups fill the lanes
+    const uint64_t m = io.m;
+    uint32_t most = 8;  // lookups per lane
+    if (m <= 1u << 18) most = 1;
+    else if (h->learned && p.model != 2) most = m < 1u << 20 ? 1 : m < 1u << 22 ? 2 : 8;
+    else if (h->layout == IDX_EKS || (h->layout == IDX_BS && h->n > 1u << 17)) most = m < 1u << 22 ? 1 : 8;
+    else if (p.lds_levels) most = m < 1u << 19 ? 1 : m < 1u << 20 ? 2 : 8;
+    if (p.per_lane > most) p.per_lane = most;
+    if (m <= 1u << 17) {
+        p.lds_levels = 0;
+        if (p.block > 256) p.block = 256;
+    }
+    if (m <= 1u << 14) p.block = 64;
+    return p;
+}
+
 int point_run(idx_index *h, const PointIO &io, hipStream_t s) {
-    const idx_lookup_params &p = h->params;
-    if (h->learned && p.model != 2) return point_learned(h, io, s);
+    const idx_lookup_params p = fit_params(h, io);
+    if (h->learned && p.model != 2) return point_learned(h, p, io, s);
     if (p.lds_levels) {
         const int rc = build_pin(h, p.lds_levels, s);
         if (rc != IDX_OK) return rc;

@@ -243,7 +243,7 @@ template <int MAP, typename K, bool AOS>
 __device__ __forceinline__ uint64_t slot_of_rank(const RangeArgs<K, AOS> &a, uint64_t r) {
     if constexpr (MAP == MAP_SORTED) return r;
     else if constexpr (MAP == MAP_BINARY) return a.off + rank_slot_binary(a.G, r);
-    else return a.off + rank_slot_general(a.G, r, a.kinv);
+    else return a.off + rank_slot_general(a.G, (uint32_t)r, a.kinv);
 }
 
 // Each wave takes 64 consecutive queries, whose row-ID runs are consecutive
@@ -254,7 +254,7 @@ __device__ __forceinline__ uint64_t slot_of_rank(const RangeArgs<K, AOS> &a, uin
 template <typename K, bool AOS, int MAP>
 __global__ __launch_bounds__(256) void k_range_fill_rank(RangeArgs<K, AOS> a) {
     constexpr int WPB = 256 / kWave;
-    __shared__ uint64_t s_start[WPB][kWave + 1];
+    __shared__ uint64_t s_start[WPB][kWave];
     __shared__ uint64_t s_src[WPB][kWave];  // first rank of the run minus its start
     const uint32_t lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
     const uint64_t q0 = ((uint64_t)blockIdx.x * WPB + w) * kWave;
@@ -274,32 +274,34 @@ __global__ __launch_bounds__(256) void k_range_fill_rank(RangeArgs<K, AOS> a) {
     const uint64_t total = (uint64_t)__shfl((long long)incl, kWave - 1, kWave);
     if (total == 0) return;
     const uint64_t start = incl - len;
-    s_start[w][lane] = start;
-    if (lane == kWave - 1) s_start[w][kWave] = total;
-    s_src[w][lane] = r0 - start;
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     uint32_t *out = a.out + a.offsets[q0];
-    constexpr int CU = 4;
-    for (uint64_t t0 = lane; t0 < total; t0 += (uint64_t)kWave * CU) {
-        uint32_t v[CU];
+    auto copy = [&](auto *run_start, auto *run_src) {  // in 32 bits, unless the 64 ranges hold 2^32 entries
+        using T = std::remove_reference_t<decltype(*run_start)>;
+        run_start[lane] = (T)start;
+        run_src[lane] = (T)(r0 - start);
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        constexpr int CU = 4;
+        for (uint64_t t0 = lane; t0 < total; t0 += (uint64_t)kWave * CU) {
+            uint32_t v[CU];
 #pragma unroll
-        for (int u = 0; u < CU; ++u) {
-            const uint64_t t = t0 + (uint64_t)u * kWave;
-            if (t >= total) continue;
-            uint32_t lo = 0;
+            for (int u = 0; u < CU; ++u) {
+                const T t = (T)t0 + (T)(u * kWave);
+                if (t0 + u * kWave >= total) continue;
+                uint32_t lo = 0;
 #pragma unroll
-            for (uint32_t step = kWave / 2; step > 0; step >>= 1)
-                if (s_start[w][lo + step] <= t) lo += step;
-            v[u] = a.L.row(slot_of_rank<MAP>(a, s_src[w][lo] + t));
+                for (uint32_t step = kWave / 2; step > 0; step >>= 1)
+                    if (run_start[lo + step] <= t) lo += step;
+                v[u] = a.L.row(slot_of_rank<MAP>(a, (uint32_t)(run_src[lo] + t)));
+            }
+#pragma unroll
+            for (int u = 0; u < CU; ++u)
+                if (t0 + u * kWave < total) out[t0 + u * kWave] = v[u];
         }
-#pragma unroll
-        for (int u = 0; u < CU; ++u) {
-            const uint64_t t = t0 + (uint64_t)u * kWave;
-            if (t < total) out[t] = v[u];
-        }
-    }
+    };
+    if (total < 1ull << 32) copy((uint32_t *)s_start[w], (uint32_t *)s_src[w]);
+    else copy(s_start[w], s_src[w]);
 }
 
 // EBS/EKS: level scan along the lower-bound path of lo, one lane per range,

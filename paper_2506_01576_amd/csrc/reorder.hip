@@ -46,17 +46,41 @@ constexpr uint32_t kPartTile = kPartThreads * kPartPer;
 constexpr uint32_t kMaxBuckets = 1024;                 // one thread per bucket in the tile's scan
 constexpr uint64_t kBucketBytes = 3 * 512 * 1024;      // index bytes per bucket aimed at
 constexpr uint64_t kBucketQueries = 1024;              // queries per bucket at least, on average
-// Batches below this are looked up as they come: at n = 2^21..2^26 the
+// Batches below this are looked up as they come: on BS, n = 2^21..2^26, the
 // partition's launches take 62-170 us up to 2^18 queries, unpartitioned
 // lookups 21-68 us; at 2^20 they take 65-221 and 59-271 us.  Range calls: 114-
 // 236 and 71-128 us at 2^18, 143-405 and 164-402 us at 2^20.
 constexpr uint64_t kPartMin = 3ull << 18;
-// k-ary layouts: an unpartitioned lookup reads few lines, so the partition pays
-// later, and the later the larger its tables (a ninth of the keys): 64-bit keys,
-// k = 9, 2^20 and 2^22 lookups, unpartitioned against partitioned: n = 2^21 52
-// and 172 us against 64 and 116; n = 2^23 67 and 222 against 89 and 141; n = 2^26
-// 90 and 309 against 220 and 348 (2^24 lookups: 1183 against 725).
-inline uint64_t part_min(const idx_index *h) { return h->layout == IDX_EKS ? (3ull << 19) + h->n / 12 : kPartMin; }
+// On smaller sets and other layouts the partition pays later, against the
+// launches tuned for them.  us unpartitioned / partitioned, 64-bit keys:
+//   BS   n = 2^17: 95 / 88 at 2^22 lookups, 342 / 283 at 2^24 (32-bit keys 77 /
+//        86 and 276 / 250); 2^18: 55 / 63 at 2^21, 115 / 92 at 2^22; 2^20: 63 /
+//        62 at 2^20, 258 / 98 at 2^22
+//   EBS  n = 2^18: 119 / 139 at 2^22, 441 / 502 at 2^24; 2^20: 103 / 92 at 2^21,
+//        193 / 141 at 2^22
+//   EKS  k = 9, which reads few lines as it is; tables of a ninth of the keys:
+//        n = 2^18: 86 / 93 at 2^22, 325 / 301 at 2^24; 2^20: 69 / 76 at 2^21, 136
+//        / 103 at 2^22; 2^23: 67 / 89 at 2^20, 222 / 141 at 2^22; 2^26: 90 / 220
+//        at 2^20, 309 / 348 at 2^22, 1183 / 725 at 2^24
+inline uint64_t part_min(const idx_index *h) {
+    const uint64_t n = h->n;
+    const bool small = n < 3u << 18;
+    if (h->layout == IDX_EKS) return small ? 3ull << 21 : (1ull << 21) + n / 12;
+    if (h->layout == IDX_EBS) return small ? ~0ull : n < 1u << 21 ? 3ull << 20 : kPartMin;
+    return n < 1u << 18 ? 1ull << 23 : small ? 3ull << 20 : kPartMin;
+}
+
+// The same for range calls: BS n = 2^18 123 / 130 at 2^20 ranges, 372 / 285 at
+// 2^22; 2^20 164 / 142 and 539 / 309; EBS n = 2^18 407 / 482 at 2^22, 1554 / 1783
+// at 2^24; 2^20 174 / 193 at 2^20, 573 / 527 at 2^22.  k-ary layouts never: 2^24
+// ranges of 16 rows, n = 2^21, 2^23 and 2^26, 64-bit keys 1.85 / 1.92, 2.04 /
+// 2.08 and 2.64 / 2.48 ms, 32-bit keys 1.92 / 2.14, 1.95 / 2.34 and 2.37 / 2.72.
+inline uint64_t range_part_min(const idx_index *h) {
+    const bool small = h->n < 3u << 18;
+    if (h->layout == IDX_EKS) return ~0ull;
+    if (h->layout == IDX_EBS) return small ? ~0ull : h->n < 1u << 21 ? 3ull << 20 : kPartMin;
+    return small ? 3ull << 19 : kPartMin;
+}
 
 // How a call is partitioned.
 struct PartGeo {
@@ -1272,12 +1296,8 @@ int range_chunk_t(idx_index *h, const K *lo, const K *hi, uint64_t m, const Part
 }  // namespace
 
 // ---- the partition for range counts
-// (On the k-ary layout the count over the partitioned batch gains less than the
-// partition costs: 2^24 ranges of 16 rows, n = 2^21, 2^23 and 2^26, 64-bit keys
-// 1.85, 2.04 and 2.64 ms unpartitioned and 1.92, 2.08 and 2.48 partitioned,
-// 32-bit keys 1.92, 1.95 and 2.37 against 2.14, 2.34 and 2.72.)
 bool range_partition_pays(const idx_index *h, uint64_t m) {
-    return h->layout != IDX_EKS && m >= kPartMin && part_geo(h, m).NB > 1;
+    return m >= range_part_min(h) && part_geo(h, m).NB > 1;
 }
 
 size_t range_partition_bytes(const idx_index *h, uint64_t m) {
