@@ -251,7 +251,8 @@ typedef struct idx_info {
     uint32_t full_levels;     /* fully occupied levels m (Sections 4, 6.1) */
     uint64_t bottom_keys;     /* keys on the partial lowest level b */
     float build_ms_sort;      /* device time of the sort phase of the last build */
-    float build_ms_permute;   /* device time of the permutation phase (0 for BS) */
+    float build_ms_permute;   /* device time of the permutation phase (about 0 for BS, and where the sort's
+                                 last step writes the layout) */
 } idx_info;
 
 int idx_get_info(idx_handle h, idx_info *out);

@@ -240,11 +240,13 @@ int idx_build(const void *keys, const uint32_t *rowids, uint64_t n, int layout, 
         hipError_t e = hipMemsetAsync(dflags, 0, 2 * sizeof(uint32_t), s);
         if (e != hipSuccess) { rc = hip_fail(e); break; }
         (void)hipEventRecord(ev[0], s);
-        rc = sort_pairs(keys, rowids, n, h->u64, sk, sr, sort_tmp, dflags, s);
+        SortPlace place{};
+        const bool placing = n > 0 && sort_place(h, &place);
+        rc = sort_pairs(keys, rowids, n, h->u64, sk, sr, sort_tmp, placing ? &place : nullptr, dflags, s);
         if (rc != IDX_OK) break;
         (void)hipEventRecord(ev[1], s);
         if (!direct) {
-            rc = build_layout(h, sk, sr, s);
+            rc = place.done ? build_layout_rest(h, s) : build_layout(h, sk, sr, s);
             if (rc != IDX_OK) break;
         }
         (void)hipEventRecord(ev[2], s);

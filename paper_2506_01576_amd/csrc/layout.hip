@@ -173,6 +173,27 @@ int build_layout(idx_index *h, const void *sorted_keys, const uint32_t *sorted_r
                   : build_layout_t<uint32_t, false>(h, (const uint32_t *)sorted_keys, sorted_rows, s);
 }
 
+bool sort_place(const idx_index *h, SortPlace *place) {
+    if (h->layout == IDX_BS || h->aos) return false;
+    place->G = h->geo;
+    place->kinv = ~0ull / h->geo.k + 1;
+    place->keys = h->keys;
+    place->rows = h->rowids;
+    place->off = h->layout == IDX_EBS ? 1u : 0u;
+    place->done = false;
+    return true;
+}
+
+int build_layout_rest(idx_index *h, hipStream_t s) {
+    if (h->layout != IDX_EBS) return IDX_OK;
+    if (h->u64)
+        hipLaunchKernelGGL((k_empty_slot0<uint64_t, false>), dim3(1), dim3(64), 0, s, make_store<uint64_t, false>(h));
+    else
+        hipLaunchKernelGGL((k_empty_slot0<uint32_t, false>), dim3(1), dim3(64), 0, s, make_store<uint32_t, false>(h));
+    IDX_LAUNCH_CHECK();
+    return IDX_OK;
+}
+
 int check_sorted(const void *sorted_keys, const uint32_t *sorted_rows, uint64_t n, bool u64, uint32_t *flags,
                  hipStream_t s) {
     if (n == 0) return IDX_OK;

@@ -613,10 +613,13 @@ __device__ __forceinline__ void lds_radix_pass(K *s_key, uint16_t *s_idx, uint32
     __syncthreads();
 }
 
-// Writes a tile's pairs from LDS; flags as k_bucket_sort.
-template <typename K, int THREADS>
-__device__ __forceinline__ void tile_out(const K *s_key, const uint32_t *s_row, uint32_t cnt, K *ko, uint32_t *ro,
-                                         uint32_t *flags) {
+// Writes a tile's pairs (ranks from p0 on) from LDS; flags as k_bucket_sort.
+// PLACE: to their slots of a level-order layout, whose lowest level takes runs of
+// k - 1 consecutive ranks, so that the separate pass from the sorted arrays (285
+// us for 2^26 64-bit keys, k = 9) is saved for 60 us more here.
+template <typename K, int THREADS, bool PLACE>
+__device__ __forceinline__ void tile_out(const K *s_key, const uint32_t *s_row, uint32_t cnt, uint64_t p0, K *ko,
+                                         uint32_t *ro, const SortPlace &place, uint32_t *flags) {
     bool dup = false, miss = false;
 #pragma unroll
     for (int j = 0; j < BK_ITEMS; ++j) {
@@ -626,8 +629,12 @@ __device__ __forceinline__ void tile_out(const K *s_key, const uint32_t *s_row, 
         const uint32_t r = s_row[i];
         dup |= i > 0 && s_key[i - 1] == k;  // the previous tile's keys lie in other buckets
         miss |= r == kMiss;
-        ko[i] = k;
-        ro[i] = r;
+        uint64_t at = p0 + i;
+        if constexpr (PLACE)
+            at = place.G.k == 2 ? rank_slot_binary(place.G, at) + place.off
+                                : rank_slot_general(place.G, (uint32_t)at, place.kinv);
+        ko[at] = k;
+        ro[at] = r;
     }
     if (flags) {
         if (__any(dup) && (threadIdx.x & (kWave - 1)) == 0 && flags[0] == 0) atomicOr(&flags[0], 1u);
@@ -658,11 +665,11 @@ __device__ __forceinline__ void tile_out(const K *s_key, const uint32_t *s_row, 
 // LDS per 4096 64-bit pairs let three workgroups share a compute unit.
 // flags (when given): [0] |= 1 for two equal adjacent keys, [1] |= 1 for a
 // row ID equal to IDX_MISS.
-template <typename K, int THREADS, bool LOG>
+template <typename K, int THREADS, bool LOG, bool PLACE>
 __global__ __launch_bounds__(THREADS, THREADS == 512 ? 6 : 4) void k_bucket_sort(
     const K *keys_in, const uint32_t *rows_in, K *keys_out, uint32_t *rows_out, uint64_t n,
     const uint32_t *__restrict__ starts, const uint32_t *__restrict__ first, uint32_t tiles, uint32_t bits, uint32_t hb,
-    uint32_t *__restrict__ todo, uint32_t *flags) {
+    uint32_t *__restrict__ todo, SortPlace place, uint32_t *flags) {
     constexpr uint32_t CAP = THREADS * BK_ITEMS;
     constexpr uint32_t POS = 0x1FFF;  // positions, starts: 13 bits
     static_assert(BK_ITEMS == 8 && CAP <= POS + 1, "two 16-byte reads of bins per thread; 13-bit positions");
@@ -837,18 +844,19 @@ __global__ __launch_bounds__(THREADS, THREADS == 512 ? 6 : 4) void k_bucket_sort
         }
     }
     __syncthreads();
-    tile_out<K, THREADS>(s_key, s_row, cnt, keys_out + p0, rows_out + p0, flags);
+    tile_out<K, THREADS, PLACE>(s_key, s_row, cnt, p0, keys_out, rows_out, place, flags);
 }
 
 // The tiles that k_bucket_sort left (todo), by radix passes in LDS.
 // The row IDs are read by input position once the keys are in order, all of
 // them before any is written.
-template <typename K, int THREADS>
+template <typename K, int THREADS, bool PLACE>
 __global__ __launch_bounds__(THREADS) void k_bucket_radix(const K *keys_in, const uint32_t *rows_in, K *keys_out,
                                                           uint32_t *rows_out, uint64_t n,
                                                           const uint32_t *__restrict__ starts,
                                                           const uint32_t *__restrict__ first,
-                                                          const uint32_t *__restrict__ todo, uint32_t *flags) {
+                                                          const uint32_t *__restrict__ todo, SortPlace place,
+                                                          uint32_t *flags) {
     constexpr uint32_t CAP = THREADS * BK_ITEMS;
     extern __shared__ __align__(16) char smem[];
     K *s_key = (K *)smem;
@@ -892,7 +900,7 @@ __global__ __launch_bounds__(THREADS) void k_bucket_radix(const K *keys_in, cons
             if (i < cnt) s_row[i] = row[j];
         }
         __syncthreads();
-        tile_out<K, THREADS>(s_key, s_row, cnt, keys_out + p0, rows_out + p0, flags);
+        tile_out<K, THREADS, PLACE>(s_key, s_row, cnt, p0, keys_out, rows_out, place, flags);
         __syncthreads();  // before the next tile is staged
     }
 }
@@ -1001,23 +1009,38 @@ int sort_lsd(const TempLayout &tl, char *tb, const K *keys_in, const uint32_t *r
     return IDX_OK;
 }
 
-template <typename K, int THREADS, bool LOG>
+template <typename K, int THREADS, bool LOG, bool PLACE>
 int bucket_sort(const K *ki, const uint32_t *ri, K *ko, uint32_t *ro, uint64_t n, const uint32_t *starts,
-                const uint32_t *first, uint32_t tiles, uint32_t bits, uint32_t hb, uint32_t *todo, uint32_t *flags,
-                hipStream_t s) {
-    hipLaunchKernelGGL((k_bucket_sort<K, THREADS, LOG>), dim3(tiles), dim3(THREADS), bucket_lds_bytes<K>(THREADS), s,
-                       ki, ri, ko, ro, n, starts, first, tiles, bits, hb, todo, flags);
+                const uint32_t *first, uint32_t tiles, uint32_t bits, uint32_t hb, uint32_t *todo,
+                const SortPlace &place, uint32_t *flags, hipStream_t s) {
+    hipLaunchKernelGGL((k_bucket_sort<K, THREADS, LOG, PLACE>), dim3(tiles), dim3(THREADS),
+                       bucket_lds_bytes<K>(THREADS), s, ki, ri, ko, ro, n, starts, first, tiles, bits, hb, todo, place,
+                       flags);
     IDX_LAUNCH_CHECK();
-    hipLaunchKernelGGL((k_bucket_radix<K, THREADS>), dim3(tiles < 512 ? tiles : 512), dim3(THREADS),
-                       bucket_lds_bytes<K>(THREADS), s, ki, ri, ko, ro, n, starts, first, (const uint32_t *)todo, flags);
+    hipLaunchKernelGGL((k_bucket_radix<K, THREADS, PLACE>), dim3(tiles < 512 ? tiles : 512), dim3(THREADS),
+                       bucket_lds_bytes<K>(THREADS), s, ki, ri, ko, ro, n, starts, first, (const uint32_t *)todo,
+                       place, flags);
     IDX_LAUNCH_CHECK();
     return IDX_OK;
+}
+
+// The same to the sorted arrays ko, ro, or (place) to the layout's.
+template <typename K, int THREADS, bool LOG>
+int bucket_sort_to(const K *ki, const uint32_t *ri, K *ko, uint32_t *ro, uint64_t n, const uint32_t *starts,
+                   const uint32_t *first, uint32_t tiles, uint32_t bits, uint32_t hb, uint32_t *todo, SortPlace *place,
+                   uint32_t *flags, hipStream_t s) {
+    if (!place)
+        return bucket_sort<K, THREADS, LOG, false>(ki, ri, ko, ro, n, starts, first, tiles, bits, hb, todo, SortPlace{},
+                                                   flags, s);
+    place->done = true;
+    return bucket_sort<K, THREADS, LOG, true>(ki, ri, (K *)place->keys, place->rows, n, starts, first, tiles, bits, hb,
+                                              todo, *place, flags, s);
 }
 
 // The radix passes over the bucket bits [bits - hb, bits), then the buckets.
 template <typename K, bool LOG>
 int sort_buckets(const TempLayout &tl, char *tb, const K *keys_in, const uint32_t *rows_in, uint64_t n, K *keys_out,
-                 uint32_t *rows_out, const SortInfo &info, uint32_t hb, uint32_t *flags, hipStream_t s) {
+                 uint32_t *rows_out, const SortInfo &info, uint32_t hb, SortPlace *place, uint32_t *flags, hipStream_t s) {
     const uint32_t lo = hb > RS_BITS ? hb / 2 : 0, hi = hb - lo;  // bits of the passes (lo first, when there are two)
     const int base = (int)(info.bits - hb);
     K *tkeys = (K *)(tb + tl.keys_off);
@@ -1042,26 +1065,26 @@ int sort_buckets(const TempLayout &tl, char *tb, const K *keys_in, const uint32_
     const uint32_t tiles = (uint32_t)((n + tile - 1) / tile);
     hipLaunchKernelGGL(k_sort_tiles, dim3(tiles / 256 + 1), dim3(256), 0, s, starts, 1u << tl.want, tile, tiles, first, todo);
     IDX_LAUNCH_CHECK();
-    return small ? bucket_sort<K, BK_SMALL, LOG>(keys_out, rows_out, keys_out, rows_out, n, starts, first, tiles,
-                                                 info.bits, hb, todo, flags, s)
-                 : bucket_sort<K, BK_LARGE, LOG>(keys_out, rows_out, keys_out, rows_out, n, starts, first, tiles,
-                                                 info.bits, hb, todo, flags, s);
+    return small ? bucket_sort_to<K, BK_SMALL, LOG>(keys_out, rows_out, keys_out, rows_out, n, starts, first, tiles,
+                                                 info.bits, hb, todo, place, flags, s)
+                 : bucket_sort_to<K, BK_LARGE, LOG>(keys_out, rows_out, keys_out, rows_out, n, starts, first, tiles,
+                                                 info.bits, hb, todo, place, flags, s);
 }
 
 template <typename K>
 int sort_impl(const K *keys_in, const uint32_t *rows_in, uint64_t n, K *keys_out, uint32_t *rows_out, void *temp,
-              uint32_t *flags, hipStream_t s) {
+              SortPlace *place, uint32_t *flags, hipStream_t s) {
     if (n == 0) return IDX_OK;
     const TempLayout tl = temp_layout(n, sizeof(K) == 8);
     char *tb = (char *)temp;
     uint32_t *todo = (uint32_t *)(tb + tl.todo_off);
     // one workgroup takes it all: no histogram, nothing for the host to read
     if (n <= BK_SMALL * BK_ITEMS)
-        return bucket_sort<K, BK_SMALL, false>(keys_in, rows_in, keys_out, rows_out, n, nullptr, nullptr, 1, 0, 0,
-                                               todo, flags, s);
+        return bucket_sort_to<K, BK_SMALL, false>(keys_in, rows_in, keys_out, rows_out, n, nullptr, nullptr, 1, 0, 0,
+                                               todo, place, flags, s);
     if (n <= BK_LARGE * BK_ITEMS)
-        return bucket_sort<K, BK_LARGE, false>(keys_in, rows_in, keys_out, rows_out, n, nullptr, nullptr, 1, 0, 0,
-                                               todo, flags, s);
+        return bucket_sort_to<K, BK_LARGE, false>(keys_in, rows_in, keys_out, rows_out, n, nullptr, nullptr, 1, 0, 0,
+                                               todo, place, flags, s);
     SortInfo *dinfo = (SortInfo *)(tb + tl.info_off);
     uint32_t *partial = (uint32_t *)(tb + tl.keys_off);  // hist_grid * 2^want / 2 words <= n words; free until the passes
     uint32_t *block = (uint32_t *)(tb + tl.block_off);
@@ -1095,8 +1118,8 @@ int sort_impl(const K *keys_in, const uint32_t *rows_in, uint64_t n, K *keys_out
     const uint32_t hb = bucket_bits(tl.want, info.bits);
     const bool all_bits = hb == info.bits && !info.log;
     if (known && info.bits > 0 && (all_bits || (!info.bad && info.max_bucket <= 6144)))
-        return info.log ? sort_buckets<K, true>(tl, tb, keys_in, rows_in, n, keys_out, rows_out, info, hb, flags, s)
-                        : sort_buckets<K, false>(tl, tb, keys_in, rows_in, n, keys_out, rows_out, info, hb, flags, s);
+        return info.log ? sort_buckets<K, true>(tl, tb, keys_in, rows_in, n, keys_out, rows_out, info, hb, place, flags, s)
+                        : sort_buckets<K, false>(tl, tb, keys_in, rows_in, n, keys_out, rows_out, info, hb, place, flags, s);
     const int rc = sort_lsd<K>(tl, tb, keys_in, rows_in, n, keys_out, rows_out, s);
     if (rc != IDX_OK || !flags) return rc;
     return check_sorted(keys_out, rows_out, n, sizeof(K) == 8, flags, s);
@@ -1107,11 +1130,12 @@ int sort_impl(const K *keys_in, const uint32_t *rows_in, uint64_t n, K *keys_out
 size_t sort_temp_bytes(uint64_t n, bool u64) { return temp_layout(n, u64).bytes; }
 
 int sort_pairs(const void *keys_in, const uint32_t *rows_in, uint64_t n, bool u64, void *keys_out,
-               uint32_t *rows_out, void *temp, uint32_t *flags, hipStream_t s) {
+               uint32_t *rows_out, void *temp, SortPlace *place, uint32_t *flags, hipStream_t s) {
     if (u64)
-        return sort_impl<uint64_t>((const uint64_t *)keys_in, rows_in, n, (uint64_t *)keys_out, rows_out, temp, flags,
-                                   s);
-    return sort_impl<uint32_t>((const uint32_t *)keys_in, rows_in, n, (uint32_t *)keys_out, rows_out, temp, flags, s);
+        return sort_impl<uint64_t>((const uint64_t *)keys_in, rows_in, n, (uint64_t *)keys_out, rows_out, temp, place,
+                                   flags, s);
+    return sort_impl<uint32_t>((const uint32_t *)keys_in, rows_in, n, (uint32_t *)keys_out, rows_out, temp, place,
+                               flags, s);
 }
 
 }  // namespace idx

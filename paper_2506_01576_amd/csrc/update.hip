@@ -168,7 +168,7 @@ int idx_merge(idx_handle src, const void *keys, const uint32_t *rowids, uint64_t
     do {
         hipError_t e = hipMemsetAsync(dflags, 0, 2 * sizeof(uint32_t), s);
         if (e != hipSuccess) { rc = hip_fail(e); break; }
-        rc = sort_pairs(keys, rowids, m, h->u64, dk, dr, sort_tmp, nullptr, s);
+        rc = sort_pairs(keys, rowids, m, h->u64, dk, dr, sort_tmp, nullptr, nullptr, s);
         if (rc != IDX_OK) break;
         if (n > 0) {
             if (h->u64)

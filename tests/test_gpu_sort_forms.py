@@ -8,6 +8,7 @@ import pytest
 import torch
 
 import gen
+import oracle
 from gpu_util import to_dev
 
 pytestmark = pytest.mark.gpu
@@ -81,3 +82,26 @@ def test_sort_distributions(kind, n, bits):
 def test_sort_large(kind):
     # two passes of bucket bits; skewed: more than 2^16 keys of one bucket per counting workgroup
     _check(_keys(kind, (1 << 24) + (1 << 22) + 5, 64))
+
+
+@pytest.mark.parametrize("layout,k", [("ebs", 2), ("eks", 2), ("eks", 9), ("eks", 17)])
+@pytest.mark.parametrize("kind,n,bits", [("uniform", 1, 64), ("uniform", 4097, 32), ("uniform", 100003, 64),
+                                         ("uniform", 1 << 20, 32), ("clustered", 8000, 64), ("replicated", 70001, 32),
+                                         ("equal", 70001, 64), ("few", 70001, 32), ("skewed", 1 << 20, 64),
+                                         ("lognormal", 1 << 20, 64)])
+def test_sort_into_layouts(kind, n, bits, layout, k):
+    """The layouts that the sort's last step writes itself, whichever form it takes."""
+    keys = _keys(kind, n, bits)
+    rows = np.random.RandomState(n % 1000).permutation(n).astype(np.uint32)
+    order = np.argsort(keys, kind="stable")
+    wk, wr = oracle.eytzinger_layout(keys[order], rows[order], k, layout == "ebs")
+    with idx.Index(to_dev(keys), to_dev(rows), layout=layout, k=k) as ix:
+        gk, gr = ix.export()
+        assert ix.info()["unique"] == int(len(np.unique(keys)) == n)
+    gk, gr = gk.cpu().numpy().view(keys.dtype), gr.cpu().numpy().view(np.uint32)
+    first = 1 if layout == "ebs" else 0
+    assert len(gk) == n + first and len(gk) == len(wk)
+    assert np.array_equal(gk[first:], np.asarray(wk[first:]).astype(keys.dtype))
+    assert np.array_equal(gr[first:], np.asarray(wr[first:]).astype(np.uint32))
+    if first:
+        assert gk[0] == 0 and gr[0] == 0xFFFFFFFF
