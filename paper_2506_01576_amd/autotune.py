@@ -63,11 +63,11 @@ def candidates(key_bits: int, n: int):
                                                 "block": 1024}))
             out.append(("eks", k, "padded", {"group": 1, "per_lane": 4}))
     # lookup reordering (Section 7.4): the tile-local sort, and the batch
-    # partitioned by rank bucket, which pays once the index is far larger
-    # than one XCD's L2
+    # partitioned by rank bucket (the launch parameters beside it serve the
+    # batches too small for it)
     out.append(("bs", 1, False, {"reorder": 1, "per_lane": 4, "block": 1024}))
     out.append(("ebs", 2, False, {"reorder": 1, "per_lane": 8, "block": 512}))
-    if n >= 1 << 20:
+    if n >= 1 << 17:
         out.append(("bs", 1, False, {"reorder": 2, "per_lane": 4}))
         out.append(("bs", 1, False, {"reorder": 2, "per_lane": 8}))
         # partitioned and pinned: the top levels from LDS, the rest from L2
@@ -77,10 +77,8 @@ def candidates(key_bits: int, n: int):
                                       "block": 1024}))
         out.append(("ebs", 2, False, {"reorder": 2, "per_lane": 8}))
         out.append(("ebs", 2, False, {"reorder": 2, "per_lane": 4}))
-        out.append(("eks", 9, False, {"group": 1, "per_lane": 4, "reorder": 2}))
-        # the partition with each answer written straight to its position
-        out.append(("bs", 1, False, {"reorder": 3, "per_lane": 4}))
-        out.append(("ebs", 2, False, {"reorder": 3, "per_lane": 4}))
+        for k in (9, 17):
+            out.append(("eks", k, False, {"group": 1, "per_lane": 4, "reorder": 2}))
         out.append(("eks", 17, "padded", {"group": 1, "per_lane": 4, "reorder": 2}))
     return out
 
