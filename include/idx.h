@@ -307,10 +307,10 @@ typedef struct idx_lookup_params {
                             lookups, and the count phase of range lookups by their lower bounds)
                             and gather the answers back; batches too small for their index (of
                             under 3 * 2^18 in any case), and EKS range lookups, are looked up as
-                            they come.  BS and EBS lookups (with a model: on separate arrays),
-                            and EKS ones on separate arrays with nodes of 32, 64 or 128 bytes,
-                            then search each bucket through a table in LDS and use none of the
-                            launch parameters above, nor the model;
+                            they come.  Plain
+                            BS and EBS lookups, and EKS ones on separate arrays with nodes of 32,
+                            64 or 128 bytes, then search each bucket through a table in LDS and
+                            use none of the launch parameters above;
                             3 = the same as 2 */
     uint32_t early_exit; /* 1 = stop at an equal key (only used when keys are unique) */
     uint32_t model;      /* 0/1 = use the learned model when one is trained (idx_learn), 2 = ignore it */

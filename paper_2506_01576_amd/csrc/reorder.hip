@@ -62,13 +62,8 @@ constexpr uint64_t kPartMin = 3ull << 18;
 //        n = 2^18: 86 / 93 at 2^22, 325 / 301 at 2^24; 2^20: 69 / 76 at 2^21, 136
 //        / 103 at 2^22; 2^23: 67 / 89 at 2^20, 222 / 141 at 2^22; 2^26: 90 / 220
 //        at 2^20, 309 / 348 at 2^22, 1183 / 725 at 2^24
-//   BS with a rank model (leaf lines on separate arrays, whose tables then answer
-//        in its place): n = 2^20 1.19 / 1.18 ms at 2^26, n = 2^23 1.33 / 1.20 at 2^26
-//        and 2.65 / 2.32 at 2^27, n = 2^26 0.46 / 0.62 at 2^24 (its lines searched),
-//        1.83 / 1.67 at 2^26 and 3.64 / 2.97 at 2^27
 inline uint64_t part_min(const idx_index *h) {
     const uint64_t n = h->n;
-    if (h->learned && h->params.model != 2) return n < 1u << 20 ? ~0ull : 1ull << 26;
     const bool small = n < 3u << 18;
     if (h->layout == IDX_EKS) return small ? 3ull << 21 : (1ull << 21) + n / 12;
     if (h->layout == IDX_EBS) return small ? ~0ull : n < 1u << 21 ? 3ull << 20 : kPartMin;
@@ -1245,7 +1240,7 @@ int chunk_t(idx_index *h, const K *q, uint64_t m, uint32_t *out, const PartGeo &
     const bool model = h->learned && h->params.model != 2;
     uint32_t *ans = (uint32_t *)B.ans;
     const uint64_t node = h->geo.g * sizeof(K);
-    if (h->layout == IDX_BS && (!model || !AOS)) {
+    if (h->layout == IDX_BS && !model) {
         rc = build_tables<K, AOS>(h, P, B, s);
         if (rc != IDX_OK) return rc;
         hipLaunchKernelGGL((k_part_bs<K, AOS>), span_grid(spans), dim3(kLookThreads), sizeof(K) << P.L, s,

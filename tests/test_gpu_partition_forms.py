@@ -103,19 +103,3 @@ def test_partition_eks_tables(n, bits, k, kind):
         got = ix.point(to_dev(q)).cpu().numpy().view(np.uint32)
     bad = np.nonzero(got != want)[0]
     assert len(bad) == 0, (len(bad), q[bad[0]], got[bad[0]], want[bad[0]])
-
-
-def test_partition_with_a_model():
-    """The smallest batch that is partitioned on a set with a rank model: the
-    buckets' tables give what the model gives."""
-    n, m = (1 << 20) + 5, (1 << 26) + 3
-    keys, rows = gen.unique_keys(gen.BASE_SEED + 9, n, 64, 40)
-    g = torch.Generator(device="cuda").manual_seed(1)
-    dk, q = to_dev(keys), torch.randint(0, 1 << 40, (m,), generator=g, device="cuda")
-    q[::3] = dk[torch.randint(0, n, (len(q[::3]),), generator=g, device="cuda")]
-    with idx.Index(dk, to_dev(rows), layout="bs") as ix:
-        ix.learn(n // 4, 2)
-        want = ix.point(q)
-        ix.set_params(reorder=2)
-        assert torch.equal(ix.point(q), want)
-    assert int((want != -1).sum()) >= m // 3
