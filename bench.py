@@ -1111,6 +1111,12 @@ def main():
                     window=hrec.get("mean_window", 0.0), leaves=hrec["params"].get("leaves", 0),
                     aos=hrec["aos"] if hrec["layout"] == "learned" else False,
                     lines=hrec["params"].get("leaf_lines") == 1, over=hrec.get("line_overflow", 0.0))
+    if hrec["params"].get("reorder", 0) >= 2:
+        # partitioned batch: the lookups of a bucket share its entries, so what
+        # a call cannot do without is its queries, its answers and the index once
+        once = round(n * 12 / m, 1)
+        ab = {"stream": 12, "tree": once, "rowid": 0, "total": 12 + once, "random_lines": 0.0,
+              "path": "partitioned batch, bucket tables"}
     t_kernel = mean[f"point_{headline}"] / 1e3
     achieved = ab["total"] * m / t_kernel / 1e9
     hp = hrec["params"]

@@ -53,9 +53,10 @@ constexpr uint64_t kBucketQueries = 1024;              // queries per bucket at 
 constexpr uint64_t kPartMin = 3ull << 18;
 // On smaller sets and other layouts the partition pays later, against the
 // launches tuned for them.  us unpartitioned / partitioned, 64-bit keys:
-//   BS   n = 2^17: 95 / 88 at 2^22 lookups, 342 / 283 at 2^24 (32-bit keys 77 /
-//        86 and 276 / 250); 2^18: 55 / 63 at 2^21, 115 / 92 at 2^22; 2^20: 63 /
-//        62 at 2^20, 258 / 98 at 2^22
+//   BS   n = 2^17: 316 / 292 at 2^24 lookups, 2858 / 1967 at 2^27 (32-bit keys,
+//        Zipf 1.1: 228 / 248 and 2097 / 1813); 2^18: 102 / 97 at 2^22, 195 / 158
+//        at 2^23 (Zipf 1.1: 86 / 89 and 163 / 143); 2^20: 112 / 73 at 2^21, 211 /
+//        103 at 2^22
 //   EBS  n = 2^18: 119 / 139 at 2^22, 441 / 502 at 2^24; 2^20: 103 / 92 at 2^21,
 //        193 / 141 at 2^22
 //   EKS  k = 9, which reads few lines as it is; tables of a ninth of the keys:
@@ -67,7 +68,7 @@ inline uint64_t part_min(const idx_index *h) {
     const bool small = n < 3u << 18;
     if (h->layout == IDX_EKS) return small ? 3ull << 21 : (1ull << 21) + n / 12;
     if (h->layout == IDX_EBS) return small ? ~0ull : n < 1u << 21 ? 3ull << 20 : kPartMin;
-    return n < 1u << 18 ? 1ull << 23 : small ? 3ull << 20 : kPartMin;
+    return n < 1u << 18 ? 1ull << 26 : small ? 1ull << 23 : kPartMin;
 }
 
 // The same for range calls: BS n = 2^18 123 / 130 at 2^20 ranges, 372 / 285 at

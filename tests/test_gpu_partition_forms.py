@@ -17,8 +17,9 @@ if not torch.cuda.is_available():  # pragma: no cover
     pytest.skip("no GPU", allow_module_level=True)
 
 def _batch(n):
-    """A batch that is partitioned on sets of n keys: the smallest at n >= 2^21."""
-    return 3 << 18 if n >= 1 << 21 else 3 << 20 if n >= 3 << 18 else 1 << 23
+    """A batch that is partitioned on sets of n keys (n >= 2^18; of ranges, any
+    n): the smallest at n >= 2^21."""
+    return 3 << 18 if n >= 1 << 21 else 3 << 20
 
 
 M_KARY = 3 << 21
@@ -54,7 +55,7 @@ def test_partition_points_and_ranges(n, bits, kind):
     at = np.searchsorted(sk, q)
     hit = sk[np.minimum(at, n - 1)] == q
     want = np.where(hit, sr[np.minimum(at, n - 1)], np.uint32(0xFFFFFFFF))
-    lo = _bounds(sk, rs, dt, min(_batch(n), 3 << 20) + 3)
+    lo = _bounds(sk, rs, dt, _batch(n) + 3)
     hi = lo + dt(rs.randint(0, 1000))
     wide = rs.randint(0, n, 64)
     lo[100:164] = sk[wide]
@@ -103,3 +104,18 @@ def test_partition_eks_tables(n, bits, k, kind):
         got = ix.point(to_dev(q)).cpu().numpy().view(np.uint32)
     bad = np.nonzero(got != want)[0]
     assert len(bad) == 0, (len(bad), q[bad[0]], got[bad[0]], want[bad[0]])
+
+
+@pytest.mark.parametrize("n,m", [(1025, 1 << 26), ((1 << 17) - 1, (1 << 26) + 3), ((1 << 18) + 1, (1 << 23) + 1)])
+def test_partition_small_sets(n, m):
+    """Sets whose tables are short, at the smallest batches that are partitioned there."""
+    keys, rows = gen.unique_keys(gen.BASE_SEED + n, n, 32, 31)
+    g = torch.Generator(device="cuda").manual_seed(n)
+    dk, q = to_dev(keys), torch.randint(0, 1 << 31, (m,), generator=g, device="cuda").to(torch.int32)
+    q[::3] = dk[torch.randint(0, n, (len(q[::3]),), generator=g, device="cuda")]
+    with idx.Index(dk, to_dev(rows), layout="bs") as ix:
+        ix.set_params(reorder=0)
+        want = ix.point(q)
+        ix.set_params(reorder=2)
+        assert torch.equal(ix.point(q), want)
+    assert int((want != -1).sum()) >= m // 3
