@@ -62,11 +62,12 @@ constexpr uint64_t kPartMin = 3ull << 18;
 //   EKS  k = 9, which reads few lines as it is; tables of a ninth of the keys:
 //        n = 2^18: 86 / 93 at 2^22, 325 / 301 at 2^24; 2^20: 69 / 76 at 2^21, 136
 //        / 103 at 2^22; 2^23: 67 / 89 at 2^20, 222 / 141 at 2^22; 2^26: 90 / 220
-//        at 2^20, 309 / 348 at 2^22, 1183 / 725 at 2^24
+//        at 2^20, 309 / 348 at 2^22, 1183 / 725 at 2^24; n = 5 10^7, half misses,
+//        Zipf 1.1: 335 / 354 at 7 10^6
 inline uint64_t part_min(const idx_index *h) {
     const uint64_t n = h->n;
     const bool small = n < 3u << 18;
-    if (h->layout == IDX_EKS) return small ? 3ull << 21 : (1ull << 21) + n / 12;
+    if (h->layout == IDX_EKS) return small ? 3ull << 21 : (1ull << 21) + n / 8;
     if (h->layout == IDX_EBS) return small ? ~0ull : n < 1u << 21 ? 3ull << 20 : kPartMin;
     return n < 1u << 18 ? 1ull << 26 : small ? 1ull << 23 : kPartMin;
 }
