@@ -12,13 +12,14 @@
 // Rules:
 //   * A block carries an event recorded on the stream that freed it; the
 //     stream that takes it next waits for that event, so any stream and any
-//     thread may take it.  The null stream, which cannot be destroyed, needs
-//     none from itself: a block it freed records its event only when another
-//     stream takes the block (a record and a wait cost a range call 21 us of
-//     2555 on its two scratch blocks).
+//     thread may take it.  A block that the null stream freed has none (a
+//     record and a wait cost a range call 21 us of 2555 on its two scratch
+//     blocks): calls on the null stream alone take it again or give it back.
+//     A call on another stream does no work on the null stream, which would
+//     break a capture that any thread has under way.
 //   * At most kCacheBytes and kCacheBlocks idle blocks are kept per device;
-//     a block not taken again within kCacheAge requests goes back to the
-//     driver, and all idle blocks do when an allocation fails.
+//     a block not taken again within kCacheAge requests is given back, and
+//     all idle blocks are when an allocation fails.
 //   * A stream under graph capture bypasses the cache: its allocations and
 //     frees become graph nodes, as without it.
 #include <mutex>
@@ -40,7 +41,7 @@ struct Block {
     size_t bytes;
     int dev;
     hipEvent_t ev;   // recorded where the block was last freed, unless on_null
-    bool on_null;    // last freed on the null stream
+    bool on_null;    // last freed on the null stream, whose calls alone may touch it
     uint64_t tick;   // request count at that time
 };
 
@@ -76,8 +77,8 @@ bool capturing(hipStream_t s) {
 
 // Orders `s` after the work that used b (b.dev is the current device).
 void wait_for(const Block &b, hipStream_t s) {
-    if (b.on_null && s == nullptr) return;
-    if ((b.on_null && hipEventRecord(b.ev, nullptr) != hipSuccess) || hipStreamWaitEvent(s, b.ev, 0) != hipSuccess) {
+    if (b.on_null) return;  // s is the null stream
+    if (hipStreamWaitEvent(s, b.ev, 0) != hipSuccess) {
         (void)hipGetLastError();
         (void)hipDeviceSynchronize();
     }
@@ -93,13 +94,22 @@ void give_back(const std::vector<Block> &gone, hipStream_t s) {
     (void)hipGetLastError();
 }
 
+// Whether a call on stream s of device dev may take b or give it back.
+bool reach(const Block &b, int dev, hipStream_t s) { return b.dev == dev && (!b.on_null || s == nullptr); }
+
 // Moves device dev's idle blocks that are beyond the bounds (all: every one)
-// from the cache to `gone`.
-void evict(Cache *c, int dev, bool all, std::vector<Block> &gone) {
+// from the cache to `gone`, as far as a call on s reaches them; the others
+// count first, so that the bounds hold.
+void evict(Cache *c, int dev, hipStream_t s, bool all, std::vector<Block> &gone) {
     size_t bytes = 0, blocks = 0;
+    for (const Block &b : c->idle)
+        if (b.dev == dev && !reach(b, dev, s)) {
+            bytes += b.bytes;
+            ++blocks;
+        }
     for (size_t i = c->idle.size(); i-- > 0;) {  // newest first
         const Block &b = c->idle[i];
-        if (b.dev != dev) continue;
+        if (!reach(b, dev, s)) continue;
         bytes += b.bytes;
         ++blocks;
         if (all || bytes > kCacheBytes || blocks > kCacheBlocks || c->tick - b.tick > kCacheAge) {
@@ -156,7 +166,7 @@ void *cached_get(size_t bytes, hipStream_t s, hipError_t *err) {
         size_t best = c->idle.size();
         for (size_t i = 0; i < c->idle.size(); ++i) {
             const Block &f = c->idle[i];
-            if (f.dev == dev && f.bytes >= want && f.bytes <= want + want / 4 &&
+            if (reach(f, dev, s) && f.bytes >= want && f.bytes <= want + want / 4 &&
                 (best == c->idle.size() || f.bytes <= c->idle[best].bytes))
                 best = i;
         }
@@ -165,7 +175,7 @@ void *cached_get(size_t bytes, hipStream_t s, hipError_t *err) {
             b = c->idle[best];
             c->idle.erase(c->idle.begin() + (long)best);
         }
-        evict(c, dev, false, gone);
+        evict(c, dev, s, false, gone);
     } catch (...) {  // host memory: what was found so far stands
     }
     give_back(gone, s);
@@ -179,7 +189,7 @@ void *cached_get(size_t bytes, hipStream_t s, hipError_t *err) {
     if (!b.p) {
         try {
             std::lock_guard<std::mutex> lock(c->mu);
-            evict(c, dev, true, gone);
+            evict(c, dev, s, true, gone);
         } catch (...) {
         }
         if (gone.empty()) return nullptr;
@@ -216,7 +226,7 @@ void cached_put(void *p, hipStream_t s) {
                     b.tick = c->tick;
                     c->idle.push_back(b);
                     kept = true;
-                    evict(c, b.dev, false, gone);
+                    evict(c, b.dev, s, false, gone);
                 }
             } catch (...) {  // host memory
             }
