@@ -75,19 +75,33 @@ bool capturing(hipStream_t s) {
     return st != hipStreamCaptureStatusNone;
 }
 
-// Orders `s` after the work that used b (b.dev is the current device).
-void wait_for(const Block &b, hipStream_t s) {
-    if (b.on_null) return;  // s is the null stream
-    if (hipStreamWaitEvent(s, b.ev, 0) != hipSuccess) {
-        (void)hipGetLastError();
-        (void)hipDeviceSynchronize();
+// Orders `s` after the work that used b (b.dev is the current device); false:
+// neither the stream nor the host can wait for it, and b stays as it is.
+bool wait_for(const Block &b, hipStream_t s) {
+    if (b.on_null) return true;  // s is the null stream
+    if (hipStreamWaitEvent(s, b.ev, 0) == hipSuccess || hipEventSynchronize(b.ev) == hipSuccess) return true;
+    (void)hipGetLastError();
+    return false;
+}
+
+// Back to the idle blocks, the next to be evicted (without host memory for
+// that, b is lost).
+void restore(Cache *c, const Block &b) {
+    try {
+        std::lock_guard<std::mutex> lock(c->mu);
+        c->taken.erase(b.p);
+        c->idle.insert(c->idle.begin(), b);
+    } catch (...) {
     }
 }
 
 // Blocks back to the driver, after the work that used them.
-void give_back(const std::vector<Block> &gone, hipStream_t s) {
+void give_back(Cache *c, const std::vector<Block> &gone, hipStream_t s) {
     for (const Block &b : gone) {
-        wait_for(b, s);
+        if (!wait_for(b, s)) {
+            restore(c, b);
+            continue;
+        }
         (void)hipFreeAsync(b.p, s);
         (void)hipEventDestroy(b.ev);
     }
@@ -178,12 +192,13 @@ void *cached_get(size_t bytes, hipStream_t s, hipError_t *err) {
         evict(c, dev, s, false, gone);
     } catch (...) {  // host memory: what was found so far stands
     }
-    give_back(gone, s);
+    give_back(c, gone, s);
     gone.clear();
     *err = hipSuccess;
     if (b.p) {
-        wait_for(b, s);
-        return b.p;
+        if (wait_for(b, s)) return b.p;
+        restore(c, b);
+        b = Block{nullptr, want, dev, nullptr, false, 0};
     }
     b.p = plain_get(want, s, err);
     if (!b.p) {
@@ -193,7 +208,7 @@ void *cached_get(size_t bytes, hipStream_t s, hipError_t *err) {
         } catch (...) {
         }
         if (gone.empty()) return nullptr;
-        give_back(gone, s);
+        give_back(c, gone, s);
         (void)hipStreamSynchronize(s);
         return plain_get(bytes, s, err);
     }
@@ -237,7 +252,7 @@ void cached_put(void *p, hipStream_t s) {
         }
     }
     if (!kept) (void)hipFreeAsync(p, s);
-    give_back(gone, s);
+    give_back(c, gone, s);
 }
 
 }  // namespace idx

@@ -34,7 +34,8 @@ size_t g_held = 0, g_capacity = ~(size_t)0;  // live, and freed but still in the
 char *g_next = (char *)0x100000;
 std::map<hipEvent_t, Clock> g_events;
 uint64_t g_event_id = 0;
-bool g_capture = false;      // SC is being captured (a blocking stream, any thread)
+bool g_no_wait = false;  // waits for events and for the device fail
+bool g_capture = false;  // SC is being captured (a blocking stream, any thread)
 std::vector<std::string> g_wrong;
 
 void wrong(const std::string &what) {
@@ -110,7 +111,14 @@ hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) {
 }
 hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned) {
     if (breaks_capture(s, "hipStreamWaitEvent")) return hipErrorStreamCaptureImplicit;
+    if (g_no_wait) return hipErrorUnknown;
     join(g_clock[id(s)], g_events[e]);
+    return hipSuccess;
+}
+hipError_t hipEventSynchronize(hipEvent_t e) {
+    if (g_no_wait) return hipErrorUnknown;
+    join(g_host, g_events[e]);
+    for (auto &c : g_clock) join(c, g_host);
     return hipSuccess;
 }
 hipError_t hipStreamSynchronize(hipStream_t s) {
@@ -120,6 +128,7 @@ hipError_t hipStreamSynchronize(hipStream_t s) {
 }
 hipError_t hipDeviceSynchronize(void) {
     if (breaks_capture(nullptr, "hipDeviceSynchronize")) return hipErrorStreamCaptureImplicit;
+    if (g_no_wait) return hipErrorUnknown;
     for (auto &c : g_clock) join(g_host, c);
     for (auto &c : g_clock) join(c, g_host);
     return hipSuccess;
@@ -190,8 +199,23 @@ void capture_elsewhere() {
     if (!c || g_mem[(char *)c].live) wrong("a captured stream's block stayed in the cache");
 }
 
+// A block whose last use cannot be waited for is neither handed out nor freed;
+// it serves again once it can be.
+void failed_wait() {
+    void *p = get(3 * MiB, SA);
+    use(p, SA);
+    put(p, SA);
+    g_no_wait = true;
+    void *q = get(3 * MiB, SB);
+    if (!q || q == p) return wrong("a block was handed out unordered");
+    for (int i = 0; i < 600; ++i) put(get((size_t)(1 + i % 40) * 40 * MiB, SB), SB);  // outlives and pushes out
+    g_no_wait = false;
+    if (get(3 * MiB, SA) != p) wrong("the block was lost");
+}
+
 struct Scenario { const char *name; void (*run)(); };
-const Scenario kAll[] = {{"order", order}, {"capture_elsewhere", capture_elsewhere}};
+const Scenario kAll[] = {{"order", order}, {"capture_elsewhere", capture_elsewhere},
+                         {"failed_wait", failed_wait}};
 
 }  // namespace
 
