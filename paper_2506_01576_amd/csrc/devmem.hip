@@ -18,8 +18,9 @@
 //     A call on another stream does no work on the null stream, which would
 //     break a capture that any thread has under way.
 //   * At most kCacheBytes and kCacheBlocks idle blocks are kept per device;
-//     a block not taken again within kCacheAge requests is given back, and
-//     all idle blocks are when an allocation fails.
+//     a block not taken again within kCacheAge requests is given back to the
+//     runtime's pool, and all idle blocks are, through it, to the driver when
+//     an allocation of any size fails.
 //   * A stream under graph capture bypasses the cache: its allocations and
 //     frees become graph nodes, as without it.
 #include <mutex>
@@ -162,13 +163,39 @@ void *plain_get(size_t bytes, hipStream_t s, hipError_t *err) {
     return nullptr;
 }
 
+// Device dev's idle blocks back to the driver, with what the runtime's pool
+// keeps: for a call on s that found no memory.  The null stream's blocks go
+// too, unless a capture is under way that work on the null stream would break.
+void give_back_all(Cache *c, int dev, hipStream_t s) {
+    const hipStream_t streams[2] = {s, nullptr};
+    for (int i = 0; i < (s != nullptr && !capturing(nullptr) ? 2 : 1); ++i) {
+        std::vector<Block> gone;
+        try {
+            std::lock_guard<std::mutex> lock(c->mu);
+            evict(c, dev, streams[i], true, gone);
+        } catch (...) {  // host memory: what was found so far
+        }
+        give_back(c, gone, streams[i]);
+        (void)hipStreamSynchronize(streams[i]);
+    }
+    hipMemPool_t pool;
+    if (hipDeviceGetDefaultMemPool(&pool, dev) == hipSuccess) (void)hipMemPoolTrimTo(pool, 0);
+    (void)hipGetLastError();
+}
+
 }  // namespace
 
 void *cached_get(size_t bytes, hipStream_t s, hipError_t *err) {
     Cache *c = cache();
     int dev = 0;
-    if (!c || bytes > kCacheBytes || hipGetDevice(&dev) != hipSuccess || capturing(s)) {
+    if (!c || hipGetDevice(&dev) != hipSuccess || capturing(s)) {
         (void)hipGetLastError();
+        return plain_get(bytes, s, err);
+    }
+    if (bytes > kCacheBytes) {  // not kept when it is freed
+        void *p = plain_get(bytes, s, err);
+        if (p) return p;
+        give_back_all(c, dev, s);
         return plain_get(bytes, s, err);
     }
     const size_t want = rounded(bytes);
@@ -202,14 +229,7 @@ void *cached_get(size_t bytes, hipStream_t s, hipError_t *err) {
     }
     b.p = plain_get(want, s, err);
     if (!b.p) {
-        try {
-            std::lock_guard<std::mutex> lock(c->mu);
-            evict(c, dev, s, true, gone);
-        } catch (...) {
-        }
-        if (gone.empty()) return nullptr;
-        give_back(c, gone, s);
-        (void)hipStreamSynchronize(s);
+        give_back_all(c, dev, s);
         return plain_get(bytes, s, err);
     }
     if (hipEventCreateWithFlags(&b.ev, hipEventDisableTiming) != hipSuccess) {

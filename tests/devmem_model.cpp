@@ -76,6 +76,14 @@ hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
 hipError_t hipGetLastError(void) { return hipSuccess; }
 hipError_t hipDeviceGetDefaultMemPool(hipMemPool_t *p, int) { *p = nullptr; return hipSuccess; }
 hipError_t hipMemPoolSetAttribute(hipMemPool_t, hipMemPoolAttr, void *) { return hipSuccess; }
+hipError_t hipMemPoolTrimTo(hipMemPool_t, size_t) {  // freed blocks that the host has waited for
+    for (auto &m : g_mem)
+        if (!m.second.live && m.second.bytes && before(m.second.used, g_host)) {
+            g_held -= m.second.bytes;
+            m.second.bytes = 0;
+        }
+    return hipSuccess;
+}
 hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus *st) {
     *st = s == SC && g_capture ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
     return s == nullptr && g_capture ? hipErrorStreamCaptureImplicit : hipSuccess;
@@ -213,9 +221,40 @@ void failed_wait() {
     if (get(3 * MiB, SA) != p) wrong("the block was lost");
 }
 
+// A request that does not fit beside the idle blocks gets their memory, also
+// one larger than the cache keeps, and also from the null stream's blocks.
+void memory_short() {
+    g_capacity = 12ull << 30;
+    const size_t sizes[] = {7ull << 30, 11ull << 30};
+    const hipStream_t from[] = {S0, SA}, to[] = {S0, SA, SB};
+    for (size_t bytes : sizes)
+        for (hipStream_t f : from)
+            for (hipStream_t t : to) {
+                std::vector<void *> p;
+                for (int i = 0; i < 6; ++i) p.push_back(get((900 + 10 * i) * MiB, f));
+                for (void *q : p) {
+                    if (!q) return wrong("no memory for the first blocks");
+                    use(q, f);
+                    put(q, f);
+                }
+                void *big = get(bytes, t);
+                if (!big) return wrong("no memory, with idle blocks kept");
+                put(big, t);
+                (void)hipStreamSynchronize(t);  // one larger than the cache keeps is freed
+            }
+    // what the null stream freed stays out of reach during another stream's capture
+    void *p = get(7ull << 30, S0);
+    if (!p) return wrong("no memory");
+    put(p, S0);
+    g_capture = true;
+    if (get(8ull << 30, SA)) wrong("memory from nowhere");
+    g_capture = false;
+    if (!get(8ull << 30, SA)) wrong("no memory after the capture");
+}
+
 struct Scenario { const char *name; void (*run)(); };
 const Scenario kAll[] = {{"order", order}, {"capture_elsewhere", capture_elsewhere},
-                         {"failed_wait", failed_wait}};
+                         {"failed_wait", failed_wait}, {"memory_short", memory_short}};
 
 }  // namespace
 
