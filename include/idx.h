@@ -77,7 +77,8 @@ typedef void *idx_stream;             /* hipStream_t */
  * Both must be stream-ordered with respect to `stream`: a buffer released on
  * a stream may be reused only by work enqueued after the release.  Passing
  * NULL selects hipMallocAsync / hipFreeAsync on the call's stream, with up to
- * 8 GiB of freed blocks per device kept mapped for later calls.
+ * 8 GiB of freed blocks per device kept mapped for later calls (idx_trim gives
+ * them back).
  */
 typedef struct idx_allocator {
     void *(*alloc)(void *ctx, size_t bytes, idx_stream stream);
@@ -228,6 +229,13 @@ int idx_range_noalloc(idx_handle h, const void *lo, const void *hi, uint64_t m, 
  * IDX_ERR_ARG, and nothing is freed, while a batch (idx_batch_create) holds
  * the handle. */
 int idx_destroy(idx_handle h);
+
+/* idx_trim -- give the freed blocks that the library keeps on the current
+ * device for later calls (no allocator given) back to the driver, with what
+ * the runtime's default memory pool holds beside them.  Synchronises the
+ * device, so it may not be called while a stream is captured.  IDX_ERR_HIP when
+ * that fails (the blocks are kept). */
+int idx_trim(void);
 
 /* Text for a status code (static storage). */
 const char *idx_strerror(int status);

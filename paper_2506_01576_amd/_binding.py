@@ -116,6 +116,7 @@ SIGNATURES = {
     "idx_range": (_I, [_P, _P, _P, _U64, _P, _P, _U64, ctypes.POINTER(_U64), _P]),
     "idx_range_noalloc": (_I, [_P, _P, _P, _U64, _P, _P, _U64, ctypes.POINTER(_U64), _P]),
     "idx_destroy": (_I, [_P]),
+    "idx_trim": (_I, []),
     "idx_strerror": (ctypes.c_char_p, [_I]),
     "idx_last_hip_error": (_I, []),
     "idx_get_info": (_I, [_P, ctypes.POINTER(idx_info)]),
@@ -165,6 +166,12 @@ def lib():
             fn.argtypes = args
         _lib = L
     return _lib
+
+
+def trim():
+    """Give the freed device memory that the library keeps for later calls
+    back to the driver (idx_trim); synchronises the device."""
+    _check(lib().idx_trim(), "idx_trim")
 
 
 def _stream(stream) -> int:

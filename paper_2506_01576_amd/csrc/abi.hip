@@ -330,6 +330,8 @@ int idx_destroy(idx_handle h) {
     return IDX_OK;
 }
 
+int idx_trim(void) { return cached_trim(); }
+
 int idx_get_info(idx_handle h, idx_info *o) {
     if (!h || !o) return IDX_ERR_ARG;
     idx_info i{};

@@ -20,7 +20,7 @@
 //   * At most kCacheBytes and kCacheBlocks idle blocks are kept per device;
 //     a block not taken again within kCacheAge requests is given back to the
 //     runtime's pool, and all idle blocks are, through it, to the driver when
-//     an allocation of any size fails.
+//     an allocation of any size fails, or on request (cached_trim).
 //   * A stream under graph capture bypasses the cache: its allocations and
 //     frees become graph nodes, as without it.
 #include <mutex>
@@ -163,24 +163,33 @@ void *plain_get(size_t bytes, hipStream_t s, hipError_t *err) {
     return nullptr;
 }
 
+// Device dev's idle blocks that a call on s reaches, to the runtime's pool.
+void give_back_idle(Cache *c, int dev, hipStream_t s) {
+    std::vector<Block> gone;
+    try {
+        std::lock_guard<std::mutex> lock(c->mu);
+        evict(c, dev, s, true, gone);
+    } catch (...) {  // host memory: what was found so far
+    }
+    give_back(c, gone, s);
+    (void)hipStreamSynchronize(s);
+    (void)hipGetLastError();
+}
+
+// What the runtime's pool keeps, to the driver.
+void trim_pool(int dev) {
+    hipMemPool_t pool;
+    if (hipDeviceGetDefaultMemPool(&pool, dev) == hipSuccess) (void)hipMemPoolTrimTo(pool, 0);
+    (void)hipGetLastError();
+}
+
 // Device dev's idle blocks back to the driver, with what the runtime's pool
 // keeps: for a call on s that found no memory.  The null stream's blocks go
 // too, unless a capture is under way that work on the null stream would break.
 void give_back_all(Cache *c, int dev, hipStream_t s) {
-    const hipStream_t streams[2] = {s, nullptr};
-    for (int i = 0; i < (s != nullptr && !capturing(nullptr) ? 2 : 1); ++i) {
-        std::vector<Block> gone;
-        try {
-            std::lock_guard<std::mutex> lock(c->mu);
-            evict(c, dev, streams[i], true, gone);
-        } catch (...) {  // host memory: what was found so far
-        }
-        give_back(c, gone, streams[i]);
-        (void)hipStreamSynchronize(streams[i]);
-    }
-    hipMemPool_t pool;
-    if (hipDeviceGetDefaultMemPool(&pool, dev) == hipSuccess) (void)hipMemPoolTrimTo(pool, 0);
-    (void)hipGetLastError();
+    give_back_idle(c, dev, s);
+    if (s != nullptr && !capturing(nullptr)) give_back_idle(c, dev, nullptr);
+    trim_pool(dev);
 }
 
 }  // namespace
@@ -243,6 +252,19 @@ void *cached_get(size_t bytes, hipStream_t s, hipError_t *err) {
         (void)hipEventDestroy(b.ev);
     }
     return b.p;
+}
+
+int cached_trim() {
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e == hipSuccess) e = hipDeviceSynchronize();
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        return hip_fail(e);
+    }
+    if (Cache *c = cache()) give_back_idle(c, dev, nullptr);
+    trim_pool(dev);
+    return IDX_OK;
 }
 
 void cached_put(void *p, hipStream_t s) {

@@ -45,6 +45,7 @@ struct Alloc {
 // a bounded cache of freed blocks, stream-ordered like them)
 void *cached_get(size_t bytes, hipStream_t s, hipError_t *err);
 void cached_put(void *p, hipStream_t s);
+int cached_trim();  // the current device's idle blocks back to the driver
 
 struct LearnedModel;  // learned rank model (learned.hip)
 

@@ -14,6 +14,10 @@
 
 #include "devmem.hip"
 
+namespace idx {
+int hip_fail(hipError_t) { return IDX_ERR_HIP; }
+}  // namespace idx
+
 namespace {
 
 constexpr int kStreams = 4;
@@ -252,9 +256,27 @@ void memory_short() {
     if (!get(8ull << 30, SA)) wrong("no memory after the capture");
 }
 
+// Every idle block goes back on request, whichever stream freed it.
+void trim() {
+    const hipStream_t all[3] = {S0, SA, SB};
+    void *kept = get(5 * MiB, SB);
+    for (int i = 0; i < 30; ++i) put(get((size_t)(1 + i) * 7 * MiB, all[i % 3]), all[i % 3]);
+    if (idx::cached_trim() != IDX_OK) wrong("trim failed");
+    if (g_held != g_mem[(char *)kept].bytes) wrong("memory is held after the trim");
+    put(kept, SB);
+    void *p = get(6 * MiB, SA);
+    use(p, SA);
+    put(p, SA);
+    g_no_wait = true;
+    if (idx::cached_trim() == IDX_OK) wrong("trim without the device's synchronisation");
+    g_no_wait = false;
+    if (get(6 * MiB, SA) != p) wrong("the block was lost");
+}
+
 struct Scenario { const char *name; void (*run)(); };
 const Scenario kAll[] = {{"order", order}, {"capture_elsewhere", capture_elsewhere},
-                         {"failed_wait", failed_wait}, {"memory_short", memory_short}};
+                         {"failed_wait", failed_wait}, {"memory_short", memory_short},
+                         {"trim", trim}};
 
 }  // namespace
 
