@@ -278,8 +278,10 @@ void cached_put(void *p, hipStream_t s) {
             Block b = it->second;
             c->taken.erase(it);
             try {
+                int dev = -1;  // s may belong to another device than the block: not kept then
                 b.on_null = s == nullptr;
-                if (!capturing(s) && (b.on_null || hipEventRecord(b.ev, s) == hipSuccess)) {
+                if (hipGetDevice(&dev) == hipSuccess && dev == b.dev && !capturing(s) &&
+                    (b.on_null || hipEventRecord(b.ev, s) == hipSuccess)) {
                     b.tick = c->tick;
                     c->idle.push_back(b);
                     kept = true;

@@ -45,7 +45,8 @@ std::vector<std::string> g_wrong;
 void wrong(const std::string &what) {
     if (g_wrong.size() < 5) g_wrong.push_back(what);
 }
-int id(hipStream_t s) { return s == nullptr ? 0 : (int)((char *)s - g_handle); }
+int g_dev = 0;  // current device; device 1 has a null stream alone, with SC's clock
+int id(hipStream_t s) { return s == nullptr ? 3 * g_dev : (int)((char *)s - g_handle); }
 bool before(const Clock &a, const Clock &b) {
     for (int i = 0; i < kStreams; ++i)
         if (a[i] > b[i]) return false;
@@ -76,7 +77,7 @@ void use(void *p, hipStream_t s) {
 }  // namespace
 
 extern "C" {
-hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
+hipError_t hipGetDevice(int *d) { *d = g_dev; return hipSuccess; }
 hipError_t hipGetLastError(void) { return hipSuccess; }
 hipError_t hipDeviceGetDefaultMemPool(hipMemPool_t *p, int) { *p = nullptr; return hipSuccess; }
 hipError_t hipMemPoolSetAttribute(hipMemPool_t, hipMemPoolAttr, void *) { return hipSuccess; }
@@ -273,10 +274,21 @@ void trim() {
     if (get(6 * MiB, SA) != p) wrong("the block was lost");
 }
 
+// A block of device 0 freed with device 1 current: its null stream is another.
+void other_device() {
+    void *p = get(3 * MiB, S0);
+    g_dev = 1;
+    (void)hipDeviceSynchronize();
+    use(p, S0);
+    put(p, S0);
+    g_dev = 0;
+    if (!get(3 * MiB, S0)) wrong("no memory");
+}
+
 struct Scenario { const char *name; void (*run)(); };
 const Scenario kAll[] = {{"order", order}, {"capture_elsewhere", capture_elsewhere},
                          {"failed_wait", failed_wait}, {"memory_short", memory_short},
-                         {"trim", trim}};
+                         {"trim", trim}, {"other_device", other_device}};
 
 }  // namespace
 

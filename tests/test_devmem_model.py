@@ -19,7 +19,8 @@ def model(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("scenario", ["order", "capture_elsewhere", "failed_wait", "memory_short", "trim"])
+@pytest.mark.parametrize("scenario", ["order", "capture_elsewhere", "failed_wait", "memory_short", "trim",
+                                      "other_device"])
 def test_devmem_model(model, scenario):
     r = subprocess.run([model, scenario], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0, r.stdout
