@@ -1001,9 +1001,11 @@ int idx_batch_create(const idx_handle *indexes, uint32_t count, idx_stream strea
         if (h->params.lds_levels && !(h->learned && h->params.model != 2)) {
             const int rc = build_pin(h, h->params.lds_levels, (hipStream_t)stream);
             if (rc != IDX_OK) return rc;
-            d.pin = h->pin;
-            d.pin_levels = h->params.lds_levels;
-            d.pin_keys = h->pin_keys;
+            if (h->pin_levels_built == h->params.lds_levels) {
+                d.pin = h->pin;
+                d.pin_levels = h->params.lds_levels;
+                d.pin_keys = h->pin_keys;
+            }
         }
         if (h->layout == IDX_BS) {
             d.form = F_BS;

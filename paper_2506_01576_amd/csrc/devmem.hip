@@ -67,15 +67,6 @@ size_t rounded(size_t bytes) {
     return (bytes + step - 1) / step * step;
 }
 
-bool capturing(hipStream_t s) {
-    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(s, &st) != hipSuccess) {
-        (void)hipGetLastError();
-        return true;
-    }
-    return st != hipStreamCaptureStatusNone;
-}
-
 // Orders `s` after the work that used b (b.dev is the current device); false:
 // neither the stream nor the host can wait for it, and b stays as it is.
 bool wait_for(const Block &b, hipStream_t s) {
@@ -193,6 +184,15 @@ void give_back_all(Cache *c, int dev, hipStream_t s) {
 }
 
 }  // namespace
+
+bool capturing(hipStream_t s) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &st) != hipSuccess) {
+        (void)hipGetLastError();
+        return true;
+    }
+    return st != hipStreamCaptureStatusNone;
+}
 
 void *cached_get(size_t bytes, hipStream_t s, hipError_t *err) {
     Cache *c = cache();

@@ -46,6 +46,10 @@ struct Alloc {
 void *cached_get(size_t bytes, hipStream_t s, hipError_t *err);
 void cached_put(void *p, hipStream_t s);
 int cached_trim();  // the current device's idle blocks back to the driver
+// Whether work on s is recorded into a graph (or may not be enqueued, for
+// another stream's capture).  What a handle keeps is not made then: its memory
+// and contents would be there only while the graph runs.
+bool capturing(hipStream_t s);
 
 struct LearnedModel;  // learned rank model (learned.hip)
 
@@ -125,7 +129,8 @@ int check_sorted(const void *sorted_keys, const uint32_t *sorted_rows, uint64_t 
                  hipStream_t s);
 // Copies the layout into SoA caller buffers.
 int export_layout(const idx_index *h, void *keys_out, uint32_t *rows_out, hipStream_t s);
-// (Re)builds the LDS pin table of the top `levels` tree levels.
+// (Re)builds the LDS pin table of the top `levels` tree levels unless it is
+// there; not under capture (pin_levels_built tells).
 int build_pin(idx_index *h, uint32_t levels, hipStream_t s);
 // Sorted rank of level-order slot t (0-based) -- Sections 4 and 6.1.
 __host__ __device__ inline uint64_t slot_rank(const Geo &G, uint64_t t);

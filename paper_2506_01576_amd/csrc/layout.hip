@@ -267,6 +267,7 @@ uint32_t pin_levels_for(const idx_index *h, size_t bytes) {
 
 int build_pin(idx_index *h, uint32_t levels, hipStream_t s) {
     if (levels == h->pin_levels_built && (levels == 0 || h->pin)) return IDX_OK;
+    if (capturing(s)) return IDX_OK;
     if (h->pin) {
         h->alloc.put(h->pin, s);
         h->pin = nullptr;
