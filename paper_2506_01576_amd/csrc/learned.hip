@@ -1378,10 +1378,11 @@ __global__ __launch_bounds__(256) void k_point_lines_pair(Load<K, AOS> keys, uin
 
 }  // namespace
 
-// Write the model's leaf lines unless they are there.
+// Write the model's leaf lines unless they are there; not under capture (the
+// leaf records' windows then serve).
 int ensure_lines(idx_index *h, hipStream_t s) {
     LearnedModel *M = h->learned;
-    if (M->lines) return IDX_OK;
+    if (M->lines || capturing(s)) return IDX_OK;
     const uint32_t L = M->root.L;
     const size_t bytes = (size_t)L * kLineBytes;
     uint4 *lines = nullptr;
@@ -1499,7 +1500,8 @@ int point_lines(idx_index *h, const idx_lookup_params &p, const PointIO &pio, hi
 int point_learned(idx_index *h, const idx_lookup_params &p, const PointIO &pio, hipStream_t s) {
     if (p.leaf_lines == 1) {
         const int rc = ensure_lines(h, s);
-        return rc != IDX_OK ? rc : point_lines(h, p, pio, s);
+        if (rc != IDX_OK) return rc;
+        if (h->learned->lines) return point_lines(h, p, pio, s);
     }
     const LearnedModel *M = h->learned;
     const uint32_t block = p.block;

@@ -47,3 +47,12 @@ def test_pinned_levels(layout, k, levels, warm):
     with idx.Index(keys, rows, layout=layout, k=k) as ix:
         ix.set_params(lds_levels=levels, persistent=2, block=1024, per_lane=4)
         _captured_point(ix, warm)
+
+
+@pytest.mark.parametrize("warm", [(), (1000,)])
+def test_leaf_lines_asked_for_after_training(warm):
+    keys, rows = gen.unique_keys(SEED, N, 64, 63)
+    with idx.Index(to_dev(keys), to_dev(rows), layout="bs") as ix:
+        ix.learn(N // 4, 2)
+        ix.set_params(leaf_lines=1)
+        _captured_point(ix, warm)
