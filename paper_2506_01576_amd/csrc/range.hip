@@ -205,11 +205,8 @@ __global__ __launch_bounds__(256) void k_range_count_part(RangeArgs<K, AOS> a, u
 // them by their lower bounds, count in partitioned order, then bring each
 // range's packed first rank and count to its position (the scan unpacks them).
 template <typename K, bool AOS>
-int range_count_partitioned(idx_index *h, const RangeArgs<K, AOS> &a, hipStream_t s) {
+int range_count_partitioned(idx_index *h, const RangeArgs<K, AOS> &a, uint64_t chunk, void *t, hipStream_t s) {
     const uint64_t m = a.m;
-    const uint64_t chunk = m < kPartChunk ? m : kPartChunk;
-    void *t = h->alloc.get(range_partition_bytes(h, chunk), s);
-    if (!t) return IDX_ERR_NOMEM;
     int rc = IDX_OK;
     for (uint64_t c0 = 0; c0 < m && rc == IDX_OK; c0 += chunk) {
         const uint64_t mc = (m - c0) < chunk ? (m - c0) : chunk;
@@ -231,7 +228,6 @@ int range_count_partitioned(idx_index *h, const RangeArgs<K, AOS> &a, hipStream_
         }
         rc = range_partition_back(h, v, t, mc, a.offsets + c0, s);
     }
-    h->alloc.put(t, s);
     return rc;
 }
 
@@ -533,16 +529,20 @@ int range_t(idx_index *h, const void *lo, const void *hi, uint64_t m, uint64_t *
     uint64_t tot = 0;
     bool packed = false;  // offsets hold the partition's packed words
     const uint32_t blocks = (uint32_t)((m + 255) / 256);
+    const uint64_t chunk = m < kPartChunk ? m : kPartChunk;
+    void *part = nullptr;  // scratch of the partition; none: ranges are counted as they come
     do {
         if (h->learned && h->params.model != 2) {
             // the no-allocation entry point uses leaf lines only when they
             // exist already (writing them would allocate)
             rc = range_count_learned(h, lo, hi, m, a.first_rank, offsets, given == nullptr, s);
             if (rc != IDX_OK) break;
-        } else if (h->params.reorder >= 2 && !given && range_partition_pays(h, m < kPartChunk ? m : kPartChunk)) {
+        } else if (h->params.reorder >= 2 && !given && range_partition_pays(h, chunk) &&
+                   (part = h->alloc.get(range_partition_bytes(h, chunk), s))) {
             // the caller-given scratch (no-allocation entry point) has no room
             // for the partition: those calls count unpartitioned
-            rc = range_count_partitioned(h, a, s);
+            rc = range_count_partitioned(h, a, chunk, part, s);
+            h->alloc.put(part, s);
             if (rc != IDX_OK) break;
             packed = true;
         } else {

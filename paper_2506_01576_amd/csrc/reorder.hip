@@ -1331,7 +1331,7 @@ int point_partitioned(idx_index *h, const void *q, uint64_t m, uint32_t *out, hi
     if (m < part_min(h) || P.NB == 1) return point_run(h, PointIO{q, m, out, false, false}, s);
     const size_t kb = h->u64 ? 8 : 4;
     char *tmp = (char *)h->alloc.get(part_bytes(chunk, kb, P, false), s);
-    if (!tmp) return IDX_ERR_NOMEM;
+    if (!tmp) return point_run(h, PointIO{q, m, out, false, false}, s);  // the same answers, without scratch
     int rc = IDX_OK;
     for (uint64_t c0 = 0; c0 < m && rc == IDX_OK; c0 += chunk) {
         const uint64_t mc = (m - c0) < chunk ? (m - c0) : chunk;
