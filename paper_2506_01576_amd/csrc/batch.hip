@@ -877,9 +877,7 @@ __global__ __launch_bounds__(BT) void k_batch_mixed_fill(const Desc *__restrict_
                     s_geo[w][lane] = run_geo;
                     s_kinv[w][lane] = run_kinv;
                     s_mode[w][lane] = run_mode;
-                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                    __builtin_amdgcn_wave_barrier();
-                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                    wave_lds_order();
                     constexpr int CU = 4;
                     for (uint32_t t0 = lane; t0 < total; t0 += kWave * CU) {
                         uint32_t v[CU], q[CU];
@@ -906,9 +904,7 @@ __global__ __launch_bounds__(BT) void k_batch_mixed_fill(const Desc *__restrict_
                             if (t < total) s_dst[w][q[u]][t] = v[u];
                         }
                     }
-                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                    __builtin_amdgcn_wave_barrier();
-                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                    wave_lds_order();
                 }
             }
         }

@@ -428,12 +428,12 @@ __global__ __launch_bounds__(256) void k_leaf_train_wave(Load<K, AOS> keys, uint
                 }
 #pragma unroll
                 for (int c = 0; c < 4; ++c) term[lane][c] = v[c];
-                __builtin_amdgcn_wave_barrier();
+                wave_lds_order();
                 if (lane < 4) {
 #pragma unroll 16
                     for (int i = 0; i < kWave; ++i) col += term[i][lane];
                 }
-                __builtin_amdgcn_wave_barrier();
+                wave_lds_order();
             }
 #pragma unroll
             for (int c = 0; c < 4; ++c) a[1 + c] = __shfl(col, c, kWave);

@@ -275,9 +275,7 @@ __global__ __launch_bounds__(256) void k_range_fill_rank(RangeArgs<K, AOS> a) {
         using T = std::remove_reference_t<decltype(*run_start)>;
         run_start[lane] = (T)start;
         run_src[lane] = (T)(r0 - start);
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        wave_lds_order();
         constexpr int CU = 4;
         for (uint64_t t0 = lane; t0 < total; t0 += (uint64_t)kWave * CU) {
             uint32_t v[CU];

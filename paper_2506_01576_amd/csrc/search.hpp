@@ -11,6 +11,14 @@
 
 namespace idx {
 
+// Between a lane's LDS accesses and another lane's of the same wave: those
+// before come first.
+__device__ __forceinline__ void wave_lds_order() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Keys of sorted[b, b + len) (len <= W) below x; `eq` tells whether one of
 // them equals x.  Reads whole 16-byte chunks covering the window: up to one
 // chunk beyond b + len, which the padded layout allocations keep in bounds.

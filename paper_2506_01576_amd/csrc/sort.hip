@@ -226,9 +226,9 @@ __global__ __launch_bounds__(RS_THREADS) void k_scatter(const K *__restrict__ ke
         const uint32_t below = (uint32_t)__popcll(peers & lt_mask);
         const uint32_t before = sm.wave_cnt[wave][d];
         rank[j] = before + below;
-        __builtin_amdgcn_wave_barrier();
+        wave_lds_order();
         if (valid && below == 0) sm.wave_cnt[wave][d] = before + (uint32_t)__popcll(peers);
-        __builtin_amdgcn_wave_barrier();
+        wave_lds_order();
     }
     __syncthreads();
 
@@ -585,9 +585,9 @@ __device__ __forceinline__ void lds_radix_pass(K *s_key, uint16_t *s_idx, uint32
         const uint32_t below = (uint32_t)__popcll(peers & lt_mask);
         const uint32_t before = mine[d];
         rank[j] |= before + below;
-        __builtin_amdgcn_wave_barrier();
+        wave_lds_order();
         if (valid && below == 0) mine[d] = before + (uint32_t)__popcll(peers);
-        __builtin_amdgcn_wave_barrier();
+        wave_lds_order();
         __builtin_amdgcn_sched_barrier(0);  // one pair's ballots at a time: together they spill registers
     }
     __syncthreads();
