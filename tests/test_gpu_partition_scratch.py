@@ -1,7 +1,5 @@
 """Partitioned calls whose scratch the handle's allocator refuses: the answers
 are those of the unpartitioned lookups, which need none."""
-import ctypes
-
 import pytest
 import torch
 
@@ -10,31 +8,12 @@ from gpu_util import to_dev
 
 pytestmark = pytest.mark.gpu
 
-idx = pytest.importorskip("paper_2506_01576_amd")
+pytest.importorskip("paper_2506_01576_amd")
 
 if not torch.cuda.is_available():  # pragma: no cover
     pytest.skip("no GPU", allow_module_level=True)
 
-
-class Arena:
-    """An idx_allocator over torch tensors that refuses requests above `limit`."""
-
-    def __init__(self):
-        self.limit, self.blocks, self.refused = 1 << 62, {}, 0
-        fields = dict(idx.idx_allocator._fields_)
-        self.c = idx.idx_allocator(fields["alloc"](self._alloc), fields["release"](self._release), None)
-
-    def _alloc(self, ctx, nbytes, stream):
-        if nbytes > self.limit:
-            self.refused += 1
-            return None
-        t = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
-        self.blocks[t.data_ptr()] = t
-        return t.data_ptr()
-
-    def _release(self, ctx, p, stream):
-        torch.cuda.synchronize()
-        del self.blocks[p]
+from gpu_arena import Arena  # noqa: E402
 
 
 @pytest.mark.parametrize("layout,k", [("bs", 1), ("ebs", 2), ("eks", 9)])
@@ -45,11 +24,8 @@ def test_refused_scratch(layout, k):
     lo, hi, cnt = gen.ranges(seed, hk, r, 1, 9)
     keys, rows, q, want = to_dev(hk), to_dev(hr), to_dev(q), to_dev(want)
     lo, hi, cnt = to_dev(lo), to_dev(hi), to_dev(cnt)
-    arena, h = Arena(), ctypes.c_void_p()
-    st = idx.lib().idx_build(keys.data_ptr(), rows.data_ptr(), n, {"bs": 0, "ebs": 1, "eks": 2}[layout], k,
-                             idx.IDX_KEY_U64, ctypes.byref(arena.c), None, ctypes.byref(h))
-    assert st == idx.IDX_OK
-    with idx.Index._wrap(h, n, k, layout, 64, keys.dtype) as ix:
+    arena = Arena()
+    with arena.index(keys, rows, layout, k) as ix:
         ix.set_params(reorder=2)
         for limit, refused in ((1 << 62, 0), (8 << 20, 1)):  # the partition's scratch is above 8 MiB, a range call's below
             arena.limit = limit
