@@ -101,7 +101,23 @@ struct PartGeo {
     // others: where the partial level ends, so that every bucket spans about as
     // many keys.
     uint32_t entries, cut_l, cut_r, NB_l, left, right, gaps;
+
+    uint64_t tab;  // entries of the buckets' tables in memory: NB << L, or none
 };
+
+// How a partitioned batch is searched: through the tables of k_part_bs or
+// k_part_eks, by k_part_ebs's descent, or by the handle's own lookup kernel.
+enum class Search { sorted_tables, node_tables, subtrees, own };
+
+Search point_search(const idx_index *h) {
+    if (h->layout == IDX_EBS) return Search::subtrees;
+    if (h->layout == IDX_BS) return h->learned && h->params.model != 2 ? Search::own : Search::sorted_tables;
+    const uint64_t node = (uint64_t)h->geo.g * (h->u64 ? 8 : 4);
+    return !h->aos && (node == 32 || node == 64 || node == 128) ? Search::node_tables : Search::own;
+}
+
+// Ranges: k_part_range_bs's tables, or the counting kernel over the batch.
+Search range_search(const idx_index *h) { return h->layout == IDX_BS ? Search::sorted_tables : Search::own; }
 
 // Bucket b of the k-ary Eytzinger layout: nodes [j0, j1) of level `cut`.
 __host__ __device__ inline void bucket_nodes(const PartGeo &P, uint32_t b, uint32_t &cut, uint32_t &j0, uint32_t &j1) {
@@ -1090,7 +1106,7 @@ void eks_geo(const Geo &G, uint64_t m, PartGeo &P) {
 // whole lines makes them: 1.5 MiB of 64-bit keys and row IDs, 2 MiB of 32-bit
 // ones (an XCD's L2 holds the one or two in flight).  Small sets get shorter
 // tables, for eight buckets or more.
-PartGeo part_geo(const idx_index *h, uint64_t m) {
+PartGeo bucket_geo(const idx_index *h, uint64_t m) {
     PartGeo P{};
     P.NB = 1;
     if (h->n < 4) return P;
@@ -1127,6 +1143,12 @@ PartGeo part_geo(const idx_index *h, uint64_t m) {
     return P;
 }
 
+PartGeo part_geo(const idx_index *h, uint64_t m, Search search) {
+    PartGeo P = bucket_geo(h, m);
+    if (search == Search::sorted_tables || search == Search::node_tables) P.tab = (uint64_t)P.NB << P.L;
+    return P;
+}
+
 size_t up256(size_t v) { return (v + 255) & ~(size_t)255; }
 
 uint64_t part_tiles(uint64_t m) { return (m + kPartTile - 1) / kPartTile; }
@@ -1140,18 +1162,18 @@ struct PartBufs {
     uint32_t *total;    // NB
     uint32_t *starts;   // NB + 1
     void *split;        // NB keys
-    void *tab;          // the buckets' tables: NB << L keys
+    void *tab;          // the buckets' tables, if any: NB << L keys
     uint32_t *rows;     // their row IDs (k-ary Eytzinger layout)
 };
 
 // Row IDs of the tables' entries (k-ary Eytzinger layout).
-size_t row_entries(const PartGeo &P) { return P.entries ? (size_t)P.NB << P.L : 0; }
+size_t row_entries(const PartGeo &P) { return P.entries ? P.tab : 0; }
 
 size_t part_bytes(uint64_t m, size_t kb, const PartGeo &P, bool range) {
     const uint32_t NB = P.NB;
     return up256(m * kb) * (range ? 2 : 1) + up256(m * 2) + up256(m * (range ? 8 : 4)) +
            up256((size_t)NB * part_tiles(m) * 4) + up256((size_t)NB * 4) + up256(((size_t)NB + 1) * 4) +
-           up256((size_t)NB * kb) + up256(((size_t)NB << P.L) * kb) + up256(row_entries(P) * 4);
+           up256((size_t)NB * kb) + up256(P.tab * kb) + up256(row_entries(P) * 4);
 }
 
 PartBufs carve(char *t, uint64_t m, size_t kb, const PartGeo &P, bool range) {
@@ -1170,7 +1192,7 @@ PartBufs carve(char *t, uint64_t m, size_t kb, const PartGeo &P, bool range) {
     p.total = (uint32_t *)take((size_t)NB * 4);
     p.starts = (uint32_t *)take(((size_t)NB + 1) * 4);
     p.split = take((size_t)NB * kb);
-    p.tab = take(((size_t)NB << P.L) * kb);
+    p.tab = take(P.tab * kb);
     p.rows = (uint32_t *)take(row_entries(P) * 4);
     return p;
 }
@@ -1212,8 +1234,7 @@ int partition_t(idx_index *h, const K *q, const K *q_hi, uint64_t m, const PartG
 
 template <typename K, bool AOS>
 int build_tables(const idx_index *h, const PartGeo &P, const PartBufs &B, hipStream_t s) {
-    const uint64_t entries = (uint64_t)P.NB << P.L;
-    hipLaunchKernelGGL((k_part_tables<K, AOS>), dim3((uint32_t)((entries + 255) / 256)), dim3(256), 0, s,
+    hipLaunchKernelGGL((k_part_tables<K, AOS>), dim3((uint32_t)((P.tab + 255) / 256)), dim3(256), 0, s,
                        make_load<K, AOS>(h), h->n, P, (K *)B.tab);
     IDX_LAUNCH_CHECK();
     return IDX_OK;
@@ -1239,29 +1260,28 @@ int chunk_t(idx_index *h, const K *q, uint64_t m, uint32_t *out, const PartGeo &
     int rc = partition_t<K, AOS>(h, q, (const K *)nullptr, m, P, B, s);
     if (rc != IDX_OK) return rc;
     const uint64_t spans = spans_of(m);
-    const bool model = h->learned && h->params.model != 2;
+    const Search search = point_search(h);
     uint32_t *ans = (uint32_t *)B.ans;
-    const uint64_t node = h->geo.g * sizeof(K);
-    if (h->layout == IDX_BS && !model) {
+    if (search == Search::sorted_tables) {
         rc = build_tables<K, AOS>(h, P, B, s);
         if (rc != IDX_OK) return rc;
         hipLaunchKernelGGL((k_part_bs<K, AOS>), span_grid(spans), dim3(kLookThreads), sizeof(K) << P.L, s,
                            make_load<K, AOS>(h), h->n, (const K *)B.q2, m, B.starts, P, (const K *)B.tab, spans, ans);
         IDX_LAUNCH_CHECK();
-    } else if (h->layout == IDX_EBS) {
+    } else if (search == Search::subtrees) {
         hipLaunchKernelGGL((k_part_ebs<K, AOS>), span_grid(spans), dim3(kLookThreads), sizeof(K) << P.L, s,
                            make_load<K, AOS>(h), h->n, h->geo.m, (const K *)B.q2, m, B.starts, P, spans, ans);
         IDX_LAUNCH_CHECK();
-    } else if (!AOS && h->layout == IDX_EKS && (node == 32 || node == 64 || node == 128)) {
+    } else if (search == Search::node_tables) {  // (keys and row IDs apart)
         const Load<K, false> A = make_load<K, false>(h);
-        hipLaunchKernelGGL(k_part_tables_eks<K>, dim3((uint32_t)((((uint64_t)P.NB << P.L) + 255) / 256)), dim3(256), 0,
-                           s, A, h->geo, P, (K *)B.tab, B.rows);
+        hipLaunchKernelGGL(k_part_tables_eks<K>, dim3((uint32_t)((P.tab + 255) / 256)), dim3(256), 0, s, A, h->geo, P,
+                           (K *)B.tab, B.rows);
         IDX_LAUNCH_CHECK();
         auto look = [&](auto kernel) {
             hipLaunchKernelGGL(kernel, span_grid(spans), dim3(kLookThreads), sizeof(K) << P.L, s, A, h->geo,
                                (const K *)B.q2, m, B.starts, P, (const K *)B.tab, (const uint32_t *)B.rows, spans, ans);
         };
-        switch (node) {
+        switch (h->geo.g * sizeof(K)) {
             case 32: look(k_part_eks<K, 2>); break;
             case 64: look(k_part_eks<K, 4>); break;
             default: look(k_part_eks<K, 8>); break;
@@ -1283,7 +1303,7 @@ int range_chunk_t(idx_index *h, const K *lo, const K *hi, uint64_t m, const Part
     out->lo = B.q2;
     out->hi = B.q2_hi;
     out->packed = (uint64_t *)B.ans;
-    out->counted = h->layout == IDX_BS;
+    out->counted = range_search(h) == Search::sorted_tables;
     if (!out->counted) return IDX_OK;
     rc = build_tables<K, AOS>(h, P, B, s);
     if (rc != IDX_OK) return rc;
@@ -1299,17 +1319,17 @@ int range_chunk_t(idx_index *h, const K *lo, const K *hi, uint64_t m, const Part
 
 // ---- the partition for range counts
 bool range_partition_pays(const idx_index *h, uint64_t m) {
-    return m >= range_part_min(h) && part_geo(h, m).NB > 1;
+    return m >= range_part_min(h) && part_geo(h, m, range_search(h)).NB > 1;
 }
 
 size_t range_partition_bytes(const idx_index *h, uint64_t m) {
-    return part_bytes(m, h->u64 ? 8 : 4, part_geo(h, m), true);
+    return part_bytes(m, h->u64 ? 8 : 4, part_geo(h, m, range_search(h)), true);
 }
 
 int range_partition(idx_index *h, const void *lo, const void *hi, uint64_t m, void *scratch, RangePart *out,
                     hipStream_t s) {
     if (m == 0 || m > kPartChunk) return IDX_ERR_ARG;
-    const PartGeo P = part_geo(h, m);
+    const PartGeo P = part_geo(h, m, range_search(h));
     char *t = (char *)scratch;
     if (h->u64)
         return h->aos ? range_chunk_t<uint64_t, true>(h, (const uint64_t *)lo, (const uint64_t *)hi, m, P, t, out, s)
@@ -1320,14 +1340,14 @@ int range_partition(idx_index *h, const void *lo, const void *hi, uint64_t m, vo
 
 int range_partition_back(const idx_index *h, const RangePart &v, void *scratch, uint64_t m, uint64_t *packed,
                          hipStream_t s) {
-    const PartGeo P = part_geo(h, m);
+    const PartGeo P = part_geo(h, m, range_search(h));
     const PartBufs B = carve((char *)scratch, m, h->u64 ? 8 : 4, P, true);
     return gather(h, B, m, P.NB, (const uint64_t *)v.packed, packed, s);
 }
 
 int point_partitioned(idx_index *h, const void *q, uint64_t m, uint32_t *out, hipStream_t s) {
     const uint64_t chunk = m < kPartChunk ? m : kPartChunk;
-    const PartGeo P = part_geo(h, chunk);
+    const PartGeo P = part_geo(h, chunk, point_search(h));
     if (m < part_min(h) || P.NB == 1) return point_run(h, PointIO{q, m, out, false, false}, s);
     const size_t kb = h->u64 ? 8 : 4;
     char *tmp = (char *)h->alloc.get(part_bytes(chunk, kb, P, false), s);

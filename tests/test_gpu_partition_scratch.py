@@ -36,3 +36,19 @@ def test_refused_scratch(layout, k):
         assert arena.refused == (1 if layout == "eks" else 2)
     torch.cuda.synchronize()
     assert not arena.blocks
+
+
+@pytest.mark.parametrize("layout,k,aos", [("ebs", 2, False), ("eks", 17, "padded"), ("learned", 1, False)])
+def test_no_tables_where_none_are_searched(layout, k, aos):
+    """Forms that search a bucket without a table in memory ask for 14 bytes a
+    64-bit query and little more."""
+    n, m = (1 << 21) + 5, 3 << 20
+    hk, hr = gen.unique_keys(gen.BASE_SEED + 961, n, 64, 63)
+    arena, keys = Arena(), to_dev(hk)
+    with arena.index(keys, to_dev(hr), "bs" if layout == "learned" else layout, k, aos) as ix:
+        if layout == "learned":
+            ix.learn(n // 64, 2)
+        ix.set_params(reorder=2)
+        arena.asked.clear()
+        ix.point(keys[torch.arange(m, device="cuda") % n])
+        assert 14 * m <= max(arena.asked) < 14 * m + (1 << 20)
