@@ -477,7 +477,7 @@ __global__ __launch_bounds__(kPartThreads) void k_part_gather(const T *__restric
                                                               const uint32_t *__restrict__ starts,
                                                               T *__restrict__ out) {
     __shared__ T s_ans[kPartTile];
-    __shared__ uint16_t s_run[kPartTile];  // bucket of every place
+    __shared__ __align__(16) uint16_t s_run[kPartTile];  // bucket of every place, eight to a 16-byte word
     __shared__ uint32_t s_off[kMaxBuckets];  // place in ans minus place in the tile
     __shared__ uint32_t s_wave[kPartThreads / kWave];
     const uint32_t tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
