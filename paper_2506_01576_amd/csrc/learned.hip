@@ -399,14 +399,18 @@ __device__ __forceinline__ void atomic_max_pos(double *p, double v) {  // values
 // their keys' terms side by side into LDS, then lanes 0-3 add one column each
 // in key order.  The sums are those of leaf_sums_thread, addition by addition,
 // at the latency of one FP64 addition a key where the walk of one thread takes
-// about 40 instructions.
+// about 40 instructions.  part[3 * blockIdx.x] as in k_leaf_train: statistics
+// added by every leaf to one place cost 13 ns an addition, 2.7 ms for 67108
+// leaves of 1000 64-bit keys that take 1.17 ms so (a thread a leaf, a pass over
+// the keys for each step and the bounds: 1.86 ms).
 template <typename K, bool AOS>
 __global__ __launch_bounds__(256) void k_leaf_train_wave(Load<K, AOS> keys, uint32_t epochs,
                                                          LeafRec *__restrict__ leaves,
                                                          const uint32_t *__restrict__ todo,
                                                          const uint32_t *__restrict__ ntodo,
-                                                         double *__restrict__ stats) {
-    __shared__ double s_term[256 / kWave][kWave][4];
+                                                         double *__restrict__ part) {
+    __shared__ double s_term[256 / kWave][kWave][4], s_part[256 / kWave][3];
+    double ws = 0.0, wmax = 0.0, ls = 0.0;
     const uint32_t lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave, count = *ntodo;
     double(*term)[4] = s_term[wave];
     for (uint32_t t = blockIdx.x * (256 / kWave) + wave; t < count; t += gridDim.x * (256 / kWave)) {
@@ -430,8 +434,11 @@ __global__ __launch_bounds__(256) void k_leaf_train_wave(Load<K, AOS> keys, uint
                 for (int c = 0; c < 4; ++c) term[lane][c] = v[c];
                 wave_lds_order();
                 if (lane < 4) {
-#pragma unroll 16
-                    for (int i = 0; i < kWave; ++i) col += term[i][lane];
+                    const uint32_t end = r.size - j0 < (uint32_t)kWave ? r.size - j0 : (uint32_t)kWave;
+                    for (uint32_t i0 = 0; i0 < end; i0 += 16) {  // (zeros past the leaf)
+#pragma unroll
+                        for (uint32_t i = 0; i < 16; ++i) col += term[i0 + i][lane];
+                    }
                 }
                 wave_lds_order();
             }
@@ -459,11 +466,28 @@ __global__ __launch_bounds__(256) void k_leaf_train_wave(Load<K, AOS> keys, uint
             r.elo = lo;
             r.ehi = hi;
             leaves[l] = r;
-            const double w = (double)hi - (double)lo + 2.0;
-            atomicAdd(&stats[0], w * r.size);
-            atomic_max_pos(&stats[1], w);
-            atomicAdd(&stats[2], loss);
         }
+        const double w = (double)hi - (double)lo + 2.0;
+        ws += w * r.size;
+        wmax = w > wmax ? w : wmax;
+        ls += loss;
+    }
+    if (lane == 0) {
+        s_part[wave][0] = ws;
+        s_part[wave][1] = wmax;
+        s_part[wave][2] = ls;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (uint32_t w = 1; w < 256 / kWave; ++w) {
+            ws += s_part[w][0];
+            wmax = s_part[w][1] > wmax ? s_part[w][1] : wmax;
+            ls += s_part[w][2];
+        }
+        double *p = part + 3 * (uint64_t)blockIdx.x;
+        p[0] = ws;
+        p[1] = wmax;
+        p[2] = ls;
     }
 }
 
@@ -673,8 +697,10 @@ int train_t(idx_index *h, uint32_t L, uint32_t epochs, uint32_t feature, hipStre
     // the model's when they win
     const uint32_t tblocks = grid_for(L, kLeafBlock);
     const size_t ctl_b = up256(sizeof(TrainCtl)), bounds_b = bounds_bytes(L);
-    const size_t acc_b = up256((size_t)L * NACC * sizeof(double)), part_b = up256((size_t)tblocks * 3 * sizeof(double));
     const uint64_t todo_n = n / (kWaveLeaf + 1) + 1;  // leaves of more than kWaveLeaf keys at most
+    const uint32_t wblocks = grid_for(todo_n, 4) < 2048 ? grid_for(todo_n, 4) : 2048;
+    const size_t acc_b = up256((size_t)L * NACC * sizeof(double));
+    const size_t part_b = up256(((size_t)tblocks + wblocks) * 3 * sizeof(double));
     char *tmp = (char *)h->alloc.get(ctl_b + bounds_b + acc_b + part_b + up256(todo_n * 4), s);
     LeafRec *alt = tmp && both ? (LeafRec *)h->alloc.get((size_t)L * sizeof(LeafRec), s) : nullptr;
     SplineBin *bins2 = tmp && want_sp ? (SplineBin *)h->alloc.get((size_t)spline_bins(n) * sizeof(SplineBin), s)
@@ -695,7 +721,6 @@ int train_t(idx_index *h, uint32_t L, uint32_t epochs, uint32_t feature, hipStre
     const uint32_t cblocks = grid_for((n + CHUNK - 1) / CHUNK, LT);
     const uint32_t lblocks = grid_for(L, 256) < 1024 ? grid_for(L, 256) : 1024;  // passes over large leaves alone
     const uint32_t cap = stage_cap(n, L);  // keys staged per workgroup of the leaf pass
-    const uint32_t wblocks = grid_for(todo_n, 4) < 2048 ? grid_for(todo_n, 4) : 2048;
 
     // Leaves under candidate c into `leaves`: first ranks, Newton steps, error
     // bounds and statistics of family f.
@@ -707,7 +732,7 @@ int train_t(idx_index *h, uint32_t L, uint32_t epochs, uint32_t feature, hipStre
         hipLaunchKernelGGL((k_leaf_train<K, AOS>), dim3(tblocks), dim3(kLeafBlock), (size_t)cap * sizeof(K), s, keys,
                            (const uint32_t *)bounds, L, epochs, leaves, leaf_acc, big, todo, &ctl->ntodo[f], cap, part);
         hipLaunchKernelGGL((k_leaf_train_wave<K, AOS>), dim3(wblocks), dim3(256), 0, s, keys, epochs, leaves, todo,
-                           &ctl->ntodo[f], ctl->stats[f]);
+                           &ctl->ntodo[f], part + 3 * (size_t)tblocks);
         for (uint32_t ep = 0; ep < epochs; ++ep) {
             hipLaunchKernelGGL((k_leaf_accum_big<K, AOS>), dim3(cblocks), dim3(LT), 0, s, keys, n, d_root, leaves,
                                leaf_acc, big);
@@ -716,8 +741,9 @@ int train_t(idx_index *h, uint32_t L, uint32_t epochs, uint32_t feature, hipStre
         hipLaunchKernelGGL((k_leaf_errors_big<K, AOS>), dim3(cblocks), dim3(LT), 0, s, keys, n, d_root, leaves, big,
                            &ctl->stats[f][2]);
         hipLaunchKernelGGL(k_leaf_stats_big, dim3(lblocks), dim3(256), 0, s, leaves, L, big, ctl->stats[f]);
-        hipLaunchKernelGGL(k_leaf_stats, dim3(grid_for(tblocks, 256) < 64 ? grid_for(tblocks, 256) : 64), dim3(256), 0,
-                           s, part, tblocks, ctl->stats[f]);
+        const uint32_t parts = tblocks + wblocks;
+        hipLaunchKernelGGL(k_leaf_stats, dim3(grid_for(parts, 256) < 64 ? grid_for(parts, 256) : 64), dim3(256), 0, s,
+                           part, parts, ctl->stats[f]);
         IDX_LAUNCH_CHECK();
         return IDX_OK;
     };
