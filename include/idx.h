@@ -315,7 +315,8 @@ typedef struct idx_lookup_params {
                             lookups, and the count phase of range lookups by their lower bounds)
                             and gather the answers back; batches too small for their index (of
                             under 3 * 2^18 in any case), those whose scratch the allocator does
-                            not give, and EKS range lookups, are looked up as they come.  Plain
+                            not give, and EKS range lookups that read nodes of up to 128 bytes
+                            by 16-byte loads, are looked up as they come.  Plain
                             BS and EBS lookups, and EKS ones on separate arrays with nodes of 32,
                             64 or 128 bytes, then search each bucket through a table in LDS and
                             use none of the launch parameters above;

@@ -74,12 +74,28 @@ inline uint64_t part_min(const idx_index *h) {
 
 // The same for range calls: BS n = 2^18 123 / 130 at 2^20 ranges, 372 / 285 at
 // 2^22; 2^20 164 / 142 and 539 / 309; EBS n = 2^18 407 / 482 at 2^22, 1554 / 1783
-// at 2^24; 2^20 174 / 193 at 2^20, 573 / 527 at 2^22.  k-ary layouts never: 2^24
-// ranges of 16 rows, n = 2^21, 2^23 and 2^26, 64-bit keys 1.85 / 1.92, 2.04 /
-// 2.08 and 2.64 / 2.48 ms, 32-bit keys 1.92 / 2.14, 1.95 / 2.34 and 2.37 / 2.72.
+// at 2^24; 2^20 174 / 193 at 2^20, 573 / 527 at 2^22.
+// k-ary counts that read whole nodes of up to 128 bytes by 16-byte loads touch
+// few lines as they come: k = 9, 64-bit keys, n = 2^26: 436 / 468 at 2^22, 1579 /
+// 1482 at 2^24; 32-bit keys 1633 / 1740; k = 17 and 5 alike.  The others pay for
+// every probe:
+//   interleaved, k = 17, 64-bit keys: n = 2^18 809 / 711 at 2^22; 2^21 704 / 479 at
+//        2^21; 2^23 431 / 261 at 3 2^18, 5816 / 3162 at 2^24; 2^26 193 / 221 at 2^18,
+//        559 / 341 at 3 2^18, 7774 / 3474 at 2^24; k = 5 n = 2^23 214 / 172 at 3 2^18;
+//        k = 3 n = 2^22 153 / 157 at 3 2^18, 302 / 242 at 2^21
+//   apart, k = 65: n = 2^20 1120 / 938 at 2^21; 2^26 747 / 586 at 3 2^18; k = 4 and 64-bit
+//        keys: n = 2^20 439 / 368 at 2^22; 2^23 189 / 181 at 2^20, 324 / 253 at 2^21;
+//        2^26 3085 / 1756 at 2^24; k = 2 and 32-bit keys: n = 2^18 923 / 1041 at 2^24;
+//        2^20 326 / 325 at 2^22; 2^22 144 / 154 at 2^20, 242 / 219 at 2^21
 inline uint64_t range_part_min(const idx_index *h) {
     const bool small = h->n < 3u << 18;
-    if (h->layout == IDX_EKS) return ~0ull;
+    if (h->layout == IDX_EKS) {
+        const uint32_t g = h->geo.g, node = g * (h->u64 ? 8 : 4);
+        const bool whole = !h->aos && g >= 4 && node % 16 == 0 && node <= 128;
+        if (small || whole) return ~0ull;
+        if (h->n < 1u << 22) return 1ull << 22;
+        return (h->aos && g >= 4) || node > 128 ? kPartMin : 1ull << 21;
+    }
     if (h->layout == IDX_EBS) return small ? ~0ull : h->n < 1u << 21 ? 3ull << 20 : kPartMin;
     return small ? 3ull << 19 : kPartMin;
 }

@@ -1,4 +1,4 @@
-"""Partitioned point lookups of every form, with batches above the sizes from
+"""Partitioned lookups of every form, with batches above the sizes from
 which a batch is partitioned at all: interleaved and padded storage, lane
 groups, launch parameters, the learned form, skewed and sorted batches, and
 k-ary trees so large that the bucket tables are cut above the last level.  That
@@ -17,7 +17,7 @@ pytest.importorskip("paper_2506_01576_amd")
 if not torch.cuda.is_available():  # pragma: no cover
     pytest.skip("no GPU", allow_module_level=True)
 
-from gpu_arena import Arena, expected_points  # noqa: E402
+from gpu_arena import Arena, expected_points, ordered  # noqa: E402
 
 N = (1 << 21) + 5
 FORMS = [
@@ -120,3 +120,40 @@ def test_nodes_below_the_table(bits, k, n):
             keys = keys % (n // 3)
         q = _mixed_batch(keys, _least("eks", n) + 3, g)
         _check(Arena(), keys, rows, "eks", k, False, {"group": 1}, 2, q, expected_points(keys, rows, q))
+
+
+@pytest.mark.parametrize("bits", [32, 64])
+@pytest.mark.parametrize("layout,k,aos,n", [
+    ("bs", 1, True, N), ("ebs", 2, True, N), ("eks", 17, "padded", 1 << 22), ("eks", 5, True, (1 << 22) + 1),
+    ("eks", 3, True, (1 << 22) + 5), ("eks", 4, False, (1 << 22) + 7), ("eks", 65, False, (1 << 22) + 9),
+    ("eks", 2, False, (1 << 22) + 11), ("eks", 9, True, (1 << 20) + 3)])
+def test_ranges(layout, k, aos, n, bits):
+    g = torch.Generator(device="cuda").manual_seed(n + bits + k)
+    dt = torch.int64 if bits == 64 else torch.int32
+    least = 3 << 18 if layout != "eks" else 1 << 22 if n < 1 << 22 else 1 << 21 if k in (2, 3, 4) else 3 << 18
+    rows = torch.randperm(n, generator=g, device="cuda").to(torch.int32)
+    for copies in (False, True):
+        keys = torch.randint(-(1 << (bits - 2)), 1 << (bits - 2), (n,), generator=g, device="cuda").to(dt)
+        if copies:
+            keys = keys % (n // 4)
+        lo = _mixed_batch(keys, least + 9, g)
+        sk, perm = torch.sort(ordered(keys), stable=True)
+        wide = torch.randint(0, 4, lo.shape, generator=g, device="cuda")
+        wide[::65537] = n // 50  # past the bucket
+        at = (torch.searchsorted(sk, ordered(lo)) + wide).clamp_(max=n - 1)
+        hi = torch.where(wide > 2, keys[perm[at]], lo + wide.to(dt))
+        hi[:3] = -1
+        lo, hi = lo[1:], hi[1:]
+        r0 = torch.searchsorted(sk, ordered(lo))
+        r1 = torch.searchsorted(sk, ordered(hi), right=True)
+        count = torch.where(ordered(lo) <= ordered(hi), (r1 - r0).clamp_(min=0), 0)
+        arena = Arena()
+        with arena.index(keys, rows, layout, k, aos) as ix:
+            ix.set_params(reorder=2)
+            arena.asked.clear()
+            off, got = ix.range(lo, hi)
+            assert max(arena.asked) > len(lo) * (2 * keys.element_size() + 10), "the batch was not partitioned"
+        assert torch.equal(off[1:] - off[:-1], count)
+        first = torch.repeat_interleave(r0 - off[:-1], count)
+        ranks = first + torch.arange(len(first), device="cuda")
+        assert torch.equal(got, rows[perm[ranks]])
