@@ -675,8 +675,10 @@ int resolve_params(const idx_index *h, const idx_lookup_params *in, idx_lookup_p
 //    110 / 122 / 129 at 2^21 lookups; EKS n = 2^23 111 / 112 / 119 at 2^21 and
 //    equal at 2^22; EBS n = 2^23 31.7 / 31.6 / 32.2 at 2^18 and 61 / 61 / 55 at
 //    2^19, pinned n = 2^16 11.9 / 11.9 / 14.9 at 2^19; BS pinned n = 2^16 14.6 /
-//    13.2 / 18.3 at 2^19, 32-bit keys 18.4 / - / 17.8 at 2^20; learned n = 2^20
-//    18.1 / 18.7 / 19.8 at 2^19, 49 / 47 / 49 at 2^21, 91 / 83 / 85 at 2^22);
+//    13.2 / 18.3 at 2^19, 32-bit keys 18.4 / - / 17.8 at 2^20; leaf lines n = 2^20
+//    18.1 / 18.7 / 19.8 at 2^19, 49 / 47 / 49 at 2^21, 91 / 83 / 85 at 2^22; window
+//    search of 64-key leaves, 32-bit keys, n = 2^26 9.3 / 10.7 / 16.2 at 2^17, 17.6 /
+//    16.8 / 18.8 at 2^18, 32.8 / 32.8 / 30.7 at 2^19, 61.3 / 67.7 / 63.2 at 2^20);
 //  - pinned levels: none up to 2^17 lookups, which do not pay for a copy per
 //    compute unit (EKS n = 2^23: 12.9 against 16.2 us at 2^17, 20.7 and 20.8 at
 //    2^18; BS n = 2^16: 8.0 and 7.6 at 2^17, 6.1 and 7.1 at 2^16);
@@ -689,8 +691,10 @@ idx_lookup_params fit_params(const idx_index *h, const PointIO &io) {
     if (io.local_sort || p.group > 1) return p;  // tiles as asked for; groups fill the lanes
     const uint64_t m = io.m;
     uint32_t most = 8;  // lookups per lane
-    if (m <= 1u << 18) most = 1;
-    else if (h->learned && p.model != 2) most = m < 1u << 20 ? 1 : m < 1u << 22 ? 2 : 8;
+    const bool model = h->learned && p.model != 2;
+    if (model && p.leaf_lines != 1 && m > 3u << 16) most = m <= 3u << 17 ? 2 : m < 1u << 20 ? 4 : 8;
+    else if (m <= 1u << 18) most = 1;
+    else if (model) most = m < 1u << 20 ? 1 : m < 1u << 22 ? 2 : 8;
     else if (h->layout == IDX_EKS || (h->layout == IDX_BS && h->n > 1u << 17)) most = m < 1u << 22 ? 1 : 8;
     else if (p.lds_levels) most = m < 1u << 19 ? 1 : m < 1u << 20 ? 2 : 8;
     if (p.per_lane > most) p.per_lane = most;
