@@ -475,7 +475,7 @@ class Batch:
             raise ValueError("a batch needs at least one index")
         self.key_bits = self._indexes[0].key_bits
         self.count = len(self._indexes)
-        self._total_seen = {}
+        self._total_seen = None
         arr = (ctypes.c_void_p * len(self._indexes))(*[ix._h.value for ix in self._indexes])
         h = ctypes.c_void_p()
         _check(lib().idx_batch_create(arr, len(self._indexes), _stream(stream), ctypes.byref(h)), "idx_batch_create")
@@ -484,12 +484,11 @@ class Batch:
     def _check_total(self, offsets: torch.Tensor, m: int, exact: bool):
         """The kernels read offsets[count] entries of the query arrays: it may
         not exceed their length (exact: must equal it).  Read once per offsets
-        tensor and version."""
-        key = (offsets.data_ptr(), offsets._version, len(offsets))
-        total = self._total_seen.get(key)
-        if total is None:
-            total = int(offsets[-1].item())
-            self._total_seen = {key: total}
+        tensor and version; the tensor is kept, so that no other is taken for it."""
+        seen = self._total_seen
+        if not seen or seen[0] is not offsets or seen[1] != offsets._version:
+            seen = self._total_seen = (offsets, offsets._version, int(offsets[-1].item()))
+        total = seen[2]
         if total > m or (exact and total != m):
             raise ValueError(f"offsets[-1] = {total} does not fit the {m} queries given")
 
