@@ -413,6 +413,7 @@ __global__ __launch_bounds__(256) void k_leaf_train_wave(Load<K, AOS> keys, uint
     double ws = 0.0, wmax = 0.0, ls = 0.0;
     const uint32_t lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave, count = *ntodo;
     double(*term)[4] = s_term[wave];
+    if (count == 0) return;  // k_leaf_stats then leaves part out
     for (uint32_t t = blockIdx.x * (256 / kWave) + wave; t < count; t += gridDim.x * (256 / kWave)) {
         const uint32_t l = todo[t];
         LeafRec r = leaves[l];
@@ -491,11 +492,13 @@ __global__ __launch_bounds__(256) void k_leaf_train_wave(Load<K, AOS> keys, uint
     }
 }
 
-// stats += the workgroups' window sums, largest window and losses.  A few
+// stats += the workgroups' window sums, largest window and losses: those of
+// k_leaf_train, then (if leaves were listed) k_leaf_train_wave's.  A few
 // workgroups, one atomic each.
-__global__ __launch_bounds__(256) void k_leaf_stats(const double *__restrict__ part, uint32_t blocks,
-                                                    double *__restrict__ stats) {
+__global__ __launch_bounds__(256) void k_leaf_stats(const double *__restrict__ part, uint32_t tblocks, uint32_t wblocks,
+                                                    const uint32_t *__restrict__ ntodo, double *__restrict__ stats) {
     double ws = 0.0, wmax = 0.0, ls = 0.0;
+    const uint32_t blocks = tblocks + (*ntodo ? wblocks : 0);
     for (uint32_t b = blockIdx.x * 256 + threadIdx.x; b < blocks; b += gridDim.x * 256) {
         ws += part[3 * (uint64_t)b];
         wmax = part[3 * (uint64_t)b + 1] > wmax ? part[3 * (uint64_t)b + 1] : wmax;
@@ -741,9 +744,9 @@ int train_t(idx_index *h, uint32_t L, uint32_t epochs, uint32_t feature, hipStre
         hipLaunchKernelGGL((k_leaf_errors_big<K, AOS>), dim3(cblocks), dim3(LT), 0, s, keys, n, d_root, leaves, big,
                            &ctl->stats[f][2]);
         hipLaunchKernelGGL(k_leaf_stats_big, dim3(lblocks), dim3(256), 0, s, leaves, L, big, ctl->stats[f]);
-        const uint32_t parts = tblocks + wblocks;
-        hipLaunchKernelGGL(k_leaf_stats, dim3(grid_for(parts, 256) < 64 ? grid_for(parts, 256) : 64), dim3(256), 0, s,
-                           part, parts, ctl->stats[f]);
+        const uint32_t sblocks = grid_for(tblocks + wblocks, 256);
+        hipLaunchKernelGGL(k_leaf_stats, dim3(sblocks < 64 ? sblocks : 64), dim3(256), 0, s, part, tblocks, wblocks,
+                           &ctl->ntodo[f], ctl->stats[f]);
         IDX_LAUNCH_CHECK();
         return IDX_OK;
     };
