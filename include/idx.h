@@ -77,8 +77,9 @@ typedef void *idx_stream;             /* hipStream_t */
  * Both must be stream-ordered with respect to `stream`: a buffer released on
  * a stream may be reused only by work enqueued after the release.  Passing
  * NULL selects hipMallocAsync / hipFreeAsync on the call's stream, with up to
- * 8 GiB of freed blocks per device kept mapped for later calls (idx_trim gives
- * them back).
+ * 8 GiB of freed blocks per device kept mapped for later calls, beside what the
+ * device's default memory pool keeps (its release threshold is raised).  They
+ * are given back when a request of any size finds no memory, and by idx_trim.
  */
 typedef struct idx_allocator {
     void *(*alloc)(void *ctx, size_t bytes, idx_stream stream);

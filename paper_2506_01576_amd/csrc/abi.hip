@@ -10,9 +10,10 @@ static thread_local int g_last_hip = 0;
 
 // The C library serves every access to a thread-local variable of any library
 // the slow way, in a thread that has not touched the most recently loaded
-// library's own since it was loaded.  That made each HIP call 30 ns and a small
-// lookup call 0.9 us slower (8.6 against 7.7 us) until the first error was kept
-// here; taking the variable's address is enough.
+// library's own since it was loaded.  While nothing on the way to a lookup
+// touched one of this library's, each HIP call took 30 ns and a small lookup
+// call 0.9 us longer (8.6 against 7.7 us); taking a variable's address is enough.
+// Threads that allocate touch one in the allocator too.
 static inline void settle_thread_locals() { asm volatile("" ::"r"(&g_last_hip)); }
 
 int hip_fail(hipError_t e) {
@@ -102,7 +103,6 @@ namespace {
 int new_handle(uint64_t n, int layout, uint32_t k, uint32_t flags, const idx_allocator *alloc, hipStream_t s,
                idx_index **out) {
     *out = nullptr;
-    settle_thread_locals();
     if (n > IDX_MAX_KEYS) return IDX_ERR_ARG;
     if (flags & ~(IDX_KEY_U64 | IDX_AOS | IDX_AOS_PADDED)) return IDX_ERR_ARG;
     if ((flags & IDX_AOS_PADDED) && !(flags & IDX_AOS)) return IDX_ERR_ARG;

@@ -1,13 +1,13 @@
 // Device memory behind the default allocator: a bounded cache of freed blocks.
 //
 // Builds, merges, training and range calls take and free buffers of up to a
-// few GiB each.  hipFreeAsync returns a block that its stream has finished
-// with to the driver when the next block is freed, whatever the pool's
-// release threshold says (measured on ROCm 7.2 with thresholds of 2^36 to
-// 2^64 - 1 bytes), so every build unmapped and mapped its temporaries again:
-// about 0.6 ms per build of 2^26 64-bit keys, and 40 ms once the driver had
-// handed out all the memory it had cleared beforehand.  Blocks freed here
-// stay mapped and serve the next request of about their size.
+// few GiB each.  The runtime's pool returned a build's freed blocks to the
+// driver when the next block was freed, also with its release threshold raised
+// (ROCm 7.2, thresholds of 2^36 to 2^64 - 1 bytes), so every build unmapped and
+// mapped its temporaries again: about 0.6 ms per build of 2^26 64-bit keys, and
+// 20 to 40 ms once the driver had handed out all the memory it had cleared
+// beforehand.  Blocks freed here stay mapped and serve the next request of
+// about their size.
 //
 // Rules:
 //   * A block carries an event recorded on the stream that freed it; the
@@ -127,10 +127,11 @@ void evict(Cache *c, int dev, hipStream_t s, bool all, std::vector<Block> &gone)
     }
 }
 
-// What the cache gives back stays in the runtime's pool, as far as the runtime
-// keeps it, instead of going to the driver at the next synchronisation (which
-// the first graph replay over a new batch of 338 handles met: 620 against 340
-// us).
+// Raises the release threshold of the runtime's pool, so that what the cache
+// gives back, and blocks too large for it, need not go to the driver at the
+// next synchronisation (which the first graph replay over a new batch of 338
+// handles met: 620 against 340 us).  How much of it the pool then keeps is the
+// runtime's choice; trim_pool empties it.
 void keep_pool() {
     static thread_local int done_dev = -1;
     int dev = 0;

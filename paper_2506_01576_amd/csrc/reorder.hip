@@ -8,9 +8,11 @@
 // requests that miss L2 run at ~55 G/s whether the Infinity Cache or HBM
 // serves them), while one XCD's 4 MiB L2 can hold the whole slice of the
 // index that a narrow key range touches, and LDS the top of its search.  So
-// the batch is partitioned -- one stable counting pass, not a sort -- into up
-// to 1024 buckets of neighbouring keys, each bucket is searched through a
-// table of its own keys in LDS, and the answers are gathered back.
+// the batch is partitioned -- one counting pass, not a sort -- into up to 1024
+// buckets of neighbouring keys, each bucket is searched through a table of its
+// own keys in LDS, and the answers are gathered back.  The order within a
+// bucket is that of LDS atomics and changes from run to run; `place` below
+// records it, and no answer depends on it.
 //
 //   1. splitters: NB - 1 index keys, in key order;
 //   2. count: per tile of kPartTile queries, the queries of every bucket (a
