@@ -180,7 +180,9 @@ int idx_load(const void *blob, uint64_t size, const idx_allocator *alloc, idx_st
  *   out_rowid  device array of m uint32: out_rowid[q] is the row ID of the
  *              first build pair (in stable sorted order) whose key equals
  *              queries[q], or IDX_MISS when there is none
- * Enqueued on `stream`, no synchronisation.  Errors: IDX_ERR_ARG, IDX_ERR_HIP.
+ * Enqueued on `stream`, no synchronisation (see idx_set_params for a first
+ * call's).  Errors: IDX_ERR_ARG, IDX_ERR_HIP, and IDX_ERR_NOMEM for a table of
+ * the handle's own.
  */
 int idx_point(idx_handle h, const void *queries, uint64_t m, uint32_t *out_rowid, idx_stream stream);
 
@@ -351,8 +353,13 @@ typedef struct idx_lookup_params {
                             in the sorted array */
 } idx_lookup_params;
 
-/* Set (p != NULL) or reset to defaults (p == NULL).  Errors: IDX_ERR_ARG for an
- * unsupported combination (the handle keeps its previous parameters). */
+/* Set (p != NULL) or reset to defaults (p == NULL).  The first lookup that
+ * needs a table of the handle's own for them (pinned levels, leaf lines asked
+ * for after training) makes it and synchronises its stream for that; under
+ * graph capture lookups do without a table that is not there, with the same
+ * answers.  Lookups in flight on other streams must be ordered before one that
+ * replaces the pinned levels.  Errors: IDX_ERR_ARG for an unsupported
+ * combination (the handle keeps its previous parameters). */
 int idx_set_params(idx_handle h, const idx_lookup_params *p);
 /* The parameters point lookups will use (defaults resolved). */
 int idx_get_params(idx_handle h, idx_lookup_params *out);

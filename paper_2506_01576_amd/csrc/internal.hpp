@@ -6,6 +6,7 @@
 
 #include <cstddef>
 #include <cstdint>
+#include <mutex>
 
 #include "../../include/idx.h"
 
@@ -79,6 +80,7 @@ struct idx_index {
     hipStream_t last_stream = nullptr;
     int cu_count = 256;
     size_t lds_max = 64 * 1024;  // LDS bytes one workgroup may use on this device
+    std::mutex lazy;             // held while a lookup makes a table of the handle's own (pin, leaf lines)
     idx::LearnedModel *learned = nullptr;  // attached rank model (BS layout only)
     // Leaf-line buffer of the model a re-training replaced, kept for the new
     // model's lines when the leaf count is the same (a fresh buffer of that

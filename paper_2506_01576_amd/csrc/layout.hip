@@ -266,6 +266,7 @@ uint32_t pin_levels_for(const idx_index *h, size_t bytes) {
 }
 
 int build_pin(idx_index *h, uint32_t levels, hipStream_t s) {
+    std::lock_guard<std::mutex> lock(h->lazy);
     if (levels == h->pin_levels_built && (levels == 0 || h->pin)) return IDX_OK;
     if (capturing(s)) return IDX_OK;
     if (h->pin) {
@@ -282,6 +283,9 @@ int build_pin(idx_index *h, uint32_t levels, hipStream_t s) {
     if (h->u64) rc = h->aos ? pin_t<uint64_t, true>(h, count, s) : pin_t<uint64_t, false>(h, count, s);
     else rc = h->aos ? pin_t<uint32_t, true>(h, count, s) : pin_t<uint32_t, false>(h, count, s);
     if (rc != IDX_OK) return rc;
+    // waited for once: the next lookup may come on another stream
+    const hipError_t e = hipStreamSynchronize(s);
+    if (e != hipSuccess) return hip_fail(e);
     h->pin_keys = count;
     h->pin_levels_built = levels;
     return IDX_OK;

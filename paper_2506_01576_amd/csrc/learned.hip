@@ -874,7 +874,6 @@ int learn(idx_index *h, uint32_t L, uint32_t epochs, uint32_t feature, hipStream
     }
     if (h->params.leaf_lines == 1) {
         rc = ensure_lines(h, s);
-        if (rc == IDX_OK && hipStreamSynchronize(s) != hipSuccess) rc = IDX_ERR_HIP;
         if (rc != IDX_OK) {
             drop_model(h, s);
             return rc;
@@ -1410,6 +1409,7 @@ __global__ __launch_bounds__(256) void k_point_lines_pair(Load<K, AOS> keys, uin
 // Write the model's leaf lines unless they are there; not under capture (the
 // leaf records' windows then serve).
 int ensure_lines(idx_index *h, hipStream_t s) {
+    std::lock_guard<std::mutex> lock(h->lazy);
     LearnedModel *M = h->learned;
     if (M->lines || capturing(s)) return IDX_OK;
     const uint32_t L = M->root.L;
@@ -1432,7 +1432,8 @@ int ensure_lines(idx_index *h, hipStream_t s) {
         if (h->aos) hipLaunchKernelGGL((k_leaf_lines<uint32_t, true>), dim3(g), dim3(256), 0, s, make_load<uint32_t, true>(h), M->leaves, L, lines);
         else hipLaunchKernelGGL((k_leaf_lines<uint32_t, false>), dim3(g), dim3(256), 0, s, make_load<uint32_t, false>(h), M->leaves, L, lines);
     }
-    if (hipGetLastError() != hipSuccess) {
+    // waited for once: the next lookup may come on another stream
+    if (hipGetLastError() != hipSuccess || hipStreamSynchronize(s) != hipSuccess) {
         h->alloc.put(lines, s);
         return IDX_ERR_HIP;
     }

@@ -709,12 +709,10 @@ idx_lookup_params fit_params(const idx_index *h, const PointIO &io) {
 int point_run(idx_index *h, const PointIO &io, hipStream_t s) {
     idx_lookup_params p = fit_params(h, io);
     if (h->learned && p.model != 2) return point_learned(h, p, io, s);
-    if (h->params.lds_levels) {
-        // made by the first call of any size, so that it is there when a larger
-        // one is captured; a capture without it pins nothing
-        const int rc = build_pin(h, h->params.lds_levels, s);
+    if (p.lds_levels) {
+        const int rc = build_pin(h, p.lds_levels, s);
         if (rc != IDX_OK) return rc;
-        if (h->pin_levels_built != h->params.lds_levels) p.lds_levels = 0;
+        if (h->pin_levels_built != p.lds_levels) p.lds_levels = 0;  // under capture, without a table
     }
     if (h->u64) return h->aos ? point_t<uint64_t, true>(h, p, io, s) : point_t<uint64_t, false>(h, p, io, s);
     return h->aos ? point_t<uint32_t, true>(h, p, io, s) : point_t<uint32_t, false>(h, p, io, s);

@@ -1,6 +1,10 @@
-"""Calls captured into a graph leave nothing in the handle that only the graph
-fills: eager calls between capture and replay, and replays over changed
-queries with eager work between them, give the generator's answers."""
+"""What a handle makes on first use (pinned levels, leaf lines) is there for
+every stream and thread.  Calls captured into a graph leave nothing in the
+handle that only the graph fills: eager calls between capture and replay, and
+replays over changed queries with eager work between them, give the
+generator's answers."""
+import threading
+
 import pytest
 import torch
 
@@ -56,3 +60,49 @@ def test_leaf_lines_asked_for_after_training(warm):
         ix.learn(N // 4, 2)
         ix.set_params(leaf_lines=1)
         _captured_point(ix, warm)
+
+
+@pytest.mark.parametrize("layout,params", [("bs", {"lds_levels": 10}), ("eks", {"lds_levels": 3}),
+                                           ("learned", {"leaf_lines": 1})])
+def test_first_use_on_a_busy_stream(layout, params):
+    """The first lookup's stream has work before it; the next lookup comes on
+    another one."""
+    keys, rows = gen.unique_keys(SEED, N, 64, 63)
+    q, want = (to_dev(a) for a in gen.point_queries(SEED, N, M, 0.7, 64, 63))
+    busy, other = torch.cuda.Stream(), torch.cuda.Stream()
+    with idx.Index(to_dev(keys), to_dev(rows), layout="bs" if layout == "learned" else layout, k=9) as ix:
+        if layout == "learned":
+            ix.learn(N // 4, 2)
+        ix.set_params(**params)
+        outs = [torch.zeros(M, dtype=torch.int32, device="cuda") for _ in range(2)]
+        torch.cuda.synchronize()
+        with torch.cuda.stream(busy):
+            torch.cuda._sleep(50_000_000)
+        for s, out in zip((busy, other), outs):
+            ix.point(q, out=out, stream=s)
+        torch.cuda.synchronize()
+        for out in outs:
+            assert torch.equal(out, want)
+
+
+@pytest.mark.parametrize("layout,params", [("bs", {"lds_levels": 10}), ("learned", {"leaf_lines": 1})])
+def test_first_use_by_several_threads(layout, params):
+    keys, rows = gen.unique_keys(SEED, N, 64, 63)
+    q, want = (to_dev(a) for a in gen.point_queries(SEED, N, M, 0.7, 64, 63))
+    for _ in range(5):
+        with idx.Index(to_dev(keys), to_dev(rows), layout="bs") as ix:
+            if layout == "learned":
+                ix.learn(N // 4, 2)
+            ix.set_params(**params)
+            streams = [torch.cuda.Stream() for _ in range(4)]
+            outs = [torch.zeros(M, dtype=torch.int32, device="cuda") for _ in streams]
+            torch.cuda.synchronize()
+            work = [threading.Thread(target=ix.point, args=(q,), kwargs={"out": o, "stream": s})
+                    for o, s in zip(outs, streams)]
+            for w in work:
+                w.start()
+            for w in work:
+                w.join()
+            torch.cuda.synchronize()
+            for out in outs:
+                assert torch.equal(out, want)
