@@ -115,8 +115,9 @@ typedef struct idx_allocator {
  *   out      receives the handle (set to NULL on failure)
  *
  * The caller's keys/rowids are only read; they may be freed once the stream
- * reaches the end of the build.  The call synchronises `stream` once, at its
- * end, to read back the reserved-rowid and duplicate-key checks.
+ * reaches the end of the build.  The call synchronises `stream` to choose the
+ * sort's form (sets of more than 8192 pairs) and at its end, to read back the
+ * reserved-rowid and duplicate-key checks.
  * Errors: IDX_ERR_ARG, IDX_ERR_RESERVED_ROWID (nothing is kept),
  * IDX_ERR_NOMEM, IDX_ERR_HIP.
  */
@@ -149,7 +150,7 @@ int idx_relayout(idx_handle src, int layout, uint32_t k, uint32_t flags, const i
  *
  *   src     an IDX_BS index with SoA layout (IDX_ERR_ARG otherwise); unchanged
  *   keys, rowids   m new pairs (device), key width as in flags
- * Synchronises `stream` once.  Errors as idx_build (IDX_ERR_RESERVED_ROWID
+ * Synchronises `stream` as idx_build does.  Errors as idx_build (IDX_ERR_RESERVED_ROWID
  * for a new rowid equal to IDX_MISS).
  */
 int idx_merge(idx_handle src, const void *keys, const uint32_t *rowids, uint64_t m, int layout, uint32_t k,
