@@ -77,9 +77,11 @@ typedef void *idx_stream;             /* hipStream_t */
  * Both must be stream-ordered with respect to `stream`: a buffer released on
  * a stream may be reused only by work enqueued after the release.  Passing
  * NULL selects hipMallocAsync / hipFreeAsync on the call's stream, with up to
- * 8 GiB of freed blocks per device kept mapped for later calls, beside what the
- * device's default memory pool keeps (its release threshold is raised).  They
- * are given back when a request of any size finds no memory, and by idx_trim.
+ * 8 GiB of freed blocks per device kept mapped for later calls (8 GiB more when
+ * both the null stream and others are used), beside what the device's default
+ * memory pool keeps (its release threshold is raised).  They are given back when
+ * a request of any size finds no memory, and by idx_trim, which has to come
+ * before a reset of the device.
  */
 typedef struct idx_allocator {
     void *(*alloc)(void *ctx, size_t bytes, idx_stream stream);

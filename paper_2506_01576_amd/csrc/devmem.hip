@@ -17,10 +17,12 @@
 //     blocks): calls on the null stream alone take it again or give it back.
 //     A call on another stream does no work on the null stream, which would
 //     break a capture that any thread has under way.
-//   * At most kCacheBytes and kCacheBlocks idle blocks are kept per device;
-//     a block not taken again within kCacheAge requests is given back to the
-//     runtime's pool, and all idle blocks are, through it, to the driver when
-//     an allocation of any size fails, or on request (cached_trim).
+//   * At most kCacheBytes and kCacheBlocks idle blocks are kept per device, of
+//     those that a call reaches (twice that in all, where the null stream's are
+//     not used again while other streams work); a block not taken again within
+//     kCacheAge requests is given back to the runtime's pool, and all idle
+//     blocks are, through it, to the driver when an allocation of any size
+//     fails, or on request (cached_trim).
 //   * A stream under graph capture bypasses the cache: its allocations and
 //     frees become graph nodes, as without it.
 #include <mutex>
@@ -103,16 +105,10 @@ void give_back(Cache *c, const std::vector<Block> &gone, hipStream_t s) {
 // Whether a call on stream s of device dev may take b or give it back.
 bool reach(const Block &b, int dev, hipStream_t s) { return b.dev == dev && (!b.on_null || s == nullptr); }
 
-// Moves device dev's idle blocks that are beyond the bounds (all: every one)
-// from the cache to `gone`, as far as a call on s reaches them; the others
-// count first, so that the bounds hold.
+// Moves the idle blocks beyond the bounds (all: every one), of those that a call
+// on stream s of device dev reaches, from the cache to `gone`.
 void evict(Cache *c, int dev, hipStream_t s, bool all, std::vector<Block> &gone) {
     size_t bytes = 0, blocks = 0;
-    for (const Block &b : c->idle)
-        if (b.dev == dev && !reach(b, dev, s)) {
-            bytes += b.bytes;
-            ++blocks;
-        }
     for (size_t i = c->idle.size(); i-- > 0;) {  // newest first
         const Block &b = c->idle[i];
         if (!reach(b, dev, s)) continue;

@@ -187,7 +187,7 @@ void order() {
                 ++n;
             }
         for (auto &h : held) live -= g_mem[(char *)h.p].bytes;
-        if (live > (8ull << 30) || n - held.size() > 256) return wrong("more idle memory than the cache's bounds");
+        if (live > 2 * (8ull << 30) || n - held.size() > 2 * 256) return wrong("more idle memory than the cache's bounds");
     }
 }
 
@@ -285,10 +285,23 @@ void other_device() {
     if (!get(3 * MiB, S0)) wrong("no memory");
 }
 
+// What the null stream left idle does not push out another stream's blocks.
+void null_left_idle() {
+    std::vector<void *> p;
+    for (int i = 0; i < 8; ++i) p.push_back(get((900 + 30 * i) * MiB, S0));
+    for (void *q : p) put(q, S0);
+    void *mine = get(3000 * MiB, SA);
+    for (int i = 0; i < 5; ++i) {
+        put(mine, SA);
+        if (get(3000 * MiB, SA) != mine) return wrong("a stream's own block was not kept");
+    }
+}
+
 struct Scenario { const char *name; void (*run)(); };
 const Scenario kAll[] = {{"order", order}, {"capture_elsewhere", capture_elsewhere},
                          {"failed_wait", failed_wait}, {"memory_short", memory_short},
-                         {"trim", trim}, {"other_device", other_device}};
+                         {"trim", trim}, {"other_device", other_device},
+                         {"null_left_idle", null_left_idle}};
 
 }  // namespace
 

@@ -20,7 +20,7 @@ def model(tmp_path_factory):
 
 
 @pytest.mark.parametrize("scenario", ["order", "capture_elsewhere", "failed_wait", "memory_short", "trim",
-                                      "other_device"])
+                                      "other_device", "null_left_idle"])
 def test_devmem_model(model, scenario):
     r = subprocess.run([model, scenario], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0, r.stdout
